@@ -16,8 +16,9 @@ synchronization and timed with HIP events on the library's stream.
 
 Also in the one JSON line:
   dense / speedup_cp_vs_dense   the G-ROM beside it
-  roofline      dense contraction kernel (HBM-bound): algorithmic bytes N^3*4 per launch
-                over its event-timed average duration, against 8 TB/s
+  roofline      dense contraction kernel (HBM-bound): algorithmic bytes per launch (one word
+                per row and unordered pair j, k: N^2 (N + 1) / 2 words; N^3 in BF16) over its
+                event-timed average duration, against 8 TB/s
   roofline_cp   one CP step through the per-step kernels (resident runs off): N R + 1.5 R N
                 operator words and the FP64 Hinv_3 (8 N^2 bytes) against 8 TB/s
   resident      the headline's own path: the CP step with its operator resident in LDS
@@ -67,6 +68,12 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "bf16x3": 2500.0, "fp32": 157.3, "fp64": 78.
 ELEM_BYTES = {"fp64": 8, "fp32": 4, "bf16": 2, "bf16x3": 4}
 
 
+def dense_words(N, dtype):
+    """Tensor words the dense contraction needs: one per unordered pair j, k and row (the sum
+    of the two entries that meet the same u_j u_k); in BF16 every entry, rounded for itself."""
+    return float(N) ** 3 if dtype == "bf16" else float(N) * N * (N + 1) / 2
+
+
 def parse():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -99,6 +106,7 @@ CSRC = os.path.join(ROOT, "paper_2311_03694_amd", "csrc")
 # while their combined hash is unchanged)
 KERNEL_SOURCES = {
     "dense_gemv": ["k_dense1.hip", "kdot.h", "kcommon.h", "rom_dev.h"],
+    "fold_gemv": ["k_fold.hip", "kfold.h", "kdot.h", "kcommon.h", "rom_dev.h"],
     "kr": ["k_kr.hip", "kmfma.h", "kcommon.h", "rom_dev.h"],
 }
 
@@ -305,7 +313,7 @@ def main():
         es = ELEM_BYTES[dt]
         cp_rate = K / t_cp
         d_rate = Kd / t_d
-        d_bytes = float(N) ** 3 * es
+        d_bytes = dense_words(N, dt) * es
         # one CP step with a dense stiffness: the scatter reads Af [N][R]; the Helmholtz
         # kernel reads Hinv_k [N][N] (FP64) and the projection operator [B|C]^T Hinv_k,
         # 1.5R rows in the pair form (2R in the general form) of N values
@@ -363,10 +371,11 @@ def main():
             "cp_form": "pair form of skew column pairs (Sec. 3.3)" if cp_form else "general",
             "cp_general": None if t_gen is None else {"value": K / t_gen, "unit": "trajectory-steps/s",
                                                       "ms_per_step": t_gen / K * 1e3},
-            "roofline": {"bound": "hbm", "kernel": "k_dense_gemv (dense contraction, one trajectory)",
+            "roofline": {"bound": "hbm", "kernel": ("k_dense_gemv" if dt == "bf16" else "k_fold_gemv") +
+                                   " (dense contraction, one trajectory)",
                          "achieved": d_bytes / d_kernel / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": d_bytes / d_kernel / 1e9 / HBM_PEAK_GBS,
-                         "traffic": _traffic(f"dense_gemv_n{N}_{dt}", "dense_gemv"),
+                         "traffic": _traffic(f"fold_gemv_n{N}_{dt}", "fold_gemv"),
                          "avg_launch_us": d_kernel * 1e6, "algorithmic_bytes": d_bytes},
             "roofline_cp": {"bound": "hbm", "kernel": "one CP step through the per-step kernels: k_cp_scatter1 "
                                                       "(right-hand side) + k_helm_proj (Helmholtz apply and next "
@@ -422,11 +431,11 @@ def main():
                         checks.add("batched", f"B{B}_{bdt}_{name}_traj{b}", prob, ops, u0[b], nchk, ug[b], dtype=bdt)
                     if dense:
                         tk = kernel_avg(rom, u0, 10)
-                        fl = 2.0 * N ** 3 * B
+                        fl = 2.0 * dense_words(N, bdt) * B
                         entry[name]["contraction_us"] = tk * 1e6
                         entry[name]["tflops"] = fl / tk / 1e12
                         entry[name]["mfma_frac"] = fl / tk / 1e12 / MFMA_PEAK_TFLOPS[bdt]
-                        entry[name]["hbm_frac"] = N ** 3 * ELEM_BYTES[bdt] / tk / 1e9 / HBM_PEAK_GBS
+                        entry[name]["hbm_frac"] = dense_words(N, bdt) * ELEM_BYTES[bdt] / tk / 1e9 / HBM_PEAK_GBS
                     s.close()
                     rom.close()
                 entry["speedup_cp_vs_dense"] = entry["cp"]["traj_steps_per_s"] / entry["dense"]["traj_steps_per_s"]
@@ -448,7 +457,7 @@ def main():
             tune.apply(rom, 256, dense=True, table=tiles)
             s, t = step_rate(rom, p2.u0, 50, 5)
             tk = kernel_avg(rom, p2.u0, 10)
-            fl = 2.0 * 400 ** 3 * 256 * (3 if bdt == "bf16x3" else 1)
+            fl = 2.0 * dense_words(400, bdt) * 256 * (3 if bdt == "bf16x3" else 1)
             c2[f"dense_{bdt}"] = {"traj_steps_per_s": 50 * 256 / t, "us_per_step": t / 50 * 1e6,
                                   "contraction_us": tk * 1e6, "tflops": fl / tk / 1e12,
                                   "mfma_frac": fl / tk / 1e12 / MFMA_PEAK_TFLOPS[bdt]}

@@ -1,7 +1,9 @@
-// k_dense1.hip -- dense advection contraction for one trajectory (Sec. 2.2, eq. Cu;
-// the 2N^3-flop term of the G-ROM):
+// k_dense1.hip -- dense advection contraction for one trajectory in the BF16 format (Sec.
+// 2.2, eq. Cu; the 2N^3-flop term of the G-ROM; the other formats contract the folded
+// tensor, k_fold.hip):
 //     y_i = sum_j u_j * sum_k C[i][j][k] u_k,
-// and, with J slabs of separate weights w, the second product of the SVD-ROM (Sec. 4.4)
+// and in every format, with J slabs of separate weights w, the second product of the SVD-ROM
+// (Sec. 4.4)
 //     y_i = sum_r w_r * sum_k V[i][r][k] u_k   (w_r = sigma_r U[:,r]^T u).
 //
 // The tensor is stored [N][N][Np] with the k index padded by zeros to Np, a multiple

@@ -3,8 +3,9 @@
 //
 //   Y[b][i] = sum_j S[j][b] Z_j[b][i],   Z_j[b][i] = sum_k C[i][j][k] X[b][k],
 //
-// X = u in the contraction format, S = u in the accumulation format (for BF16 the
-// BF16-rounded value, so both positions see the same coefficient).  Over a fixed
+// for the BF16 format, which rounds every tensor entry for itself (the other formats
+// contract the folded tensor, k_fold.hip): X = u in BF16, S = the BF16-rounded u in FP32, so
+// both positions see the same coefficient.  Over a fixed
 // k-range the MFMA operand built from X does not depend on j: a wavefront loads its X
 // fragments once, keeps them in registers and streams the slabs C[i][j][k-range] of
 // its j's through a prefetch ring, so the inner loop reads only the tensor (each
@@ -19,8 +20,7 @@
 // walk one contiguous region.
 //
 // Block = 4 wavefronts over 16 rows i, 16*FN trajectories, a range of j and one
-// k-chunk of at most 4 KW fragment steps (a step is one 16-byte lane vector: 32 k in
-// BF16, 16 in FP32, 8 in FP64); wavefront w owns the w-th quarter of the chunk's steps
+// k-chunk of at most 4 KW fragment steps (a step is one 16-byte lane vector, 32 k); wavefront w owns the w-th quarter of the chunk's steps
 // and all wavefronts walk the same consecutive j's, so for each j the block reads one
 // contiguous run of every row (and, when the chunk spans the row, consecutive j's are
 // contiguous too: the tensor streams as in the single-trajectory kernel).  Column c16
@@ -46,14 +46,14 @@ typedef __attribute__((address_space(3))) void* lptr_t;   // LDS pointer
 
 struct KrArgs {
     const void* C;                 // tiled [ceil(M/16)][J][Kt/VEC][16][VEC], storage format
-    const unsigned short* Clo;     // BF16X3 low words of C, same layout
-    const void* X;                 // [Bpad][Kx] coefficients in the MFMA operand format
-    const unsigned short* Xlo;     // BF16X3 low words of X
-    const void* S;                 // [J][Bpad] j-weights (FP64 for MK_F64, else FP32)
-    void* part;                    // [nsplit][Bpad][M] partial tiles (accumulation type)
+    const void* X;                 // [Bpad][Kx] BF16 coefficients
+    const void* S;                 // [J][Bpad] FP32 j-weights
+    void* part;                    // [nsplit][Bpad][M] FP32 partial tiles
     int M, J, Kt, Kx, Bpad;
     int ksteps, nkc, jc, njr, gx, gy;
 };
+
+constexpr u32x4 kNoLow = {0u, 0u, 0u, 0u};           // mfma_step's low words: none in BF16
 
 // FN consecutive values from LDS (16-byte reads where the row allows them).
 template <int FN, class Acc>
@@ -73,16 +73,15 @@ __device__ __forceinline__ void lds_row(const Acc* p, Acc (&v)[FN]) {
     }
 }
 
-template <int ADT, int MKD, int FN, int KW, int PF>
+template <int FN, int KW, int PF>
 __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
-    typedef MfmaT<MKD> Tr;
-    typedef typename Tr::X XT;
-    typedef typename Tr::Acc Acc;
-    typedef typename Tr::Acc4 Acc4;
-    typedef typename Store<ADT>::T AT;
+    typedef MfmaT<MK_BF16> Tr;
+    typedef Tr::X XT;
+    typedef Tr::Acc Acc;
+    typedef Tr::Acc4 Acc4;
+    typedef Store<DT_BF16>::T AT;
     constexpr int KS = Tr::KS, VEC = Tr::VEC, NC = 16 * FN;
     constexpr int EV = 16 / (int)sizeof(Acc);
-    constexpr bool X3 = (MKD == MK_BF16X3);
     static_assert(1024 % (NC * (int)sizeof(Acc)) == 0, "a j-weight row must divide a 1 KB chunk");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     Acc* sl = reinterpret_cast<Acc*>(smem);              // [jn + 1][NC] j-weights, row jn zero
@@ -155,7 +154,7 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
 
     // ---- X fragments of the chunk for the lane's trajectories, zero past Kp, Bpad or
     // the chunk's last step (addresses clamped, zero selection after the barrier)
-    u32x4 xh[KW][FN], xl[KW][FN];
+    u32x4 xh[KW][FN];
     unsigned xok = 0;
 #pragma unroll
     for (int s = 0; s < KW; ++s)
@@ -166,8 +165,6 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
             if (s < ns && k < p.Kx && b < p.Bpad) xok |= 1u << (s * FN + t);
             const size_t o = (size_t)(b < p.Bpad ? b : p.Bpad - 1) * p.Kx + (k < p.Kx ? k : p.Kx - VEC);
             xh[s][t] = ld_plain<16>(reinterpret_cast<const XT*>(p.X) + o);
-            if constexpr (X3) xl[s][t] = ld_plain<16>(p.Xlo + o);
-            else xl[s][t] = u32x4{0u, 0u, 0u, 0u};
         }
 
     // The copies above must land before any wavefront reads the j-weights; the
@@ -178,17 +175,14 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
     for (int s = 0; s < KW; ++s)
 #pragma unroll
         for (int t = 0; t < FN; ++t)
-            if (!((xok >> (s * FN + t)) & 1u)) {
-                xh[s][t] = u32x4{0u, 0u, 0u, 0u};
-                xl[s][t] = u32x4{0u, 0u, 0u, 0u};
-            }
+            if (!((xok >> (s * FN + t)) & 1u)) xh[s][t] = u32x4{0u, 0u, 0u, 0u};
 
     // Prefetch ring of PF iterations (one j each).  The loop body has no branches and
     // its loads are never predicated (issues past the last j repeat it, steps past the
     // wavefront's last step repeat that step), so the compiler counts them exactly and
     // waits only for the slot it consumes.  Padding iterations up to a multiple of PF
     // take the zero j-weight row.
-    u32x4 ah[PF][KW], al[PF][KW];
+    u32x4 ah[PF][KW];
     int qp = 0;
     auto issue = [&](int d) {
         const int q = qp < nq ? qp : nq - 1;
@@ -197,7 +191,6 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
         for (int s = 0; s < KW; ++s) {
             const size_t os = o + (size_t)(s < nsa ? s : nsa - 1) * sstep;
             ah[d][s] = ld_plain<16>(reinterpret_cast<const AT*>(p.C) + os);
-            if constexpr (X3) al[d][s] = ld_plain<16>(p.Clo + os);
         }
         ++qp;
     };
@@ -236,7 +229,7 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
 #pragma unroll
                 for (int s = 0; s < NSC; ++s)
 #pragma unroll
-                    for (int t = 0; t < FN; ++t) mfma_step<MKD>(Z[t], ah[d][s], al[d][s], xh[s][t], xl[s][t]);
+                    for (int t = 0; t < FN; ++t) mfma_step<MK_BF16>(Z[t], ah[d][s], kNoLow, xh[s][t], kNoLow);
 #pragma unroll
                 for (int t = 0; t < FN; ++t) Y[t] += sv[t] * Z[t];
                 issue(d);
@@ -265,8 +258,7 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
     for (int e = threadIdx.x; e < 256 * FN; e += 256) {
         const int cl = e >> 4, rr = e & 15;              // local trajectory, local row
         const int t = cl % FN, cc = cl / FN;
-        const int gg = MKD == MK_F64 ? (rr & 3) : (rr >> 2);
-        const int v = MKD == MK_F64 ? (rr >> 2) : (rr & 3);
+        const int gg = rr >> 2, v = rr & 3;
         const int ln = gg * 16 + cc;
         Acc sum = red[(t * 4 + v) * 64 + ln];
 #pragma unroll
@@ -278,69 +270,39 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
 
 // ---------------------------------------------------------------- variants and plans
 
-// Per arithmetic kind: trajectories per block / 16 (FN), fragment steps per wavefront
+// Trajectories per block / 16 (FN), fragment steps per wavefront
 // (KW), prefetch depth in j's (PF) and the number of blocks the device runs at once
 // with this shape (256 CUs x blocks per CU), which the j-split is planned against.
 struct KrTile { int fn, kw, pf, slots; };
 constexpr int kKrVariants = 8;
-template <int MKD> struct KrTab;
-template <> struct KrTab<MK_F64> {
-    static constexpr KrTile t[kKrVariants] = {{4, 4, 3, 256}, {4, 4, 3, 512}, {8, 2, 3, 256}, {4, 2, 4, 512},
-                                              {2, 4, 3, 256}, {2, 8, 2, 256}, {1, 8, 3, 256}, {1, 4, 4, 512}};
-};
-template <> struct KrTab<MK_F32> {
-    static constexpr KrTile t[kKrVariants] = {{8, 4, 3, 256}, {8, 4, 3, 512}, {16, 2, 3, 256}, {4, 8, 3, 256},
-                                              {4, 8, 3, 512}, {8, 2, 4, 512}, {2, 8, 3, 256}, {1, 8, 4, 256}};
-};
-template <> struct KrTab<MK_BF16> {
-    static constexpr KrTile t[kKrVariants] = {{16, 2, 6, 256}, {4, 4, 5, 512}, {8, 4, 4, 256}, {4, 4, 3, 512},
-                                              {8, 2, 6, 512},  {2, 4, 4, 512},  {4, 4, 4, 512}, {1, 8, 4, 256}};
-};
-template <> struct KrTab<MK_BF16X3> {
-    static constexpr KrTile t[kKrVariants] = {{8, 2, 4, 256}, {8, 2, 4, 512}, {16, 1, 6, 256}, {4, 4, 4, 256},
-                                              {4, 4, 4, 512}, {4, 2, 6, 512}, {2, 4, 4, 256}, {1, 4, 4, 256}};
-};
-
-static int mk_of_dt(int dt) { return dt == DT_F64 ? MK_F64 : dt == DT_F32 ? MK_F32 : dt == DT_BF16 ? MK_BF16 : MK_BF16X3; }
-
-static KrTile kr_tile(int mk, int v) {
-    switch (mk) {
-        case MK_F64: return KrTab<MK_F64>::t[v];
-        case MK_F32: return KrTab<MK_F32>::t[v];
-        case MK_BF16: return KrTab<MK_BF16>::t[v];
-        default: return KrTab<MK_BF16X3>::t[v];
-    }
-}
+constexpr KrTile kKrTiles[kKrVariants] = {{16, 2, 6, 256}, {4, 4, 5, 512}, {8, 4, 4, 256}, {4, 4, 3, 512},
+                                          {8, 2, 6, 512},  {2, 4, 4, 512}, {4, 4, 4, 512}, {1, 8, 4, 256}};
 
 int kr_variants() { return kKrVariants; }
 
 // Default variant: the first one (in order of preference) whose column tile does not
 // exceed the padded batch.
-static int kr_default(int mk, int Bpad) {
+static int kr_default(int Bpad) {
     const int nct = Bpad / 16;
     for (int v = 0; v < kKrVariants; ++v)
-        if (kr_tile(mk, v).fn <= nct) return v;
+        if (kKrTiles[v].fn <= nct) return v;
     return kKrVariants - 1;
 }
 
-int kr_tiled_k(int dt, int N) {
-    const int KS = dt == DT_F64 ? 8 : dt == DT_F32 ? 16 : 32;
-    return (N + KS - 1) / KS * KS;
-}
+constexpr int kKrStep = 32;        // k per fragment step
+int kr_tiled_k(int N) { return (N + kKrStep - 1) / kKrStep * kKrStep; }
 
-KrPlan kr_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
-    const int mk = mk_of_dt(dt);
-    if (v < 0 || v >= kKrVariants) v = kr_default(mk, Bpad);
-    const KrTile t = kr_tile(mk, v);
+KrPlan kr_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
+    if (v < 0 || v >= kKrVariants) v = kr_default(Bpad);
+    const KrTile t = kKrTiles[v];
     KrPlan pl{};
     pl.v = v;
     pl.fn = t.fn;
     pl.kw = t.kw;
     pl.pf = t.pf;
-    const int KS = mk == MK_F64 ? 8 : mk == MK_F32 ? 16 : 32;
-    const size_t accb = mk == MK_F64 ? 8 : 4;
+    const size_t accb = 4;
     const int NC = 16 * t.fn;
-    pl.ksteps = Kt / KS;
+    pl.ksteps = Kt / kKrStep;
     pl.nkc = (pl.ksteps + 4 * t.kw - 1) / (4 * t.kw);
     pl.gx = (M + 15) / 16;
     pl.gy = (Bpad + NC - 1) / NC;
@@ -375,44 +337,42 @@ KrPlan kr_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
     return pl;
 }
 
-template <int ADT, int MKD, int V>
+template <int V>
 static void kr_go_v(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
-    constexpr KrTile t = KrTab<MKD>::t[V];
-    hipLaunchKernelGGL((k_kr<ADT, MKD, t.fn, t.kw, t.pf>), dim3(pl.blocks), dim3(256), pl.lds, s, a);
+    constexpr KrTile t = kKrTiles[V];
+    hipLaunchKernelGGL((k_kr<t.fn, t.kw, t.pf>), dim3(pl.blocks), dim3(256), pl.lds, s, a);
 }
 
-template <int ADT, int MKD, int V>
+template <int V>
 static hipError_t kr_attr_v(size_t lds) {
-    constexpr KrTile t = KrTab<MKD>::t[V];
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_kr<ADT, MKD, t.fn, t.kw, t.pf>),
+    constexpr KrTile t = kKrTiles[V];
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_kr<t.fn, t.kw, t.pf>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-template <int ADT, int MKD>
 static void kr_go(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
     switch (pl.v) {
-        case 0: kr_go_v<ADT, MKD, 0>(a, pl, s); break;
-        case 1: kr_go_v<ADT, MKD, 1>(a, pl, s); break;
-        case 2: kr_go_v<ADT, MKD, 2>(a, pl, s); break;
-        case 3: kr_go_v<ADT, MKD, 3>(a, pl, s); break;
-        case 4: kr_go_v<ADT, MKD, 4>(a, pl, s); break;
-        case 5: kr_go_v<ADT, MKD, 5>(a, pl, s); break;
-        case 6: kr_go_v<ADT, MKD, 6>(a, pl, s); break;
-        default: kr_go_v<ADT, MKD, 7>(a, pl, s); break;
+        case 0: kr_go_v<0>(a, pl, s); break;
+        case 1: kr_go_v<1>(a, pl, s); break;
+        case 2: kr_go_v<2>(a, pl, s); break;
+        case 3: kr_go_v<3>(a, pl, s); break;
+        case 4: kr_go_v<4>(a, pl, s); break;
+        case 5: kr_go_v<5>(a, pl, s); break;
+        case 6: kr_go_v<6>(a, pl, s); break;
+        default: kr_go_v<7>(a, pl, s); break;
     }
 }
 
-template <int ADT, int MKD>
 static hipError_t kr_attr(size_t lds) {
     hipError_t e = hipSuccess, q;
-    if ((q = kr_attr_v<ADT, MKD, 0>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 1>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 2>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 3>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 4>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 5>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 6>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr_v<ADT, MKD, 7>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<0>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<1>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<2>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<3>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<4>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<5>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<6>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr_v<7>(lds)) != hipSuccess) e = q;
     return e;
 }
 
@@ -420,26 +380,21 @@ hipError_t krs_set_lds_limit(size_t lds);
 
 hipError_t kr_set_lds_limit(size_t lds) {
     hipError_t e = hipSuccess, q;
-    if ((q = kr_attr<DT_F64, MK_F64>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr<DT_F32, MK_F32>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr<DT_BF16, MK_BF16>(lds)) != hipSuccess) e = q;
-    if ((q = kr_attr<DT_BF16X3, MK_BF16X3>(lds)) != hipSuccess) e = q;
+    if ((q = kr_attr(lds)) != hipSuccess) e = q;
     if ((q = krs_set_lds_limit(lds)) != hipSuccess) e = q;
     return e;
 }
 
-void launch_kr_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_lo, int N, int Np, int Bpad,
-                     const void* X, const void* Xlo, const void* S, void* part, hipStream_t s) {
+static KrArgs kr_args(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, const void* X, const void* S,
+                      void* part) {
     KrArgs a{};
     a.C = Ct;
-    a.Clo = (const unsigned short*)Ct_lo;
     a.X = X;
-    a.Xlo = (const unsigned short*)Xlo;
     a.S = S;
     a.part = part;
     a.M = N;
     a.J = N;
-    a.Kt = kr_tiled_k(dt, N);
+    a.Kt = kr_tiled_k(N);
     a.Kx = Np;
     a.Bpad = Bpad;
     a.ksteps = pl.ksteps;
@@ -448,12 +403,12 @@ void launch_kr_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_lo
     a.njr = pl.njr;
     a.gx = pl.gx;
     a.gy = pl.gy;
-    switch (dt) {
-        case DT_F64: kr_go<DT_F64, MK_F64>(a, pl, s); break;
-        case DT_F32: kr_go<DT_F32, MK_F32>(a, pl, s); break;
-        case DT_BF16: kr_go<DT_BF16, MK_BF16>(a, pl, s); break;
-        default: kr_go<DT_BF16X3, MK_BF16X3>(a, pl, s); break;
-    }
+    return a;
+}
+
+void launch_kr_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, const void* X, const void* S, void* part,
+                     hipStream_t s) {
+    kr_go(kr_args(pl, Ct, N, Np, Bpad, X, S, part), pl, s);
 }
 
 // ---------------------------------------------------------------- shared-tile variant
@@ -472,37 +427,23 @@ void launch_kr_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_lo
 // part[split][b][i] like k_kr.
 struct KrsTile { int fn, kc, p; };
 constexpr int kKrsVariants = 4;
-template <int MKD> struct KrsTab;
-template <> struct KrsTab<MK_F64> {
-    static constexpr KrsTile t[kKrsVariants] = {{2, 7, 3}, {2, 8, 2}, {2, 4, 3}, {1, 8, 3}};
-};
-template <> struct KrsTab<MK_F32> {
-    static constexpr KrsTile t[kKrsVariants] = {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}};
-};
-template <> struct KrsTab<MK_BF16> {
-    static constexpr KrsTile t[kKrsVariants] = {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}};
-};
-template <> struct KrsTab<MK_BF16X3> {
-    static constexpr KrsTile t[kKrsVariants] = {{4, 3, 2}, {2, 7, 2}, {2, 4, 3}, {2, 8, 2}};
-};
+constexpr KrsTile kKrsTiles[kKrsVariants] = {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}};
 
-template <int ADT, int MKD, int FN, int KC, int P>
+template <int FN, int KC, int P>
 __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
-    typedef MfmaT<MKD> Tr;
-    typedef typename Tr::X XT;
-    typedef typename Tr::Acc Acc;
-    typedef typename Tr::Acc4 Acc4;
-    typedef typename Store<ADT>::T AT;
+    typedef MfmaT<MK_BF16> Tr;
+    typedef Tr::X XT;
+    typedef Tr::Acc Acc;
+    typedef Tr::Acc4 Acc4;
+    typedef Store<DT_BF16>::T AT;
     constexpr int KS = Tr::KS, VEC = Tr::VEC;
     constexpr int NCW = 16 * FN, NCB = 4 * NCW;          // columns per wavefront, per block
     constexpr int EV = 16 / (int)sizeof(Acc);
-    constexpr bool X3 = (MKD == MK_BF16X3);
-    constexpr int NH = X3 ? 2 : 1;                       // A words per element
-    constexpr int SLOT = 2 * KC * 1024 * NH;             // bytes of one ring slot
+    constexpr int SLOT = 2 * KC * 1024;                  // bytes of one ring slot
     static_assert(1024 % (NCB * (int)sizeof(Acc)) == 0 || (NCB * (int)sizeof(Acc)) % 1024 == 0,
                   "j-weight rows and 1 KB chunks must nest");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    char* ring = smem;                                   // [2 slots][hi, lo][2 parities][KC][1 KB]
+    char* ring = smem;                                   // [2 slots][2 parities][KC][1 KB]
     Acc* sl = reinterpret_cast<Acc*>(smem + 2 * SLOT);   // [jn + 1][NCB] j-weights, row jn zero
 
     const int nwork = p.gx * p.gy * p.nkc * p.njr;
@@ -550,7 +491,7 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
     }
 
     // ---- X fragments of the wavefront's columns over the chunk
-    u32x4 xh[KC][FN], xl[KC][FN];
+    u32x4 xh[KC][FN];
     unsigned long long xok = 0;
 #pragma unroll
     for (int s = 0; s < KC; ++s)
@@ -561,18 +502,13 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
             if (s < cs && k < p.Kx && b < p.Bpad) xok |= 1ull << (s * FN + t);
             const size_t o = (size_t)(b < p.Bpad ? b : p.Bpad - 1) * p.Kx + (k < p.Kx ? k : p.Kx - VEC);
             xh[s][t] = ld_plain<16>(reinterpret_cast<const XT*>(p.X) + o);
-            if constexpr (X3) xl[s][t] = ld_plain<16>(p.Xlo + o);
-            else xl[s][t] = u32x4{0u, 0u, 0u, 0u};
         }
     __syncthreads();                                     // j-weights published
 #pragma unroll
     for (int s = 0; s < KC; ++s)
 #pragma unroll
         for (int t = 0; t < FN; ++t)
-            if (!((xok >> (s * FN + t)) & 1ull)) {
-                xh[s][t] = u32x4{0u, 0u, 0u, 0u};
-                xl[s][t] = u32x4{0u, 0u, 0u, 0u};
-            }
+            if (!((xok >> (s * FN + t)) & 1ull)) xh[s][t] = u32x4{0u, 0u, 0u, 0u};
 
     // ---- the two tensor slabs of an iteration: fragment f = par * cs + s (step s of
     // j = 2 it + par); wavefront w carries fragments w and w + 8.  Loads are
@@ -594,13 +530,12 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
         j = j < jn ? j : jn - 1;
         return ((((size_t)bx * p.J + jbeg + j) * nku + (size_t)(c0 + fs[h]) * 4) * 16) * VEC + (size_t)lane * VEC;
     };
-    u32x4 rs[P][2], rl[P][2];
+    u32x4 rs[P][2];
     auto gload = [&](int it, int st) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const size_t o = goff(it, h);
             rs[st][h] = ld_plain<16>(reinterpret_cast<const AT*>(p.C) + o);
-            if constexpr (X3) rl[st][h] = ld_plain<16>(p.Clo + o);
         }
     };
     auto swrite = [&](int st, int slot) {
@@ -609,7 +544,6 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
             if (fval[h]) {
                 char* d = ring + (size_t)slot * SLOT + (size_t)(fpar[h] * KC + fs[h]) * 1024 + lane * 16;
                 *reinterpret_cast<u32x4*>(d) = rs[st][h];
-                if constexpr (X3) *reinterpret_cast<u32x4*>(d + 2 * KC * 1024) = rl[st][h];
             }
     };
 
@@ -655,10 +589,8 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
                     // chunk's last step, which holds finite data; their X fragments are zero
                     const int sr = s < cs ? s : cs - 1;
                     const u32x4 a = *reinterpret_cast<const u32x4*>(base + (size_t)sr * 1024);
-                    u32x4 al = u32x4{0u, 0u, 0u, 0u};
-                    if constexpr (X3) al = *reinterpret_cast<const u32x4*>(base + (size_t)sr * 1024 + 2 * KC * 1024);
 #pragma unroll
-                    for (int t = 0; t < FN; ++t) mfma_step<MKD>(Z[t], a, al, xh[s][t], xl[s][t]);
+                    for (int t = 0; t < FN; ++t) mfma_step<MK_BF16>(Z[t], a, kNoLow, xh[s][t], kNoLow);
                 }
 #pragma unroll
                 for (int t = 0; t < FN; ++t) Y[t] += sv[t] * Z[t];
@@ -691,8 +623,7 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
         const int cb = e >> 4, rr = e & 15;              // block column, local row
         const int gq = cb / NCW, cl = cb - gq * NCW;     // column group, column within it
         const int t = cl % FN, cc = cl / FN;
-        const int gg = MKD == MK_F64 ? (rr & 3) : (rr >> 2);
-        const int v = MKD == MK_F64 ? (rr >> 2) : (rr & 3);
+        const int gg = rr >> 2, v = rr & 3;
         const int ln = gg * 16 + cc;
         const Acc sum = red[((gq * FN + t) * 4 + v) * 64 + ln] + red[(((gq + 4) * FN + t) * 4 + v) * 64 + ln];
         const int row = rowbase + rr, b = b0 + cb;
@@ -700,36 +631,20 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
     }
 }
 
-template <int MKD>
-static KrsTile krs_tile(int v) {
-    return KrsTab<MKD>::t[v];
-}
-
-static KrsTile krs_tile_mk(int mk, int v) {
-    switch (mk) {
-        case MK_F64: return krs_tile<MK_F64>(v);
-        case MK_F32: return krs_tile<MK_F32>(v);
-        case MK_BF16: return krs_tile<MK_BF16>(v);
-        default: return krs_tile<MK_BF16X3>(v);
-    }
-}
-
 // Same split rules as kr_plan, for 256 concurrent blocks of 8 wavefronts; the LDS holds
 // the two ring slots and the j-weights of a block's j's.
-KrPlan krs_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
-    const int mk = mk_of_dt(dt);
+KrPlan krs_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
     if (v < 0 || v >= kKrsVariants) v = 0;
-    const KrsTile t = krs_tile_mk(mk, v);
+    const KrsTile t = kKrsTiles[v];
     KrPlan pl{};
     pl.v = v;
     pl.fn = t.fn;
     pl.kw = t.kc;
     pl.pf = t.p;
-    const int KS = mk == MK_F64 ? 8 : mk == MK_F32 ? 16 : 32;
-    const size_t accb = mk == MK_F64 ? 8 : 4;
+    const size_t accb = 4;
     const int NCB = 64 * t.fn;
-    const size_t slot = (size_t)2 * t.kc * 1024 * (mk == MK_BF16X3 ? 2 : 1);
-    pl.ksteps = Kt / KS;
+    const size_t slot = (size_t)2 * t.kc * 1024;
+    pl.ksteps = Kt / kKrStep;
     pl.nkc = (pl.ksteps + t.kc - 1) / t.kc;
     pl.gx = (M + 15) / 16;
     pl.gy = (Bpad + NCB - 1) / NCB;
@@ -760,73 +675,36 @@ KrPlan krs_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
     return pl;
 }
 
-template <int ADT, int MKD, int V>
+template <int V>
 static void krs_go_v(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
-    constexpr KrsTile t = KrsTab<MKD>::t[V];
-    hipLaunchKernelGGL((k_krs<ADT, MKD, t.fn, t.kc, t.p>), dim3(pl.blocks), dim3(512), pl.lds, s, a);
+    constexpr KrsTile t = kKrsTiles[V];
+    hipLaunchKernelGGL((k_krs<t.fn, t.kc, t.p>), dim3(pl.blocks), dim3(512), pl.lds, s, a);
 }
 
-template <int ADT, int MKD, int V>
+template <int V>
 static hipError_t krs_attr_v(size_t lds) {
-    constexpr KrsTile t = KrsTab<MKD>::t[V];
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_krs<ADT, MKD, t.fn, t.kc, t.p>),
+    constexpr KrsTile t = kKrsTiles[V];
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_krs<t.fn, t.kc, t.p>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-template <int ADT, int MKD>
-static void krs_go(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
-    switch (pl.v) {
-        case 0: krs_go_v<ADT, MKD, 0>(a, pl, s); break;
-        case 1: krs_go_v<ADT, MKD, 1>(a, pl, s); break;
-        case 2: krs_go_v<ADT, MKD, 2>(a, pl, s); break;
-        default: krs_go_v<ADT, MKD, 3>(a, pl, s); break;
-    }
-}
-
-template <int ADT, int MKD>
-static hipError_t krs_attr(size_t lds) {
-    hipError_t e = hipSuccess, q;
-    if ((q = krs_attr_v<ADT, MKD, 0>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr_v<ADT, MKD, 1>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr_v<ADT, MKD, 2>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr_v<ADT, MKD, 3>(lds)) != hipSuccess) e = q;
-    return e;
 }
 
 hipError_t krs_set_lds_limit(size_t lds) {
     hipError_t e = hipSuccess, q;
-    if ((q = krs_attr<DT_F64, MK_F64>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr<DT_F32, MK_F32>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr<DT_BF16, MK_BF16>(lds)) != hipSuccess) e = q;
-    if ((q = krs_attr<DT_BF16X3, MK_BF16X3>(lds)) != hipSuccess) e = q;
+    if ((q = krs_attr_v<0>(lds)) != hipSuccess) e = q;
+    if ((q = krs_attr_v<1>(lds)) != hipSuccess) e = q;
+    if ((q = krs_attr_v<2>(lds)) != hipSuccess) e = q;
+    if ((q = krs_attr_v<3>(lds)) != hipSuccess) e = q;
     return e;
 }
 
-void launch_krs_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_lo, int N, int Np, int Bpad,
-                      const void* X, const void* Xlo, const void* S, void* part, hipStream_t s) {
-    KrArgs a{};
-    a.C = Ct;
-    a.Clo = (const unsigned short*)Ct_lo;
-    a.X = X;
-    a.Xlo = (const unsigned short*)Xlo;
-    a.S = S;
-    a.part = part;
-    a.M = N;
-    a.J = N;
-    a.Kt = kr_tiled_k(dt, N);
-    a.Kx = Np;
-    a.Bpad = Bpad;
-    a.ksteps = pl.ksteps;
-    a.nkc = pl.nkc;
-    a.jc = pl.jc;
-    a.njr = pl.njr;
-    a.gx = pl.gx;
-    a.gy = pl.gy;
-    switch (dt) {
-        case DT_F64: krs_go<DT_F64, MK_F64>(a, pl, s); break;
-        case DT_F32: krs_go<DT_F32, MK_F32>(a, pl, s); break;
-        case DT_BF16: krs_go<DT_BF16, MK_BF16>(a, pl, s); break;
-        default: krs_go<DT_BF16X3, MK_BF16X3>(a, pl, s); break;
+void launch_krs_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, const void* X, const void* S, void* part,
+                      hipStream_t s) {
+    const KrArgs a = kr_args(pl, Ct, N, Np, Bpad, X, S, part);
+    switch (pl.v) {
+        case 0: krs_go_v<0>(a, pl, s); break;
+        case 1: krs_go_v<1>(a, pl, s); break;
+        case 2: krs_go_v<2>(a, pl, s); break;
+        default: krs_go_v<3>(a, pl, s); break;
     }
 }
 
@@ -835,40 +713,39 @@ void launch_krs_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_l
 // Variants: k_kr (kKrVariants), then k_krs (kKrsVariants), then the LDS-tile kernel.
 int dense_batched_variants() { return kKrVariants + kKrsVariants + mfma_variants(); }
 
-DensePlan dense_batched_plan(int dt, int N, int Np, int Bpad, int variant, size_t lds_max) {
-    (void)Np;
+DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max) {
     DensePlan d{};
     if (variant >= kKrVariants + kKrsVariants) {
         d.engine = 1;
-        d.m = mfma_dense_plan(dt, N, Np, Bpad, mfma_variant(variant - kKrVariants - kKrsVariants));
+        d.m = mfma_dense_plan(N, Np, Bpad, mfma_variant(variant - kKrVariants - kKrsVariants));
         d.nsplit = d.m.nsplit;
     } else if (variant >= kKrVariants) {
         d.engine = 2;
-        d.k = krs_plan(dt, N, N, kr_tiled_k(dt, N), Bpad, variant - kKrVariants, lds_max);
+        d.k = krs_plan(N, N, kr_tiled_k(N), Bpad, variant - kKrVariants, lds_max);
         d.nsplit = d.k.nsplit;
     } else {
         d.engine = 0;
-        d.k = kr_plan(dt, N, N, kr_tiled_k(dt, N), Bpad, variant, lds_max);
+        d.k = kr_plan(N, N, kr_tiled_k(N), Bpad, variant, lds_max);
         d.nsplit = d.k.nsplit;
     }
     return d;
 }
 
-void launch_dense_batched(int dt, const DensePlan& pl, const void* C, const void* Clo, const void* Ct,
-                          const void* Ct_lo, int N, int Np, int Bpad, const void* X, const void* Xlo, const void* S,
-                          void* part, hipStream_t s) {
-    if (pl.engine == 1) launch_mfma_dense(dt, pl.m, C, Clo, N, Np, Bpad, X, Xlo, S, part, s);
-    else if (pl.engine == 2) launch_krs_dense(dt, pl.k, Ct, Ct_lo, N, Np, Bpad, X, Xlo, S, part, s);
-    else launch_kr_dense(dt, pl.k, Ct, Ct_lo, N, Np, Bpad, X, Xlo, S, part, s);
+void launch_dense_batched(const DensePlan& pl, const void* C, const void* Ct, int N, int Np, int Bpad, const void* X,
+                          const void* S, void* part, hipStream_t s) {
+    if (pl.engine == 1) launch_mfma_dense(pl.m, C, N, Np, Bpad, X, S, part, s);
+    else if (pl.engine == 2) launch_krs_dense(pl.k, Ct, N, Np, Bpad, X, S, part, s);
+    else launch_kr_dense(pl.k, Ct, N, Np, Bpad, X, S, part, s);
 }
 
 // ---------------------------------------------------------------- tiled copy
 
 // dst unit q = ((tile * N + j) * (Kt / VEC) + ku) * 16 + r  <-  row i = 16 tile + r,
 // elements [ku VEC, ku VEC + VEC) of row-major src [N][N][Np]; zero outside (i >= N or
-// k >= Np).  Units are 16 bytes; VEC = 16 / element size divides Np.
+// k >= Np).  Units are 16 bytes (VEC = 8 words, which divides Np).
 __global__ void k_kr_tile(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int N, int Np, int Kt,
-                          int VEC, long long units) {
+                          long long units) {
+    constexpr int VEC = 8;
     const int nku = Kt / VEC;
     for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < units;
          q += (long long)gridDim.x * blockDim.x) {
@@ -885,14 +762,11 @@ __global__ void k_kr_tile(const u32x4* __restrict__ src, u32x4* __restrict__ dst
     }
 }
 
-size_t kr_tiled_bytes(int dt, int N, int eb) {
-    return (size_t)((N + 15) / 16 * 16) * N * kr_tiled_k(dt, N) * eb;
-}
+size_t kr_tiled_bytes(int N) { return (size_t)((N + 15) / 16 * 16) * N * kr_tiled_k(N) * 2; }
 
-void launch_kr_tile(int dt, int eb, const void* src, void* dst, int N, int Np, hipStream_t s) {
-    const int VEC = 16 / eb, Kt = kr_tiled_k(dt, N);
-    const long long units = (long long)kr_tiled_bytes(dt, N, eb) / 16;
-    hipLaunchKernelGGL(k_kr_tile, dim3(4096), dim3(256), 0, s, (const u32x4*)src, (u32x4*)dst, N, Np, Kt, VEC, units);
+void launch_kr_tile(const void* src, void* dst, int N, int Np, hipStream_t s) {
+    const long long units = (long long)kr_tiled_bytes(N) / 16;
+    hipLaunchKernelGGL(k_kr_tile, dim3(4096), dim3(256), 0, s, (const u32x4*)src, (u32x4*)dst, N, Np, kr_tiled_k(N), units);
 }
 
 }  // namespace rom

@@ -373,17 +373,12 @@ static MfmaArgs fill_args(const MfmaPlan& pl, const void* A, const void* Alo, co
 
 static int mk_of(int dt) { return dt == DT_F64 ? MK_F64 : dt == DT_F32 ? MK_F32 : dt == DT_BF16 ? MK_BF16 : MK_BF16X3; }
 
-MfmaPlan mfma_dense_plan(int dt, int N, int Np, int Bpad, MfmaTile t) { return mfma_plan(mk_of(dt), N, N, Np, Bpad, t); }
+MfmaPlan mfma_dense_plan(int N, int Np, int Bpad, MfmaTile t) { return mfma_plan(MK_BF16, N, N, Np, Bpad, t); }
 
-void launch_mfma_dense(int dt, const MfmaPlan& pl, const void* C, const void* Clo, int N, int Np, int Bpad,
-                       const void* X, const void* Xlo, const void* S, void* part, hipStream_t s) {
-    const MfmaArgs a = fill_args(pl, C, Clo, X, Xlo, S, part, (long long)N * Np, Np, N, N, Np, Bpad, Bpad);
-    switch (dt) {
-        case DT_F64: go_tile<DT_F64, MK_F64, true>(a, pl, s); break;
-        case DT_F32: go_tile<DT_F32, MK_F32, true>(a, pl, s); break;
-        case DT_BF16: go_tile<DT_BF16, MK_BF16, true>(a, pl, s); break;
-        default: go_tile<DT_BF16X3, MK_BF16X3, true>(a, pl, s); break;
-    }
+void launch_mfma_dense(const MfmaPlan& pl, const void* C, int N, int Np, int Bpad, const void* X, const void* S,
+                       void* part, hipStream_t s) {
+    const MfmaArgs a = fill_args(pl, C, nullptr, X, nullptr, S, part, (long long)N * Np, Np, N, N, Np, Bpad, Bpad);
+    go_tile<DT_BF16, MK_BF16, true>(a, pl, s);
 }
 
 MfmaPlan mfma_proj_plan(int dt, int Np, int Rp, int Bpad, MfmaTile t) { return mfma_plan(mk_of(dt), 2 * Rp, 1, Np, Bpad, t); }

@@ -5,7 +5,10 @@
 // launch runs block q - blk0 of the job whose block range holds it; the job's kind and
 // format select the body (kbody.h) that the kernels of a single state run, so a state
 // gives the same results to the bit alone and in a mix.
+#include <type_traits>
+
 #include "kbody.h"
+#include "kfold.h"
 
 namespace rom {
 
@@ -19,6 +22,12 @@ __device__ __forceinline__ void mix_body(const MixJob& jb, int blk) {
     switch (jb.kind) {
         case MIX_GEMV:
             dense_gemv_body<DT, V, 4, 256>(jb.g, blk);
+            break;
+        case MIX_FOLD:
+            if constexpr (DT != DT_BF16) {
+                if (jb.d.stream) fold_gemv_body<DT, kFoldU, true>(jb.d, blk);
+                else fold_gemv_body<DT, kFoldU, false>(jb.d, blk);
+            }
             break;
         case MIX_PROJ:
             cp_proj_any_body<DT, V, 4>(jb.p, blk);
@@ -91,6 +100,7 @@ size_t proj_lds_of(int dt, int Np) { return (dt == DT_BF16 || dt == DT_BF16X3 ? 
 int mix_job_blocks(const MixJob& jb) {
     switch (jb.kind) {
         case MIX_GEMV: return jb.g.nblk;
+        case MIX_FOLD: return jb.d.nblk;
         case MIX_PROJ: return jb.p.nblk;
         case MIX_BDF: return jb.b.nblk;
         case MIX_SCAT: return jb.s.nblk;
@@ -103,6 +113,7 @@ int mix_job_blocks(const MixJob& jb) {
 size_t mix_job_lds(const MixJob& jb) {
     switch (jb.kind) {
         case MIX_GEMV: return lds_u(jb.dtype, jb.g.Np) + (jb.g.wj ? acc_size(jb.dtype) * (size_t)jb.g.J : 0);
+        case MIX_FOLD: return fold_gemv_lds(jb.dtype, jb.d);
         case MIX_PROJ: return proj_lds_of(jb.dtype, jb.p.Np);
         case MIX_BDF: return 0;
         case MIX_SCAT: return acc_size(jb.dtype) * (size_t)jb.s.Rp;

@@ -45,6 +45,14 @@ __device__ __forceinline__ typename RawT<BYTES>::T ld_plain(const void* p) {
     return *reinterpret_cast<const typename RawT<BYTES>::T*>(p);
 }
 
+// NT: non-temporal (streamed once) loads; plain loads when sibling blocks re-read the same
+// rows through L2.
+template <int BYTES, bool NT>
+__device__ __forceinline__ typename RawT<BYTES>::T ld_a(const void* p) {
+    if constexpr (NT) return ld_stream<BYTES>(p);
+    else return ld_plain<BYTES>(p);
+}
+
 // Decode V consecutive stored elements from a raw vector into the accumulation type.
 template <int DT, int V> struct Decode;
 template <int V> struct Decode<DT_F32, V> {

@@ -46,14 +46,6 @@ template <> struct MfmaT<MK_BF16X3> : MfmaT<MK_BF16> {};
 // A fragment: VEC consecutive k of one row, converted to the MFMA operand format.
 // ADT is the operator's storage format.  Loads are never predicated (the caller keeps
 // every address inside the allocation), so the compiler can count them exactly.
-// NT: non-temporal (streamed once) loads; plain loads when sibling blocks of other
-// column tiles re-read the same rows through L2.
-template <int BYTES, bool NT>
-__device__ __forceinline__ typename RawT<BYTES>::T ld_a(const void* p) {
-    if constexpr (NT) return ld_stream<BYTES>(p);
-    else return ld_plain<BYTES>(p);
-}
-
 template <int ADT, int MKD, bool NT>
 __device__ __forceinline__ void load_a(const void* A, const unsigned short* Alo, size_t off, u32x4& hi,
                                        u32x4& lo) {

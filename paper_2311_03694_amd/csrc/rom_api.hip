@@ -77,8 +77,13 @@ struct rom_ctx_s {
     bool own_stream = false;
     // operators in the contraction format
     // (contracted indices padded with zeros: Np, Rp = N, R rounded up to multiples of 8)
-    void *C = nullptr, *Clo = nullptr;         // dense [N][N][Np]
-    void *Ct = nullptr, *Ct_lo = nullptr;      // dense, max_batch > 1: tiled copy for k_kr
+    void* C = nullptr;                         // dense BF16 [N][N][Np]
+    void* Ct = nullptr;                        // dense BF16, max_batch > 1: tiled copy for k_kr
+    // dense FP64, FP32, BF16X3: the folded tensor (kfold.h), for one trajectory and batches
+    FoldLay fl{};
+    FoldPlan fplan{};                          // the latest unbounded batch plan, of fplan_B columns and
+    int fplan_B = 0, fplan_v = 0;              // variant fplan_v (planning is a search of some 100 splits)
+    void *F = nullptr, *F_lo = nullptr;
     void *BCt = nullptr, *BCt_lo = nullptr;    // CP [2Rp][Np]: rows Bf^T then Cf^T
     void *Af = nullptr, *Af_lo = nullptr;      // CP [N][Rp]
     void* lam = nullptr;                        // CP [Rp] (FP64 or FP32)
@@ -176,6 +181,12 @@ static SkewPairs skew_of(rom_ctx c);   // the skew column pairs in use (defined 
 namespace {
 
 GemvTile gemv_tile(rom_ctx c) { return dense_gemv_variant(c->tile[0] < 0 ? 0 : c->tile[0]); }
+// The folded stream's pieces per chunk: its blocks (16 rows each) are an eighth of the
+// unfolded kernel's target, 1024 by default (FP32 at N = 300: 11.7 us, with 2048 blocks 15.5).
+int fold_njr(rom_ctx c) { return fold_gemv_njr(c->fl, gemv_tile(c).chunk_target / 8); }
+FoldJob fold_job(rom_ctx c, const double* u_base, const long long* stepp, long long slot_stride, void* part) {
+    return make_fold_job(c->dtype, c->F, c->F_lo, c->fl, u_base, stepp, slot_stride, part, fold_njr(c));
+}
 // kinds 2 (CP projections) and 3 (CP scatter): k_gemm variants first, then the LDS-tile
 // kernel's
 SkinnyPlan skinny_plan(rom_ctx c, int kind, int Bpad) {
@@ -255,7 +266,9 @@ void launch_zero_fill(void* p, size_t bytes, hipStream_t s) {
 struct WsPlan {
     int B = 1, Bpad = 16;
     int nchunk = 0;                 // B = 1 dense: partial chunks per row
-    DensePlan pd{};                 // B > 1: dense contraction
+    DensePlan pd{};                 // B > 1: dense contraction (BF16)
+    FoldPlan pf{};                  // B > 1: dense contraction (folded tensor)
+    int nsplit = 1;                 // B > 1: partial tiles of the contraction
     SkinnyPlan pp{}, ps{};          // B > 1: CP projection, CP scatter
     size_t part_off = 0;            // dense / scatter partials, or CP s,t (B = 1)
     size_t part2_off = 0;           // CP projection partials (B > 1)
@@ -266,7 +279,8 @@ struct WsPlan {
     size_t total = 0;
 };
 
-WsPlan plan_ws(rom_ctx c, int B) {
+// fold_splits > 0 bounds the partial tiles of a batched folded contraction.
+WsPlan plan_ws(rom_ctx c, int B, int fold_splits = 0) {
     WsPlan p;
     p.B = B;
     p.Bpad = (B + 15) / 16 * 16;
@@ -274,7 +288,7 @@ WsPlan plan_ws(rom_ctx c, int B) {
     size_t off = 0;
     if (B == 1) {
         if (c->dense || c->svd) {
-            p.nchunk = dense_gemv_nchunk(c->N, gemv_tile(c));
+            p.nchunk = c->F ? c->fl.nk * fold_njr(c) : dense_gemv_nchunk(c->N, gemv_tile(c));
             p.part_off = off;
             off = align256(off + (size_t)p.nchunk * c->N * ab);
             if (c->svd) {
@@ -288,12 +302,28 @@ WsPlan plan_ws(rom_ctx c, int B) {
     } else {
         const size_t eb = elem_bytes(c->dtype);
         if (c->dense) {
-            p.pd = dense_batched_plan(c->dtype, c->N, c->Np, p.Bpad, c->tile[1], c->lds_max);
+            if (c->F) {
+                if (fold_splits > 0) {
+                    p.pf = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, fold_splits);
+                } else {
+                    if (c->fplan_B != p.Bpad || c->fplan_v != c->tile[1]) {
+                        c->fplan = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, 0);
+                        c->fplan_B = p.Bpad;
+                        c->fplan_v = c->tile[1];
+                    }
+                    p.pf = c->fplan;
+                }
+                p.nsplit = p.pf.nsplit;
+            } else {
+                p.pd = dense_batched_plan(c->N, c->Np, p.Bpad, c->tile[1], c->lds_max);
+                p.nsplit = p.pd.nsplit;
+            }
             p.part_off = off;
-            off = align256(off + (size_t)p.pd.nsplit * p.Bpad * c->N * ab);
+            off = align256(off + (size_t)p.nsplit * p.Bpad * c->N * ab);
         } else {
             p.pp = skinny_plan(c, 2, p.Bpad);
             p.ps = skinny_plan(c, 3, p.Bpad);
+            p.nsplit = p.ps.nsplit;
             p.part2_off = off;
             off = align256(off + (size_t)p.pp.nsplit * p.Bpad * 2 * c->Rp * ab);
             p.w_off = off;
@@ -311,6 +341,13 @@ WsPlan plan_ws(rom_ctx c, int B) {
     }
     p.total = off + 256;
     return p;
+}
+
+// The batched dense contraction of plan p: partial tiles in `part`.
+void launch_dense_term(rom_ctx c, const WsPlan& p, const void* X, const void* Xlo, const void* S, void* part,
+                       hipStream_t s) {
+    if (c->F) launch_fold_batched(c->dtype, p.pf, c->F, c->F_lo, c->fl, c->Np, p.Bpad, X, Xlo, S, part, s);
+    else launch_dense_batched(p.pd, c->C, c->Ct, c->N, c->Np, p.Bpad, X, S, part, s);
 }
 
 rom_status ensure_ws(rom_ctx c, size_t bytes) {
@@ -361,6 +398,51 @@ static rom_status upload_convert(rom_ctx c, const double* host, size_t rows, int
 // Every operator allocation ends in kSlack zero bytes: the batched kernels' lane vectors
 // may run up to one k-step past the last row (they meet zero weights).
 static constexpr size_t kSlack = 256;
+
+// The dense tensor in the folded storage (kfold.h): uploaded whole rows i at a time (the
+// stage holds at least one) and folded on the device.  A tensor whose folded words are not
+// all finite (an entry that is not, or a sum of two that overflows the format) is staged
+// unfolded instead, so its evaluations meet the entries themselves.
+static rom_status stage_folded(rom_ctx c, const double* host, double* stage, size_t stage_elems) {
+    const size_t nn = (size_t)c->N * c->N, eb = elem_bytes(c->dtype);
+    const int per = (int)std::max<size_t>(1, stage_elems / nn);
+    int* flag = nullptr;
+    HIPCHK(hipMalloc((void**)&flag, sizeof(int)));
+    struct Guard {
+        int* p;
+        ~Guard() { hipFree(p); }
+    } guard{flag};
+    for (int fold = 1; fold >= 0; --fold) {
+        c->fl = fold_layout(c->dtype, c->N, fold != 0);
+        const size_t n = fold_elems(c->fl);
+        const size_t bytes0 = c->bytes, list0 = c->allocs.size();
+        TRYS(dmalloc(&c->F, n * eb + kSlack, &c->bytes, &c->allocs));
+        HIPCHK(hipMemsetAsync(c->F, 0, n * eb + kSlack, c->stream));
+        if (c->dtype == DT_BF16X3) {
+            TRYS(dmalloc(&c->F_lo, n * 2 + kSlack, &c->bytes, &c->allocs));
+            HIPCHK(hipMemsetAsync(c->F_lo, 0, n * 2 + kSlack, c->stream));
+        }
+        HIPCHK(hipMemsetAsync(flag, 0, sizeof(int), c->stream));
+        for (int i0 = 0; i0 < c->N; i0 += per) {
+            const int ni = std::min(per, c->N - i0);
+            HIPCHK(hipMemcpyAsync(stage, host + (size_t)i0 * nn, (size_t)ni * nn * sizeof(double), hipMemcpyHostToDevice,
+                                  c->stream));
+            launch_fold_pack(c->dtype, stage, i0, ni, c->fl, c->F, c->F_lo, flag, c->stream);
+            HIPCHK(hipGetLastError());
+            HIPCHK(hipStreamSynchronize(c->stream));
+        }
+        int bad = 0;
+        HIPCHK(hipMemcpy(&bad, flag, sizeof(int), hipMemcpyDeviceToHost));
+        if (!fold || !bad) break;
+        while (c->allocs.size() > list0) {
+            hipFree(c->allocs.back());
+            c->allocs.pop_back();
+        }
+        c->bytes = bytes0;
+        c->F = c->F_lo = nullptr;
+    }
+    return ROM_OK;
+}
 
 // Column pairs of CP factors that keep the partial skew-symmetry (Sec. 3.3, eq.
 // skew_abc_struct): pair p = (c0, c1) with lam[c0] == lam[c1], Bf[:,c0] == Bf[:,c1],
@@ -561,7 +643,7 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
         c->device = dev;
         HTRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
         size_t want = lds > 122880 ? 122880 : (size_t)lds;
-        if (want > 65536 && kr_set_lds_limit(want) != hipSuccess) {
+        if (want > 65536 && (kr_set_lds_limit(want) != hipSuccess || fold_set_lds_limit(want) != hipSuccess)) {
             (void)hipGetLastError();
             want = 65536;
         }
@@ -691,23 +773,22 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
         HTRY(hipGetLastError());
     } else
     if (c->dense) {
-        const size_t n3 = nn * Np;
-        TRY(dmalloc(&c->C, n3 * eb + kSlack, &c->bytes, &c->allocs));
-        HTRY(hipMemsetAsync(c->C, 0, n3 * eb + kSlack, c->stream));
-        if (lo) {
-            TRY(dmalloc(&c->Clo, n3 * 2 + kSlack, &c->bytes, &c->allocs));
-            HTRY(hipMemsetAsync(c->Clo, 0, n3 * 2 + kSlack, c->stream));
-        }
-        TRY(upload_convert(c, d->C, nn, (int)N, (int)Np, c->C, c->Clo, stage, stage_elems));
-        if (c->max_batch > 1) {
-            // the batched kernel's tiled copy (a permutation of the converted words)
-            const size_t tb = kr_tiled_bytes(dt, (int)N, (int)eb);
-            TRY(dmalloc(&c->Ct, tb, &c->bytes, &c->allocs));
-            launch_kr_tile(dt, (int)eb, c->C, c->Ct, (int)N, (int)Np, c->stream);
-            if (lo) {
-                TRY(dmalloc(&c->Ct_lo, kr_tiled_bytes(dt, (int)N, 2), &c->bytes, &c->allocs));
-                launch_kr_tile(dt, 2, c->Clo, c->Ct_lo, (int)N, (int)Np, c->stream);
+        if (dt != DT_BF16) {
+            st = stage_folded(c, d->C, stage, stage_elems);
+            if (st != ROM_OK) {
+                rom_destroy(c);
+                return st;
             }
+        } else {
+            const size_t n3 = nn * Np;
+            TRY(dmalloc(&c->C, n3 * eb + kSlack, &c->bytes, &c->allocs));
+            HTRY(hipMemsetAsync(c->C, 0, n3 * eb + kSlack, c->stream));
+            TRY(upload_convert(c, d->C, nn, (int)N, (int)Np, c->C, nullptr, stage, stage_elems));
+        }
+        if (dt == DT_BF16 && c->max_batch > 1) {
+            // the batched kernel's tiled copy (a permutation of the converted words)
+            TRY(dmalloc(&c->Ct, kr_tiled_bytes((int)N), &c->bytes, &c->allocs));
+            launch_kr_tile(c->C, c->Ct, (int)N, (int)Np, c->stream);
             HTRY(hipGetLastError());
         }
     } else {
@@ -1141,8 +1222,11 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
     if (s->B == 1) {
         char* ws = (char*)s->scratch;
         if (c->dense) {
-            launch_dense_gemv(c->dtype, c->C, c->Clo, c->N, c->Np, c->N, nullptr, a.uring, a.step, (long long)c->N,
-                              ws + p.part_off, p.nchunk, gemv_tile(c), stream);
+            if (c->F)
+                launch_fold_gemv(c->dtype, fold_job(c, a.uring, a.step, (long long)c->N, ws + p.part_off), stream);
+            else
+                launch_dense_gemv(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, a.uring, a.step, (long long)c->N,
+                                  ws + p.part_off, p.nchunk, gemv_tile(c), stream);
             launch_bdf_from_partials(a, accf, ws + p.part_off, p.nchunk, 1, diag, stream);
         } else if (c->svd) {
             launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, a.uring, a.step, (long long)c->N,
@@ -1162,13 +1246,12 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
     } else {
         char* ws = (char*)c->ws;
         if (c->dense) {
-            launch_dense_batched(c->dtype, p.pd, c->C, c->Clo, c->Ct, c->Ct_lo, c->N, c->Np, p.Bpad, a.ucv,
-                                 a.ucv_lo, a.uj, ws + p.part_off, stream);
-            launch_bdf_from_partials(a, accf, ws + p.part_off, p.pd.nsplit, p.Bpad, diag, stream);
+            launch_dense_term(c, p, a.ucv, a.ucv_lo, a.uj, ws + p.part_off, stream);
+            launch_bdf_from_partials(a, accf, ws + p.part_off, p.nsplit, p.Bpad, diag, stream);
         } else {
             if (!launch_cp_batched(c, p.pp, p.ps, p.Bpad, s->B, a.ucv, a.ucv_lo, ws + p.part2_off, ws + p.w_off,
                                    ws + p.part_off, &a, stream))
-                launch_bdf_from_partials(a, accf, ws + p.part_off, p.ps.nsplit, p.Bpad, diag, stream);
+                launch_bdf_from_partials(a, accf, ws + p.part_off, p.nsplit, p.Bpad, diag, stream);
         }
     }
     if (!c->diagA) {
@@ -1193,7 +1276,12 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     if (!c) return fail(ROM_E_INVALID, "ctx is NULL");
     if (batch < 1 || batch > c->max_batch) return fail(ROM_E_INVALID, "batch %d outside [1, %d]", batch, c->max_batch);
     if (!u_dev || !y_dev) return fail(ROM_E_INVALID, "u_dev / y_dev is NULL");
-    const WsPlan p = plan_ws(c, batch);
+    WsPlan p = plan_ws(c, batch);
+    // a bounded workspace: fewer partial tiles where the usual plan's do not fit
+    for (int ns = p.nsplit; ws_given && c->F && batch > 1 && p.total > ws_given_bytes && ns > 1;) {
+        ns /= 2;
+        p = plan_ws(c, batch, ns);
+    }
     char* ws = ws_given;
     if (ws) {
         // a caller-chosen workspace: it must hold the plan, and what the kernels may
@@ -1226,8 +1314,11 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     auto contract = [&]() {
         if (batch == 1) {
             if (c->dense) {
-                launch_dense_gemv(c->dtype, c->C, c->Clo, c->N, c->Np, c->N, nullptr, u_dev, nullptr, 0,
-                                  ws + p.part_off, p.nchunk, gemv_tile(c), c->stream);
+                if (c->F)
+                    launch_fold_gemv(c->dtype, fold_job(c, u_dev, nullptr, 0, ws + p.part_off), c->stream);
+                else
+                    launch_dense_gemv(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, u_dev, nullptr, 0,
+                                      ws + p.part_off, p.nchunk, gemv_tile(c), c->stream);
             } else if (c->svd) {
                 launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, u_dev, nullptr, 0,
                                 ws + p.svdw_off, c->stream);
@@ -1240,8 +1331,7 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
                                    c->stream);
             }
         } else if (c->dense) {
-            launch_dense_batched(c->dtype, p.pd, c->C, c->Clo, c->Ct, c->Ct_lo, c->N, c->Np, p.Bpad, a.ucv, a.ucv_lo,
-                                 a.uj, ws + p.part_off, c->stream);
+            launch_dense_term(c, p, a.ucv, a.ucv_lo, a.uj, ws + p.part_off, c->stream);
         } else {
             launch_cp_batched(c, p.pp, p.ps, p.Bpad, batch, a.ucv, a.ucv_lo, ws + p.part2_off, ws + p.w_off,
                               ws + p.part_off, nullptr, c->stream);
@@ -1278,8 +1368,7 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     if (batch == 1) {
         if (c->dense || c->svd) launch_sum_partials(accf, ws + p.part_off, p.nchunk, 1, 1, c->N, y_dev, c->stream);
     } else {
-        launch_sum_partials(accf, ws + p.part_off, c->dense ? p.pd.nsplit : p.ps.nsplit, p.Bpad, batch, c->N, y_dev,
-                            c->stream);
+        launch_sum_partials(accf, ws + p.part_off, p.nsplit, p.Bpad, batch, c->N, y_dev, c->stream);
     }
     HIPCHK(hipGetLastError());
     return ROM_OK;
@@ -2129,11 +2218,16 @@ void pair_jobs(rom_ctx c, rom_state st, long long lev, std::vector<MixJob> (&ph)
             add(0, jv);
         }
         MixJob jg{};
-        jg.kind = MIX_GEMV;
-        jg.g = c->svd ? make_gemv_job(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, wj, sa.uring, sa.step, c->N,
-                                      scr + p.part_off, p.nchunk, gemv_tile(c))
-                      : make_gemv_job(c->dtype, c->C, c->Clo, c->N, c->Np, c->N, nullptr, sa.uring, sa.step, c->N,
-                                      scr + p.part_off, p.nchunk, gemv_tile(c));
+        if (c->F) {
+            jg.kind = MIX_FOLD;
+            jg.d = fold_job(c, sa.uring, sa.step, c->N, scr + p.part_off);
+        } else {
+            jg.kind = MIX_GEMV;
+            jg.g = c->svd ? make_gemv_job(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, wj, sa.uring, sa.step, c->N,
+                                          scr + p.part_off, p.nchunk, gemv_tile(c))
+                          : make_gemv_job(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, sa.uring, sa.step, c->N,
+                                          scr + p.part_off, p.nchunk, gemv_tile(c));
+        }
         add(1, jg);
         MixJob jb{};
         jb.kind = MIX_BDF;

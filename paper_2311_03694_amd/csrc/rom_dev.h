@@ -80,6 +80,22 @@ struct GemvJob {           // dense contraction, one trajectory
     long long chunk_len;
     int blk0, nblk;
 };
+// Layout of the folded dense tensor (kfold.h): nk chunks of kc contracted indices, at most
+// lmax j per chunk; fold 0: every chunk contracts all N j.
+struct FoldLay { int N, kc, nk, lmax, fold; };
+constexpr int kFoldU = 4;          // slabs in flight per wavefront of the one-trajectory stream
+struct FoldJob {           // folded dense contraction, one trajectory
+    const void* C;
+    const unsigned short* Clo;
+    FoldLay l;
+    const double* u_base;
+    const long long* stepp;
+    long long slot_stride;
+    void* part;                    // [nk * njr][N]
+    int njr, jc;                   // pieces per chunk, slabs per piece
+    int stream;                    // non-temporal loads
+    int blk0, nblk;
+};
 struct Proj1Job {          // CP projections and their Hadamard product, one trajectory
     const void* BCt;               // layout 0: [Bf|Cf]^T [2Rp][Np]; else the pair form [P + R][Np]
     const unsigned short* BCt_lo;
@@ -142,10 +158,10 @@ struct FinJob {            // closing energy sum of the newest level, one state
 // one one-trajectory state, of any kind and number format.  A step is at most four such
 // launches, whatever the mix of N, R, formats, stiffness kinds and operator forms:
 //   phase 0: full-form terms (MIX_FULL), SVD first products (MIX_SVDP)
-//   phase 1: dense / SVD slab streams (MIX_GEMV), CP projections, diagonal stiffness (MIX_PROJ)
+//   phase 1: dense / SVD slab streams (MIX_GEMV; MIX_FOLD over the folded tensor), CP projections, diagonal stiffness (MIX_PROJ)
 //   phase 2: BDF update or right-hand side from partials (MIX_BDF), CP scatter (MIX_SCAT)
 //   phase 3: Helmholtz apply, with the next projections for CP states (MIX_HELM)
-enum MixKind { MIX_GEMV = 0, MIX_PROJ = 1, MIX_BDF = 2, MIX_SCAT = 3, MIX_HELM = 4, MIX_SVDP = 5, MIX_FULL = 6 };
+enum MixKind { MIX_GEMV = 0, MIX_PROJ = 1, MIX_BDF = 2, MIX_SCAT = 3, MIX_HELM = 4, MIX_SVDP = 5, MIX_FULL = 6, MIX_FOLD = 7 };
 struct MixJob {
     int kind, dtype;
     int mode;                      // MIX_BDF: 1 = diagonal-stiffness update; MIX_SCAT: scatter mode 1 or 2
@@ -158,6 +174,7 @@ struct MixJob {
         HelmJob h;
         SvdProj v;
         FullJob f;
+        FoldJob d;
     };
 };
 // Blocks and dynamic LDS bytes a mixed job needs; the launch over a table (jobs sorted by
@@ -324,12 +341,12 @@ void launch_full_x(const StepArgs& a, double* X, hipStream_t s);
 
 // Batched contraction launchers (k_mfma.hip).  Partials are [nsplit][Bpad][M] in the
 // accumulation type (FP64 for DT_F64, FP32 otherwise).
-//   dense:   M = N rows of C [N][N][Np], X = u [Bpad][Np] and j-weights S [Np][Bpad]
+//   dense:   M = N rows of the BF16 tensor C [N][N][Np], X = u [Bpad][Np] and j-weights S [Np][Bpad]
 //   proj:    M = 2Rp rows of [Bf|Cf]^T [2Rp][Np], X = u [Bpad][Np]
 //   scatter: M = N rows of Af [N][Rp], X = W [Bpad][Rp] (FP32, FP64 for DT_F64)
-MfmaPlan mfma_dense_plan(int dt, int N, int Np, int Bpad, MfmaTile t);
-void launch_mfma_dense(int dt, const MfmaPlan& pl, const void* C, const void* Clo, int N, int Np, int Bpad,
-                       const void* X, const void* Xlo, const void* S, void* part, hipStream_t s);
+MfmaPlan mfma_dense_plan(int N, int Np, int Bpad, MfmaTile t);
+void launch_mfma_dense(const MfmaPlan& pl, const void* C, int N, int Np, int Bpad, const void* X, const void* S,
+                       void* part, hipStream_t s);
 MfmaPlan mfma_proj_plan(int dt, int Np, int Rp, int Bpad, MfmaTile t);
 void launch_mfma_proj(int dt, const MfmaPlan& pl, const void* BCt, const void* BCt_lo, int Np, int Rp, int Bpad,
                       const void* X, const void* Xlo, void* part, hipStream_t s);
@@ -341,10 +358,10 @@ void launch_mfma_scatter(int dt, const MfmaPlan& pl, const void* Af, const void*
 MfmaPlan mfma_helm_plan(int N, int Np, int Bpad, MfmaTile t);
 void launch_mfma_helm(const MfmaPlan& pl, const double* hinv, int N, int Np, int Bpad, const double* rhs,
                       const long long* stepp, double* part, hipStream_t s);
-// Batched dense contraction with the coefficient fragments held in registers
-// (k_kr.hip).  Partials [nsplit][Bpad][N]; X = u [Bpad][Np], j-weights S [Np][Bpad];
-// the tensor comes from the tiled copy Ct [ceil(N/16)][N][Kt/VEC][16][VEC] made by
-// launch_kr_tile (Kt = kr_tiled_k, VEC = 16 bytes / element size).
+// Batched dense contraction of the BF16 format with the coefficient fragments held in
+// registers (k_kr.hip).  Partials [nsplit][Bpad][N]; X = u [Bpad][Np], j-weights S
+// [Np][Bpad]; the tensor comes from the tiled copy Ct [ceil(N/16)][N][Kt/VEC][16][VEC] made by
+// launch_kr_tile (Kt = kr_tiled_k, VEC = 8).
 struct KrPlan {
     int v, fn, kw, pf;             // variant and its shape
     int ksteps, nkc, jc, njr;      // fragment steps, k-chunks, j per block, j-ranges
@@ -352,16 +369,16 @@ struct KrPlan {
     size_t lds;
 };
 int kr_variants();
-int kr_tiled_k(int dt, int N);
-size_t kr_tiled_bytes(int dt, int N, int eb);
-void launch_kr_tile(int dt, int eb, const void* src, void* dst, int N, int Np, hipStream_t s);
-KrPlan kr_plan(int dt, int M, int J, int Kt, int Bpad, int variant, size_t lds_max);
-void launch_kr_dense(int dt, const KrPlan& pl, const void* Ct, const void* Ct_lo, int N, int Np, int Bpad,
-                     const void* X, const void* Xlo, const void* S, void* part, hipStream_t s);
+int kr_tiled_k(int N);
+size_t kr_tiled_bytes(int N);
+void launch_kr_tile(const void* src, void* dst, int N, int Np, hipStream_t s);
+KrPlan kr_plan(int M, int J, int Kt, int Bpad, int variant, size_t lds_max);
+void launch_kr_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, const void* X, const void* S, void* part,
+                     hipStream_t s);
 // Allow every variant up to `lds` bytes of dynamic LDS.
 hipError_t kr_set_lds_limit(size_t lds);
 
-// The batched dense contraction of a context: variants [0, kr_variants()) select the
+// The batched dense contraction of a BF16 context: variants [0, kr_variants()) select the
 // register kernel, the following mfma_variants() the LDS-tile kernel; -1 = default.
 struct DensePlan {
     int engine;                    // 0 = k_kr, 1 = k_mfma_rows, 2 = k_krs
@@ -370,10 +387,33 @@ struct DensePlan {
     int nsplit;
 };
 int dense_batched_variants();
-DensePlan dense_batched_plan(int dt, int N, int Np, int Bpad, int variant, size_t lds_max);
-void launch_dense_batched(int dt, const DensePlan& pl, const void* C, const void* Clo, const void* Ct,
-                          const void* Ct_lo, int N, int Np, int Bpad, const void* X, const void* Xlo, const void* S,
-                          void* part, hipStream_t s);
+DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max);
+void launch_dense_batched(const DensePlan& pl, const void* C, const void* Ct, int N, int Np, int Bpad, const void* X,
+                          const void* S, void* part, hipStream_t s);
+
+// The dense contraction over the folded tensor (k_fold.hip; FP64, FP32 and BF16X3): staging
+// of ni rows of the FP64 tensor from row i0 on, the one-trajectory stream and the batched
+// product.  *flag (device) is raised when a word of a folded tensor is not finite.
+FoldLay fold_layout(int dt, int N, bool fold);
+size_t fold_elems(const FoldLay& l);
+void launch_fold_pack(int dt, const double* src, int i0, int ni, const FoldLay& l, void* dst, void* dst_lo, int* flag,
+                      hipStream_t s);
+int fold_gemv_njr(const FoldLay& l, int target);
+FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, const double* u_base, const long long* stepp,
+                      long long slot_stride, void* part, int njr);
+size_t fold_gemv_lds(int dt, const FoldJob& jb);
+void launch_fold_gemv(int dt, const FoldJob& jb, hipStream_t s);
+struct FoldPlan {
+    int v;                         // shape
+    bool stream;                   // non-temporal tensor loads
+    int njr, jc, ppb, nsplit;      // pieces per chunk, slabs per piece, pieces per block, partial tiles
+    int gx, gy, blocks;
+    size_t lds;
+};
+FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max, int nsplit_max);
+hipError_t fold_set_lds_limit(size_t lds);
+void launch_fold_batched(int dt, const FoldPlan& pl, const void* C, const void* Clo, const FoldLay& l, int Kx, int Bpad,
+                         const void* X, const void* Xlo, const void* S, void* part, hipStream_t s);
 
 // Skinny products of the batched path (k_gemm.hip): one block per output tile over the
 // whole contracted index; outputs in the partials layout with a single split.

@@ -102,8 +102,12 @@ class RomBackend:
         eb = {"fp64": 8, "fp32": 4, "bf16": 2, "bf16x3": 4}[dtype]
         Np = (N + 7) // 8 * 8
         helm = 3 * N * Np * 8
-        if kind == "dense":
+        if kind == "dense" and dtype == "bf16":
             return 2 * N * N * Np * eb + helm              # stream layout and the batched kernel's tiles
+        if kind == "dense":                                # folded tensor: about half the entries (small N: all)
+            kc = 64 if dtype == "bf16x3" else 32
+            lmax = min(N, N // 2 + 2 * kc)
+            return (N + 15) // 16 * 16 * lmax * ((N + kc - 1) // kc * kc) * eb + helm
         R = 2 * N
         return 2 * 3 * R * Np * eb + helm                  # factors and the projection operators
 
@@ -202,11 +206,12 @@ class RomBackend:
 
     def estimate_step_seconds(self, key) -> float:
         """Time of one step of a pool of `key`: the operator bytes a step streams (the dense
-        tensor once for all slots, or the CP factors and projection operators, and the FP64
+        tensor's folded entries, or all of them in BF16, once for all slots, or the CP factors and projection operators, and the FP64
         Helmholtz inverse) at 5 TB/s, plus 20 us of latency."""
         N, _seed, kind, dtype = key
         eb = {"fp64": 8, "fp32": 4, "bf16": 2, "bf16x3": 4}[dtype]
-        nbytes = N ** 3 * eb if kind == "dense" else 3 * N * (2 * N) * eb
+        words = N ** 3 if dtype == "bf16" else N * N * (N + 1) // 2
+        nbytes = words * eb if kind == "dense" else 3 * N * (2 * N) * eb
         return 2e-5 + (nbytes + 8 * N * N) / 5e12
 
     def slot_finite(self, pool) -> np.ndarray:
