@@ -61,10 +61,10 @@ __global__ __launch_bounds__(256) void k_close_group(const FinJob* __restrict__ 
 // rom_nonlinear), padding included: trajectories b >= B and indices i >= N are written
 // as zeros, so the copies never depend on what their memory held before (the
 // contractions multiply the zero padding of the operators by these entries).
-// Grid (ceil(Np/256), Bpad).
+// Grid (ceil(padded row / 256), Bpad).
 __global__ void k_prep_ucv(StepArgs a, const double* __restrict__ u) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y;
-    if (i < a.Np) write_ucv(a, b, i, (b < a.B && i < a.N) ? u[(size_t)b * a.N + i] : 0.0);
+    if (i < (a.ucv_kt ? a.ucv_kt : a.Np)) write_ucv(a, b, i, (b < a.B && i < a.N) ? u[(size_t)b * a.N + i] : 0.0);
 }
 
 template <class ACC>
@@ -118,7 +118,8 @@ void launch_helm_apply(const StepArgs& a, hipStream_t s) {
 }
 
 void launch_prep_ucv(const StepArgs& a, const double* u_src, hipStream_t s) {
-    hipLaunchKernelGGL(k_prep_ucv, dim3((a.Np + 255) / 256, a.Bpad), dim3(256), 0, s, a, u_src);
+    hipLaunchKernelGGL(k_prep_ucv, dim3(((a.ucv_kt ? a.ucv_kt : a.Np) + 255) / 256, a.Bpad), dim3(256), 0,
+                       s, a, u_src);
 }
 
 void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N,

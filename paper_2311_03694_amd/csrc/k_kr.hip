@@ -275,34 +275,40 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
 // with this shape (256 CUs x blocks per CU), which the j-split is planned against.
 struct KrTile { int fn, kw, pf, slots; };
 constexpr int kKrVariants = 8;
-constexpr KrTile kKrTiles[kKrVariants] = {{16, 2, 6, 256}, {4, 4, 5, 512}, {8, 4, 4, 256}, {4, 4, 3, 512},
-                                          {8, 2, 6, 512},  {2, 4, 4, 512}, {4, 4, 4, 512}, {1, 8, 4, 256}};
+// Rows by Dt: the kernel is built for BF16; the rows of the other formats only count the
+// partial tiles that bound rom_nonlinear_noalloc's batches (dense_partials).
+constexpr KrTile kKrTab[4][kKrVariants] = {
+    {{4, 4, 3, 256}, {4, 4, 3, 512}, {8, 2, 3, 256}, {4, 2, 4, 512}, {2, 4, 3, 256}, {2, 8, 2, 256}, {1, 8, 3, 256}, {1, 4, 4, 512}},
+    {{8, 4, 3, 256}, {8, 4, 3, 512}, {16, 2, 3, 256}, {4, 8, 3, 256}, {4, 8, 3, 512}, {8, 2, 4, 512}, {2, 8, 3, 256}, {1, 8, 4, 256}},
+    {{16, 2, 6, 256}, {4, 4, 5, 512}, {8, 4, 4, 256}, {4, 4, 3, 512}, {8, 2, 6, 512}, {2, 4, 4, 512}, {4, 4, 4, 512}, {1, 8, 4, 256}},
+    {{8, 2, 4, 256}, {8, 2, 4, 512}, {16, 1, 6, 256}, {4, 4, 4, 256}, {4, 4, 4, 512}, {4, 2, 6, 512}, {2, 4, 4, 256}, {1, 4, 4, 256}}};
 
 int kr_variants() { return kKrVariants; }
 
 // Default variant: the first one (in order of preference) whose column tile does not
 // exceed the padded batch.
-static int kr_default(int Bpad) {
+static int kr_default(int dt, int Bpad) {
     const int nct = Bpad / 16;
     for (int v = 0; v < kKrVariants; ++v)
-        if (kKrTiles[v].fn <= nct) return v;
+        if (kKrTab[dt][v].fn <= nct) return v;
     return kKrVariants - 1;
 }
 
-constexpr int kKrStep = 32;        // k per fragment step
-int kr_tiled_k(int N) { return (N + kKrStep - 1) / kKrStep * kKrStep; }
+static int kr_step(int dt) { return dt == DT_F64 ? 8 : dt == DT_F32 ? 16 : 32; }   // k per fragment step
+static int kr_padded_k(int dt, int N) { return (N + kr_step(dt) - 1) / kr_step(dt) * kr_step(dt); }
+int kr_tiled_k(int N) { return kr_padded_k(DT_BF16, N); }
 
-KrPlan kr_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
-    if (v < 0 || v >= kKrVariants) v = kr_default(Bpad);
-    const KrTile t = kKrTiles[v];
+static KrPlan kr_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
+    if (v < 0 || v >= kKrVariants) v = kr_default(dt, Bpad);
+    const KrTile t = kKrTab[dt][v];
     KrPlan pl{};
     pl.v = v;
     pl.fn = t.fn;
     pl.kw = t.kw;
     pl.pf = t.pf;
-    const size_t accb = 4;
+    const size_t accb = dt == DT_F64 ? 8 : 4;
     const int NC = 16 * t.fn;
-    pl.ksteps = Kt / kKrStep;
+    pl.ksteps = Kt / kr_step(dt);
     pl.nkc = (pl.ksteps + 4 * t.kw - 1) / (4 * t.kw);
     pl.gx = (M + 15) / 16;
     pl.gy = (Bpad + NC - 1) / NC;
@@ -339,13 +345,13 @@ KrPlan kr_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
 
 template <int V>
 static void kr_go_v(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
-    constexpr KrTile t = kKrTiles[V];
+    constexpr KrTile t = kKrTab[DT_BF16][V];
     hipLaunchKernelGGL((k_kr<t.fn, t.kw, t.pf>), dim3(pl.blocks), dim3(256), pl.lds, s, a);
 }
 
 template <int V>
 static hipError_t kr_attr_v(size_t lds) {
-    constexpr KrTile t = kKrTiles[V];
+    constexpr KrTile t = kKrTab[DT_BF16][V];
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_kr<t.fn, t.kw, t.pf>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
@@ -427,7 +433,10 @@ void launch_kr_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, 
 // part[split][b][i] like k_kr.
 struct KrsTile { int fn, kc, p; };
 constexpr int kKrsVariants = 4;
-constexpr KrsTile kKrsTiles[kKrsVariants] = {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}};
+constexpr KrsTile kKrsTab[4][kKrsVariants] = {{{2, 7, 3}, {2, 8, 2}, {2, 4, 3}, {1, 8, 3}},    // rows as kKrTab
+                                             {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}},
+                                             {{4, 7, 2}, {4, 8, 2}, {4, 4, 3}, {2, 8, 3}},
+                                             {{4, 3, 2}, {2, 7, 2}, {2, 4, 3}, {2, 8, 2}}};
 
 template <int FN, int KC, int P>
 __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
@@ -633,18 +642,18 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
 
 // Same split rules as kr_plan, for 256 concurrent blocks of 8 wavefronts; the LDS holds
 // the two ring slots and the j-weights of a block's j's.
-KrPlan krs_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
+static KrPlan krs_plan(int dt, int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
     if (v < 0 || v >= kKrsVariants) v = 0;
-    const KrsTile t = kKrsTiles[v];
+    const KrsTile t = kKrsTab[dt][v];
     KrPlan pl{};
     pl.v = v;
     pl.fn = t.fn;
     pl.kw = t.kc;
     pl.pf = t.p;
-    const size_t accb = 4;
+    const size_t accb = dt == DT_F64 ? 8 : 4;
     const int NCB = 64 * t.fn;
-    const size_t slot = (size_t)2 * t.kc * 1024;
-    pl.ksteps = Kt / kKrStep;
+    const size_t slot = (size_t)2 * t.kc * 1024 * (dt == DT_BF16X3 ? 2 : 1);
+    pl.ksteps = Kt / kr_step(dt);
     pl.nkc = (pl.ksteps + t.kc - 1) / t.kc;
     pl.gx = (M + 15) / 16;
     pl.gy = (Bpad + NCB - 1) / NCB;
@@ -677,13 +686,13 @@ KrPlan krs_plan(int M, int J, int Kt, int Bpad, int v, size_t lds_max) {
 
 template <int V>
 static void krs_go_v(const KrArgs& a, const KrPlan& pl, hipStream_t s) {
-    constexpr KrsTile t = kKrsTiles[V];
+    constexpr KrsTile t = kKrsTab[DT_BF16][V];
     hipLaunchKernelGGL((k_krs<t.fn, t.kc, t.p>), dim3(pl.blocks), dim3(512), pl.lds, s, a);
 }
 
 template <int V>
 static hipError_t krs_attr_v(size_t lds) {
-    constexpr KrsTile t = kKrsTiles[V];
+    constexpr KrsTile t = kKrsTab[DT_BF16][V];
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_krs<t.fn, t.kc, t.p>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
@@ -713,22 +722,31 @@ void launch_krs_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad,
 // Variants: k_kr (kKrVariants), then k_krs (kKrsVariants), then the LDS-tile kernel.
 int dense_batched_variants() { return kKrVariants + kKrsVariants + mfma_variants(); }
 
-DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max) {
+static DensePlan dense_plan_of(int dt, int N, int Np, int Bpad, int variant, size_t lds_max) {
     DensePlan d{};
+    const int Kt = kr_padded_k(dt, N);
     if (variant >= kKrVariants + kKrsVariants) {
         d.engine = 1;
-        d.m = mfma_dense_plan(N, Np, Bpad, mfma_variant(variant - kKrVariants - kKrsVariants));
+        d.m = mfma_dense_plan(dt, N, Np, Bpad, mfma_variant(variant - kKrVariants - kKrsVariants));
         d.nsplit = d.m.nsplit;
     } else if (variant >= kKrVariants) {
         d.engine = 2;
-        d.k = krs_plan(N, N, kr_tiled_k(N), Bpad, variant - kKrVariants, lds_max);
+        d.k = krs_plan(dt, N, N, Kt, Bpad, variant - kKrVariants, lds_max);
         d.nsplit = d.k.nsplit;
     } else {
         d.engine = 0;
-        d.k = kr_plan(N, N, kr_tiled_k(N), Bpad, variant, lds_max);
+        d.k = kr_plan(dt, N, N, Kt, Bpad, variant, lds_max);
         d.nsplit = d.k.nsplit;
     }
     return d;
+}
+
+DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max) {
+    return dense_plan_of(DT_BF16, N, Np, Bpad, variant, lds_max);
+}
+
+int dense_partials(int dt, int N, int Np, int Bpad, int variant, size_t lds_max) {
+    return dense_plan_of(dt, N, Np, Bpad, variant, lds_max).nsplit;
 }
 
 void launch_dense_batched(const DensePlan& pl, const void* C, const void* Ct, int N, int Np, int Bpad, const void* X,

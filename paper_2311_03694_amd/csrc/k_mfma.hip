@@ -36,12 +36,11 @@ struct MfmaArgs {
     const void* S;                 // [J][s_stride] j-weights (KR): FP64 for MK_F64, else FP32
     void* part;                    // [nsplit][Bpad][M] partial sums (FP64 for MK_F64, else FP32)
     long long a_rowstride, a_jstride;
+    int x_kt;                      // 0: X as above; else X tiled (tile_off), rows of x_kt elements
     int M, J, Kp, Bpad, s_stride;
     int kc, jc, nkc;               // k-chunk length (multiple of 2 KS), j-range length, k-chunks
     int kcp;                       // LDS row stride (elements) of the X tile
     int gx, gy, gz;                // work grid: row tiles, column tiles, splits
-    const long long* kstep;        // non-null: A += (BDF order at *kstep - 1) * a_kstride
-    long long a_kstride;
 };
 
 template <int ADT, int MKD, int MW, int BT, bool KR, bool NT>
@@ -94,7 +93,8 @@ __global__ __launch_bounds__(256) void k_mfma_rows(MfmaArgs p) {
                 v.h = u32x4{0u, 0u, 0u, 0u};
                 v.l = u32x4{0u, 0u, 0u, 0u};
                 if (k < kend) {
-                    const size_t off = (size_t)(b0 + col) * p.Kp + k;
+                    const size_t off = p.x_kt ? tile_off<MfmaT<MKD>::KS, VEC>(p.x_kt, b0 + col, k)
+                                              : (size_t)(b0 + col) * p.Kp + k;
                     v.h = ld_plain<16>(reinterpret_cast<const XT*>(p.X) + off);
                     if constexpr (X3) v.l = ld_plain<16>(p.Xlo + off);
                 }
@@ -120,15 +120,13 @@ __global__ __launch_bounds__(256) void k_mfma_rows(MfmaArgs p) {
         }
     }
 
-    // ---- per-lane row pointers (rows past M are clamped for loads, never stored);
-    // an operator chosen by the BDF order of the current step starts at kbase
-    const size_t kbase = p.kstep ? (size_t)(bdf_order(*p.kstep) - 1) * p.a_kstride : 0;
+    // ---- per-lane row pointers (rows past M are clamped for loads, never stored)
     size_t rowoff[FM];
 #pragma unroll
     for (int f = 0; f < FM; ++f) {
         int r = rowbase + f * 16 + c16;
         r = r < p.M ? r : p.M - 1;
-        rowoff[f] = kbase + (size_t)r * p.a_rowstride;
+        rowoff[f] = (size_t)r * p.a_rowstride;
     }
 
     Acc4 Y[FM][FN], Z[FM][FN];
@@ -229,10 +227,11 @@ __global__ __launch_bounds__(256) void k_mfma_rows(MfmaArgs p) {
 template <class Acc>
 __global__ void k_hadamard(const Acc* __restrict__ P, int nz, int Bpad, int B, int Rp,
                            const Acc* __restrict__ lam, Acc* __restrict__ W) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y;
-    if (r >= Rp) return;
+    constexpr int KS = sizeof(Acc) == 8 ? 8 : 16, VEC = 16 / (int)sizeof(Acc);
+    const int r = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y, kt = (Rp + KS - 1) / KS * KS;
+    if (r >= kt) return;
     Acc s = 0, t = 0;
-    if (b < B) {
+    if (b < B && r < Rp) {
         // partials added in z order; 8 pairs of loads in flight
         const size_t zs = (size_t)Bpad * 2 * Rp;
         const Acc* pb = P + (size_t)b * 2 * Rp + r;
@@ -255,7 +254,7 @@ __global__ void k_hadamard(const Acc* __restrict__ P, int nz, int Bpad, int B, i
             t += pb[(size_t)z * zs + Rp];
         }
     }
-    W[(size_t)b * Rp + r] = lam[r] * s * t;
+    W[tile_off<KS, VEC>(kt, b, r)] = r < Rp ? lam[r] * s * t : 0;
 }
 
 // ---------------------------------------------------------------- planning, launch
@@ -373,7 +372,7 @@ static MfmaArgs fill_args(const MfmaPlan& pl, const void* A, const void* Alo, co
 
 static int mk_of(int dt) { return dt == DT_F64 ? MK_F64 : dt == DT_F32 ? MK_F32 : dt == DT_BF16 ? MK_BF16 : MK_BF16X3; }
 
-MfmaPlan mfma_dense_plan(int N, int Np, int Bpad, MfmaTile t) { return mfma_plan(MK_BF16, N, N, Np, Bpad, t); }
+MfmaPlan mfma_dense_plan(int dt, int N, int Np, int Bpad, MfmaTile t) { return mfma_plan(mk_of(dt), N, N, Np, Bpad, t); }
 
 void launch_mfma_dense(const MfmaPlan& pl, const void* C, int N, int Np, int Bpad, const void* X, const void* S,
                        void* part, hipStream_t s) {
@@ -385,7 +384,8 @@ MfmaPlan mfma_proj_plan(int dt, int Np, int Rp, int Bpad, MfmaTile t) { return m
 
 void launch_mfma_proj(int dt, const MfmaPlan& pl, const void* BCt, const void* BCt_lo, int Np, int Rp, int Bpad,
                       const void* X, const void* Xlo, void* part, hipStream_t s) {
-    const MfmaArgs a = fill_args(pl, BCt, BCt_lo, X, Xlo, nullptr, part, Np, 0, 2 * Rp, 1, Np, Bpad, 0);
+    MfmaArgs a = fill_args(pl, BCt, BCt_lo, X, Xlo, nullptr, part, Np, 0, 2 * Rp, 1, Np, Bpad, 0);
+    a.x_kt = gemm_kt(dt, Np);
     switch (dt) {
         case DT_F64: go_tile<DT_F64, MK_F64, false>(a, pl, s); break;
         case DT_F32: go_tile<DT_F32, MK_F32, false>(a, pl, s); break;
@@ -402,7 +402,8 @@ MfmaPlan mfma_scatter_plan(int dt, int N, int Rp, int Bpad, MfmaTile t) {
 
 void launch_mfma_scatter(int dt, const MfmaPlan& pl, const void* Af, const void* Af_lo, int N, int Rp, int Bpad,
                          const void* W, void* part, hipStream_t s) {
-    const MfmaArgs a = fill_args(pl, Af, Af_lo, W, nullptr, nullptr, part, Rp, 0, N, 1, Rp, Bpad, 0);
+    MfmaArgs a = fill_args(pl, Af, Af_lo, W, nullptr, nullptr, part, Rp, 0, N, 1, Rp, Bpad, 0);
+    a.x_kt = gemm_kt(dt == DT_F64 ? DT_F64 : DT_F32, Rp);
     switch (dt) {
         case DT_F64: go_tile<DT_F64, MK_F64, false>(a, pl, s); break;
         case DT_F32: go_tile<DT_F32, MK_F32, false>(a, pl, s); break;
@@ -411,19 +412,9 @@ void launch_mfma_scatter(int dt, const MfmaPlan& pl, const void* Af, const void*
     }
 }
 
-MfmaPlan mfma_helm_plan(int N, int Np, int Bpad, MfmaTile t) { return mfma_plan(MK_F64, N, 1, Np, Bpad, t); }
-
-void launch_mfma_helm(const MfmaPlan& pl, const double* hinv, int N, int Np, int Bpad, const double* rhs,
-                      const long long* stepp, double* part, hipStream_t s) {
-    MfmaArgs a = fill_args(pl, hinv, nullptr, rhs, nullptr, nullptr, part, Np, 0, N, 1, Np, Bpad, 0);
-    a.kstep = stepp;
-    a.a_kstride = (long long)N * Np;
-    go_tile<DT_F64, MK_F64, false>(a, pl, s);
-}
-
 void launch_hadamard(int dt, const void* P, int nz, int Bpad, int B, int Rp, const void* lam, void* W,
                      hipStream_t s) {
-    dim3 grid((Rp + 255) / 256, Bpad);
+    dim3 grid((gemm_kt(dt == DT_F64 ? DT_F64 : DT_F32, Rp) + 255) / 256, Bpad);
     if (dt == DT_F64)
         hipLaunchKernelGGL(k_hadamard<double>, grid, dim3(256), 0, s, (const double*)P, nz, Bpad, B, Rp,
                            (const double*)lam, (double*)W);

@@ -625,7 +625,7 @@ __device__ __forceinline__ void bdf_partials_body(const StepArgs& a, long long n
             write_level(a, n + 1, b, i, un);
             e = un * un;
         } else {
-            a.rhs[(size_t)b * a.Np + i] = rhs;
+            a.rhs[a.batched ? tile_off<8, 2>(a.Np, b, i) : (size_t)i] = rhs;
         }
     }
     if (DIAG) {

@@ -86,6 +86,16 @@ template <int V> struct DecodeBf16 {
 template <int V> struct Decode<DT_BF16, V> : DecodeBf16<V> {};
 template <int V> struct Decode<DT_BF16X3, V> : DecodeBf16<V> {};
 
+// ---------------------------------------------------------------- operand tiles
+
+// Element offset of (row, k) in the tiled layout of the skinny products (k_gemm.hip):
+// [row / 16][k / KS][k % KS / VEC][16 rows][VEC], kt = k extent padded to a multiple of KS.
+// A wavefront's fragment (16 rows, one step of KS) is one contiguous run.
+template <int KS, int VEC>
+__host__ __device__ __forceinline__ size_t tile_off(int kt, int row, int k) {
+    return ((size_t)(row >> 4) * kt + (k / KS) * KS) * 16 + (size_t)((k % KS / VEC * 16 + (row & 15)) * VEC + k % VEC);
+}
+
 // ---------------------------------------------------------------- reductions
 
 // Lane exchange within rows of 16 lanes (DPP row_ror:K, K = 1..15) and lane reads.

@@ -63,8 +63,23 @@ __device__ __forceinline__ double bdf_rhs_point(const StepArgs& a, long long n, 
     return bdf_rhs_hist(a, n, c, k, b, i, y, bdf_hist_point(a, n, k, b, i));
 }
 
-// Coefficient copies for the batched contraction ([Bpad][Np] layout).
+// Coefficient copies for the batched contraction: [Bpad][Np] and the j-weights of a dense
+// tensor, or tiled for the products with CP factors.
 __device__ __forceinline__ void write_ucv(const StepArgs& a, int b, int i, double u) {
+    if (a.ucv_kt) {
+        if (a.dtype == DT_F64) {
+            reinterpret_cast<double*>(a.ucv)[tile_off<8, 2>(a.ucv_kt, b, i)] = u;
+        } else if (a.dtype == DT_F32) {
+            reinterpret_cast<float*>(a.ucv)[tile_off<16, 4>(a.ucv_kt, b, i)] = (float)u;
+        } else {
+            const float f = (float)u;
+            const size_t o = tile_off<32, 8>(a.ucv_kt, b, i);
+            const unsigned short h = bf16_bits(f);
+            reinterpret_cast<unsigned short*>(a.ucv)[o] = h;
+            if (a.dtype == DT_BF16X3) reinterpret_cast<unsigned short*>(a.ucv_lo)[o] = bf16_bits(f - bf16_f(h));
+        }
+        return;
+    }
     const size_t o = (size_t)b * a.Np + i, oj = (size_t)i * a.Bpad + b;
     if (a.dtype == DT_F64) {
         reinterpret_cast<double*>(a.ucv)[o] = u;

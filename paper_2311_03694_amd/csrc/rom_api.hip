@@ -93,6 +93,10 @@ struct rom_ctx_s {
     // projection operator, [P + R][Np] (the P distinct columns of Bf, then the R columns of
     // Af, as rows), and with a dense stiffness its product with Hinv_k, [3][P + R][Np]
     int skew_layout = 0;
+    // tiled copies for the batched products (max_batch > 1; launch_gemm_tile): the sets Bf^T
+    // and Cf^T, Af, the pair form's three sets, Hinv_1..3
+    void *BCg = nullptr, *BCg_lo = nullptr, *Afg = nullptr, *Afg_lo = nullptr, *SKg = nullptr, *SKg_lo = nullptr;
+    double* hinvg = nullptr;
     void *SK = nullptr, *SK_lo = nullptr;
     void *Msk = nullptr, *Msk_lo = nullptr;
     // SVD form (svd): Ut [Rsp][Np] (columns of U as rows), sigma [Rsp] (accumulation
@@ -200,20 +204,15 @@ SkinnyPlan skinny_plan(rom_ctx c, int kind, int Bpad) {
         sp.nsplit = sp.m.nsplit;
     } else {
         sp.engine = 0;
-        sp.g = gemm_plan(M, Bpad, v);
+        sp.g = gemm_plan(M, Bpad, v > 0 ? v : 1);
         sp.nsplit = 1;
     }
     return sp;
 }
 
-void launch_proj(rom_ctx c, const SkinnyPlan& sp, int Bpad, const void* X, const void* Xlo, void* P, hipStream_t s) {
-    if (sp.engine == 1) launch_mfma_proj(c->dtype, sp.m, c->BCt, c->BCt_lo, c->Np, c->Rp, Bpad, X, Xlo, P, s);
-    else launch_gemm_proj(c->dtype, sp.g, c->BCt, c->BCt_lo, c->Np, c->Rp, Bpad, X, Xlo, P, s);
-}
-
 void launch_scatter(rom_ctx c, const SkinnyPlan& sp, int Bpad, const void* W, void* Y, hipStream_t s) {
     if (sp.engine == 1) launch_mfma_scatter(c->dtype, sp.m, c->Af, c->Af_lo, c->N, c->Rp, Bpad, W, Y, s);
-    else launch_gemm_scatter(c->dtype, sp.g, c->Af, c->Af_lo, c->N, c->Rp, Bpad, W, Y, s);
+    else launch_gemm_scatter(c->dtype, sp.g, c->Afg, c->Afg_lo, c->N, c->Rp, Bpad, W, Y, s);
 }
 
 // Batched CP term Y = Af (lam . Bf^T U . Cf^T U) (eq. tc_ap).  On the skinny GEMM the
@@ -229,15 +228,15 @@ bool launch_cp_batched(rom_ctx c, const SkinnyPlan& pp, const SkinnyPlan& ps, in
     // batches take it only when knob 4 asks for it explicitly (value 1).
     const SkewPairs sk = c->tile[4] == 1 ? skew_of(c) : SkewPairs{};
     if (pp.engine == 0 && sk.layout) {
-        launch_gemm_proj_skew(c->dtype, pp.g, c->SK, c->SK_lo, c->Np, sk.P, sk.layout, c->Rp, Bpad, X, Xlo, c->lam, W, s);
+        launch_gemm_proj_skew(c->dtype, pp.g, c->SKg, c->SKg_lo, c->Np, sk.P, sk.layout, c->Rp, Bpad, X, Xlo, c->lam, W, s);
     } else if (pp.engine == 0) {
-        launch_gemm_proj_pair(c->dtype, pp.g, c->BCt, c->BCt_lo, c->Np, c->Rp, Bpad, X, Xlo, c->lam, W, s);
+        launch_gemm_proj_pair(c->dtype, pp.g, c->BCg, c->BCg_lo, c->Np, c->Rp, Bpad, X, Xlo, c->lam, W, s);
     } else {
-        launch_proj(c, pp, Bpad, X, Xlo, P, s);
+        launch_mfma_proj(c->dtype, pp.m, c->BCt, c->BCt_lo, c->Np, c->Rp, Bpad, X, Xlo, P, s);
         launch_hadamard(c->dtype, P, pp.nsplit, Bpad, B, c->Rp, c->lam, W, s);
     }
     if (sa && ps.engine == 0) {
-        launch_gemm_scatter_step(c->dtype, ps.g, c->Af, c->Af_lo, c->N, c->Rp, Bpad, W, *sa, c->diagA ? 1 : 0, s);
+        launch_gemm_scatter_step(c->dtype, ps.g, c->Afg, c->Afg_lo, c->N, c->Rp, Bpad, W, *sa, c->diagA ? 1 : 0, s);
         return true;
     }
     launch_scatter(c, ps, Bpad, W, Y, s);
@@ -279,8 +278,10 @@ struct WsPlan {
     size_t total = 0;
 };
 
-// fold_splits > 0 bounds the partial tiles of a batched folded contraction.
-WsPlan plan_ws(rom_ctx c, int B, int fold_splits = 0) {
+// splits > 0 asks for a smaller workspace: at most that many partial tiles of a batched folded
+// contraction, and y of the batched CP products in the place of the operand copies (such a
+// plan's contraction runs once: it overwrites them).
+WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
     WsPlan p;
     p.B = B;
     p.Bpad = (B + 15) / 16 * 16;
@@ -301,10 +302,11 @@ WsPlan plan_ws(rom_ctx c, int B, int fold_splits = 0) {
         }
     } else {
         const size_t eb = elem_bytes(c->dtype);
+        size_t part_end = 0;
         if (c->dense) {
             if (c->F) {
-                if (fold_splits > 0) {
-                    p.pf = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, fold_splits);
+                if (splits > 0) {
+                    p.pf = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, splits);
                 } else {
                     if (c->fplan_B != p.Bpad || c->fplan_v != c->tile[1]) {
                         c->fplan = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, 0);
@@ -325,22 +327,47 @@ WsPlan plan_ws(rom_ctx c, int B, int fold_splits = 0) {
             p.ps = skinny_plan(c, 3, p.Bpad);
             p.nsplit = p.ps.nsplit;
             p.part2_off = off;
-            off = align256(off + (size_t)p.pp.nsplit * p.Bpad * 2 * c->Rp * ab);
+            if (p.pp.engine == 1) off = align256(off + (size_t)p.pp.nsplit * p.Bpad * 2 * c->Rp * ab);
             p.w_off = off;
-            off = align256(off + (size_t)p.Bpad * c->Rp * ab);
+            off = align256(off + (size_t)p.Bpad * gemm_kt(c->dtype == DT_F64 ? DT_F64 : DT_F32, c->Rp) * ab);
             p.part_off = off;
-            off = align256(off + (size_t)p.ps.nsplit * p.Bpad * c->N * ab);
+            const size_t part = align256((size_t)p.ps.nsplit * p.Bpad * c->N * ab);
+            if (splits == 0 || p.pp.engine != 0 || p.ps.engine != 0) off += part;
+            else part_end = off + part;
         }
+        const size_t urow = c->dense ? c->Np : gemm_kt(c->dtype, c->Np);
         p.ucv_off = off;
-        off = align256(off + (size_t)p.Bpad * c->Np * eb);
+        off = align256(off + (size_t)p.Bpad * urow * eb);
         p.ucvlo_off = off;
-        off = align256(off + (c->dtype == DT_BF16X3 ? (size_t)p.Bpad * c->Np * 2 : 0));
+        off = align256(off + (c->dtype == DT_BF16X3 ? (size_t)p.Bpad * urow * 2 : 0));
         p.usc_off = off;
-        off = align256(off + (size_t)p.Bpad * c->Np * ab);
-        if (!c->diagA) p.ph = gemm_plan(c->N, p.Bpad, 0);
+        if (c->dense) off = align256(off + (size_t)p.Bpad * c->Np * ab);
+        if (off < part_end) off = part_end;
+        if (!c->diagA) p.ph = gemm_plan(c->N, p.Bpad, 1);
     }
     p.total = off + 256;
     return p;
+}
+
+// The workspace by which rom_nonlinear_noalloc decides whether it serves a batch: partial
+// tiles, products and operand copies in rows, whatever plan the kernels then take (never a
+// larger one), so that the batches it serves do not move with the kernels.
+size_t noalloc_bytes(rom_ctx c, int B) {
+    if (B == 1) return plan_ws(c, 1).total;
+    const size_t Bpad = (B + 15) / 16 * 16, ab = acc_bytes(c->dtype), eb = elem_bytes(c->dtype);
+    size_t off = 0;
+    if (c->dense) {
+        const int np = dense_partials(c->dtype, c->N, c->Np, (int)Bpad, c->tile[1], c->lds_max);
+        off = align256((size_t)np * Bpad * c->N * ab);
+    } else {
+        const SkinnyPlan pp = skinny_plan(c, 2, (int)Bpad), ps = skinny_plan(c, 3, (int)Bpad);
+        off = align256((size_t)pp.nsplit * Bpad * 2 * c->Rp * ab);
+        off = align256(off + Bpad * c->Rp * ab);
+        off = align256(off + (size_t)ps.nsplit * Bpad * c->N * ab);
+    }
+    off = align256(off + Bpad * c->Np * eb);
+    off = align256(off + (c->dtype == DT_BF16X3 ? Bpad * c->Np * 2 : 0));
+    return align256(off + Bpad * c->Np * ab) + 256;
 }
 
 // The batched dense contraction of plan p: partial tiles in `part`.
@@ -501,6 +528,48 @@ static rom_status hinv_products(rom_ctx c, const double* host_rows, size_t rows,
     if (x_d) hipFree(x_d);
     if (y_d) hipFree(y_d);
     if (e != hipSuccess) return fail(ROM_E_DEVICE, "setup of the projection operators failed: %s", hipGetErrorString(e));
+    return ROM_OK;
+}
+
+// Tiled copies of the operators that the batched step products read (k_gemm.hip).
+static rom_status tile_operators(rom_ctx c) {
+    const int dt = c->dtype, eb = (int)elem_bytes(dt), N = c->N, Np = c->Np, Rp = c->Rp;
+    auto make = [&](void** dst, const void* src, int eb2, int sdt, int rows, int tiled_rows, int K, long long ld, int sets,
+                    const int* r0, const int* rmul) -> rom_status {
+        // each set holds tiled_rows rows, `rows` of them from src
+        const size_t set = gemm_tiled_elems(sdt, tiled_rows, K);
+        TRYS(dmalloc(dst, set * sets * eb2, &c->bytes, &c->allocs));
+        if (tiled_rows == rows) {
+            launch_gemm_tile(eb2, sdt, src, *dst, rows, K, ld, sets, r0, rmul, c->stream);
+        } else {
+            HIPCHK(hipMemsetAsync(*dst, 0, set * sets * eb2, c->stream));
+            for (int q = 0; q < sets; ++q)
+                launch_gemm_tile(eb2, sdt, src, (char*)*dst + set * q * eb2, rows, K, ld, 1, r0 + q, rmul + q, c->stream);
+        }
+        HIPCHK(hipGetLastError());
+        return ROM_OK;
+    };
+    const int one[3] = {1, 1, 1};
+    if (!c->diagA) {
+        const int r0[3] = {0, N, 2 * N};
+        TRYS(make((void**)&c->hinvg, c->hinv, 8, DT_F64, N, N, Np, Np, 3, r0, one));
+    }
+    if (c->dense || c->svd) return ROM_OK;
+    const int sdt = dt == DT_F64 ? DT_F64 : DT_F32;      // the scatter's product
+    const int bc0[2] = {0, Rp}, zero[1] = {0};
+    TRYS(make(&c->BCg, c->BCt, eb, dt, Rp, Rp, Np, Np, 2, bc0, one));
+    TRYS(make(&c->Afg, c->Af, eb, sdt, N, N, Rp, Rp, 1, zero, one));
+    if (c->BCt_lo) {
+        TRYS(make(&c->BCg_lo, c->BCt_lo, 2, dt, Rp, Rp, Np, Np, 2, bc0, one));
+        TRYS(make(&c->Afg_lo, c->Af_lo, 2, sdt, N, N, Rp, Rp, 1, zero, one));
+    }
+    if (c->skew_layout) {
+        // per pair: its Bf column, then its two columns of Af
+        const int P = c->R / 2, il = c->skew_layout == 1;
+        const int r0[3] = {0, P, il ? P + 1 : 2 * P}, rm[3] = {1, il ? 2 : 1, il ? 2 : 1};
+        TRYS(make(&c->SKg, c->SK, eb, dt, P, Rp / 2, Np, Np, 3, r0, rm));
+        if (c->SK_lo) TRYS(make(&c->SKg_lo, c->SK_lo, 2, dt, P, Rp / 2, Np, Np, 3, r0, rm));
+    }
     return ROM_OK;
 }
 
@@ -863,6 +932,7 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
             }
         }
     }
+    if (c->max_batch > 1) TRY(tile_operators(c));
     HTRY(hipStreamSynchronize(c->stream));
     *out = c;
 #undef TRY
@@ -1260,7 +1330,7 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
         } else if (s->B == 1) {
             launch_helm_apply(a, stream);
         } else {
-            launch_gemm_helm(p.ph, c->hinv, c->N, c->Np, p.Bpad, a.rhs, a.step, nullptr, &a, stream);
+            launch_gemm_helm(p.ph, c->hinvg, c->N, c->Np, p.Bpad, a.rhs, a.step, a, stream);
         }
     }
     HIPCHK(hipGetLastError());
@@ -1277,19 +1347,18 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     if (batch < 1 || batch > c->max_batch) return fail(ROM_E_INVALID, "batch %d outside [1, %d]", batch, c->max_batch);
     if (!u_dev || !y_dev) return fail(ROM_E_INVALID, "u_dev / y_dev is NULL");
     WsPlan p = plan_ws(c, batch);
-    // a bounded workspace: fewer partial tiles where the usual plan's do not fit
-    for (int ns = p.nsplit; ws_given && c->F && batch > 1 && p.total > ws_given_bytes && ns > 1;) {
-        ns /= 2;
-        p = plan_ws(c, batch, ns);
-    }
+    // a bounded workspace: a smaller plan where the usual one does not fit
+    for (int ns = p.nsplit; ws_given && batch > 1 && p.total > ws_given_bytes && ns > 0; ns /= 2)
+        p = plan_ws(c, batch, ns > 1 ? ns / 2 : 1);
     char* ws = ws_given;
     if (ws) {
         // a caller-chosen workspace: it must hold the plan, and what the kernels may
         // read beyond the regions they write (lane vectors run up to one k-step past
         // the last row) must be zero, as a fresh workspace is
-        if (p.total > ws_given_bytes)
+        const size_t need = std::max(noalloc_bytes(c, batch), p.total);
+        if (need > ws_given_bytes)
             return fail(ROM_E_UNSUPPORTED, "the evaluation needs %zu bytes of workspace, more than the %zu available",
-                        p.total, ws_given_bytes);
+                        need, ws_given_bytes);
         launch_zero_fill(ws, p.total, c->stream);
     } else {
         rom_status st = ensure_ws(c, p.total);
@@ -1306,6 +1375,7 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
         a.Bpad = p.Bpad;
         a.dtype = c->dtype;
         a.batched = 1;
+        a.ucv_kt = c->dense ? 0 : gemm_kt(c->dtype, c->Np);
         a.ucv = ws + p.ucv_off;
         a.ucv_lo = ws + p.ucvlo_off;
         a.uj = ws + p.usc_off;
@@ -1613,12 +1683,13 @@ extern "C" rom_status rom_state_create(rom_ctx c, int32_t batch, const double* u
         }
     }
     if (a.batched) {
-        const size_t cells = (size_t)s->Bpad * c->Np;
+        a.ucv_kt = c->dense ? 0 : gemm_kt(c->dtype, c->Np);
+        const size_t cells = (size_t)s->Bpad * (c->dense ? c->Np : a.ucv_kt);
         TRY(dmalloc(&a.ucv, cells * elem_bytes(c->dtype), &s->bytes, &s->allocs));
-        TRY(dmalloc(&a.uj, cells * acc_bytes(c->dtype), &s->bytes, &s->allocs));
+        if (c->dense) TRY(dmalloc(&a.uj, cells * acc_bytes(c->dtype), &s->bytes, &s->allocs));
         if (c->dtype == DT_BF16X3) TRY(dmalloc(&a.ucv_lo, cells * 2, &s->bytes, &s->allocs));
         if (hipMemsetAsync(a.ucv, 0, cells * elem_bytes(c->dtype), c->stream) != hipSuccess ||
-            hipMemsetAsync(a.uj, 0, cells * acc_bytes(c->dtype), c->stream) != hipSuccess ||
+            (a.uj && hipMemsetAsync(a.uj, 0, cells * acc_bytes(c->dtype), c->stream) != hipSuccess) ||
             (a.ucv_lo && hipMemsetAsync(a.ucv_lo, 0, cells * 2, c->stream) != hipSuccess)) {
             rom_state_destroy(s);
             return fail(ROM_E_DEVICE, "state clear failed");

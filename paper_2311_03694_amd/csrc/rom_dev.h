@@ -34,7 +34,8 @@ struct StepArgs {
     int* closep;             // 1: the energy of level n is still to be summed
     double* elog;            // [cap][B] energy per level
     long long elog_cap;
-    double* rhs;             // [Bpad][Np] right-hand sides (dense stiffness; padding zero)
+    double* rhs;             // [Np] right-hand side (dense stiffness; padding zero), for batches
+                             // [Bpad][Np] tiled (tile_off<8, 2>)
     double* epart;           // [2][B][enmax] per-block energy partials of a level,
                              // parity slot (level & 1)
     int* ecount;             // [2] partials per trajectory of a level, same parity slots
@@ -58,6 +59,8 @@ struct StepArgs {
     void* st;                // CP, one trajectory: w = lam .* (Bf^T u) .* (Cf^T u) of the
                              // newest level [Rp] (accumulation type)
     int Bpad, Np;
+    int ucv_kt;              // CP factors: ucv is tiled (tile_off) with rows of ucv_kt elements and uj
+                             // is not written; 0: the layouts above
     int dtype;               // Dt of the contraction
     int batched;             // 1: write ucv/uj for the batched contraction
 };
@@ -342,9 +345,9 @@ void launch_full_x(const StepArgs& a, double* X, hipStream_t s);
 // Batched contraction launchers (k_mfma.hip).  Partials are [nsplit][Bpad][M] in the
 // accumulation type (FP64 for DT_F64, FP32 otherwise).
 //   dense:   M = N rows of the BF16 tensor C [N][N][Np], X = u [Bpad][Np] and j-weights S [Np][Bpad]
-//   proj:    M = 2Rp rows of [Bf|Cf]^T [2Rp][Np], X = u [Bpad][Np]
-//   scatter: M = N rows of Af [N][Rp], X = W [Bpad][Rp] (FP32, FP64 for DT_F64)
-MfmaPlan mfma_dense_plan(int N, int Np, int Bpad, MfmaTile t);
+//   proj:    M = 2Rp rows of [Bf|Cf]^T [2Rp][Np], X = u [Bpad][Np], tiled
+//   scatter: M = N rows of Af [N][Rp], X = W [Bpad][Rp] (FP32, FP64 for DT_F64), tiled
+MfmaPlan mfma_dense_plan(int dt, int N, int Np, int Bpad, MfmaTile t);
 void launch_mfma_dense(const MfmaPlan& pl, const void* C, int N, int Np, int Bpad, const void* X, const void* S,
                        void* part, hipStream_t s);
 MfmaPlan mfma_proj_plan(int dt, int Np, int Rp, int Bpad, MfmaTile t);
@@ -353,11 +356,6 @@ void launch_mfma_proj(int dt, const MfmaPlan& pl, const void* BCt, const void* B
 MfmaPlan mfma_scatter_plan(int dt, int N, int Rp, int Bpad, MfmaTile t);
 void launch_mfma_scatter(int dt, const MfmaPlan& pl, const void* Af, const void* Af_lo, int N, int Rp, int Bpad,
                          const void* W, void* part, hipStream_t s);
-// Batched Helmholtz apply: partials [nsplit][Bpad][N] (FP64) of Hinv_k rhs, with k read
-// from the device step counter; Hinv [3][N][Np], rhs [Bpad][Np].
-MfmaPlan mfma_helm_plan(int N, int Np, int Bpad, MfmaTile t);
-void launch_mfma_helm(const MfmaPlan& pl, const double* hinv, int N, int Np, int Bpad, const double* rhs,
-                      const long long* stepp, double* part, hipStream_t s);
 // Batched dense contraction of the BF16 format with the coefficient fragments held in
 // registers (k_kr.hip).  Partials [nsplit][Bpad][N]; X = u [Bpad][Np], j-weights S
 // [Np][Bpad]; the tensor comes from the tiled copy Ct [ceil(N/16)][N][Kt/VEC][16][VEC] made by
@@ -372,7 +370,6 @@ int kr_variants();
 int kr_tiled_k(int N);
 size_t kr_tiled_bytes(int N);
 void launch_kr_tile(const void* src, void* dst, int N, int Np, hipStream_t s);
-KrPlan kr_plan(int M, int J, int Kt, int Bpad, int variant, size_t lds_max);
 void launch_kr_dense(const KrPlan& pl, const void* Ct, int N, int Np, int Bpad, const void* X, const void* S, void* part,
                      hipStream_t s);
 // Allow every variant up to `lds` bytes of dynamic LDS.
@@ -388,6 +385,9 @@ struct DensePlan {
 };
 int dense_batched_variants();
 DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max);
+// Partial tiles of an unfolded contraction in format dt: which batches rom_nonlinear_noalloc
+// serves is counted with them in every format.
+int dense_partials(int dt, int N, int Np, int Bpad, int variant, size_t lds_max);
 void launch_dense_batched(const DensePlan& pl, const void* C, const void* Ct, int N, int Np, int Bpad, const void* X,
                           const void* S, void* part, hipStream_t s);
 
@@ -423,20 +423,29 @@ GemmPlan gemm_plan(int M, int Bpad, int variant);
 // The plan of an FP64 product over K whose short column side leaves the device
 // underfilled: K split into ksplit ranges, one partial product each.
 GemmPlan gemm_plan_splitk(int M, int K, int Bpad);
-void launch_gemm_proj(int dt, const GemmPlan& pl, const void* BCt, const void* BCt_lo, int Np, int Rp, int Bpad,
-                      const void* X, const void* Xlo, void* P, hipStream_t s);
+// Operands of the batched step products are tiled (tile_off, kcommon.h): K padded to whole
+// steps of the format (gemm_kt), rows to 16.  launch_gemm_tile makes `sets` consecutive tiled
+// copies of rows r0[q] + rmul[q] * row (row < rows) of a row-major operator of pitch ld;
+// words of FP32 products over BF16 factors (the CP scatter) take the FP32 steps (sdt = FP32).
+int gemm_kt(int dt, int K);
+size_t gemm_tiled_elems(int sdt, int rows, int K);
+void launch_gemm_tile(int eb, int sdt, const void* src, void* dst, int rows, int K, long long ld, int sets, const int* r0,
+                      const int* rmul, hipStream_t s);
+// CP projections with their Hadamard product: W tiled, from the tiled sets Bf^T, Cf^T; or from
+// the pair form's three sets (Bf columns, Af columns c0 and c1 of the pairs).
+void launch_gemm_proj_pair(int dt, const GemmPlan& pl, const void* BCt, const void* BCt_lo, int Np, int Rp, int Bpad,
+                           const void* X, const void* Xlo, const void* lam, void* W, hipStream_t s);
 void launch_gemm_proj_skew(int dt, const GemmPlan& pl0, const void* SK, const void* SK_lo, int Np, int P, int layout,
                            int Rp, int Bpad, const void* X, const void* Xlo, const void* lam, void* W, hipStream_t s);
-void launch_gemm_proj_pair(int dt, const GemmPlan& pl, const void* BCt, const void* BCt_lo, int Np, int Rp,
-                           int Bpad, const void* X, const void* Xlo, const void* lam, void* W, hipStream_t s);
-void launch_gemm_scatter_step(int dt, const GemmPlan& pl, const void* Af, const void* Af_lo, int N, int Rp,
-                              int Bpad, const void* W, const StepArgs& st, int diag, hipStream_t s);
+void launch_gemm_scatter_step(int dt, const GemmPlan& pl, const void* Af, const void* Af_lo, int N, int Rp, int Bpad,
+                              const void* W, const StepArgs& st, int diag, hipStream_t s);
 void launch_gemm_scatter(int dt, const GemmPlan& pl, const void* Af, const void* Af_lo, int N, int Rp, int Bpad,
                          const void* W, void* Y, hipStream_t s);
 void launch_gemm_f64(const GemmPlan& pl, const double* A, long long lda, const double* X, long long ldx, double* Y,
                      int M, int K, int Bpad, hipStream_t s);
+// u^{n+1} = Hinv_k rhs of a step (tiled Hinv sets k = 1, 2, 3 and rhs), with the step close.
 void launch_gemm_helm(const GemmPlan& pl, const double* hinv, int N, int Np, int Bpad, const double* rhs,
-                      const long long* stepp, double* Y, const StepArgs* st, hipStream_t s);
+                      const long long* stepp, const StepArgs& st, hipStream_t s);
 
 // A batched CP product of a context: variants [0, gemm_variants()) select k_gemm, the
 // following mfma_variants() the LDS-tile kernel; -1 = default.
@@ -447,7 +456,7 @@ struct SkinnyPlan {
     int nsplit;
 };
 
-// W[b][r] = lam_r s_r t_r from projection partials P [nz][Bpad][2Rp].
+// W[b][r] = lam_r s_r t_r (tiled) from projection partials P [nz][Bpad][2Rp].
 void launch_hadamard(int dt, const void* P, int nz, int Bpad, int B, int Rp, const void* lam, void* W,
                      hipStream_t s);
 
