@@ -32,6 +32,133 @@ __global__ __launch_bounds__(256) void k_cp_scatter1(Scat1Job jb, double* y_out)
         cp_scatter1_body<DT, V, U, MODE, FULL>(jb, y_out, blockIdx.x, MODE == 0 ? 0LL : *jb.a.step);
     }
 }
+
+// ============================================================== small evaluations
+//
+// y = Af (lam .* s .* t) of a small CP operator in one launch: every block forms all of w in
+// LDS (each wavefront its share of the row pairs, four at a time) and then its own rows of
+// y, so the second kernel, its launch and the trip of w through memory go; the price is the
+// projection rows read by every block.  Dot products keep cp_proj1_body's, cp_proj_skew_body's
+// and cp_scatter1_body's lane partition and order, so results are theirs to the bit.  Bound
+// by latency: N = 37, R = 40 in FP64 took 3.7 us on the device against 5.3, and 4.8 us per
+// call against 8.1.  A pair costs a wavefront about 0.5 us of reductions, so it is taken up to
+// kSmallMost pairs (R = 80 in pair form) and kSmallBytes of projection rows: N = R = 64 in
+// FP64 4.8 against 5.3 us, N = 50, R = 100 6.5 against 5.3.
+constexpr size_t kSmallBytes = 48 << 10;
+constexpr int kSmallWaves = 16, kSmallMost = 40;
+template <int DT> constexpr int kSmallPairs = DT == DT_BF16X3 ? 2 : 4;
+
+template <int DT, int V, int NR>
+__device__ __forceinline__ void cp_w_in_lds(const Proj1Job& jb, const LdsU<DT>& L, const LdsU<DT>& Ln,
+                                            typename Store<DT>::Acc* W) {
+    typedef typename Store<DT>::T T;
+    typedef typename Store<DT>::Acc Acc;
+    constexpr bool X3 = (DT == DT_BF16X3), NEGU = (DT == DT_BF16 || DT == DT_BF16X3);
+    typedef typename RawT<V * (int)sizeof(T)>::T Raw;
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int Np = jb.Np, P = jb.P, np = NR == 3 ? P : jb.Rp, k = lane * V;
+    const T* op = reinterpret_cast<const T*>(jb.BCt);
+    const Acc* lam = reinterpret_cast<const Acc*>(jb.lam);
+    auto cols = [&](int q, int& c0, int& c1) {
+        c0 = jb.layout == 1 ? 2 * q : q;
+        c1 = jb.layout == 1 ? 2 * q + 1 : P + q;
+    };
+    Raw rv[kSmallPairs<DT>][NR], rl[kSmallPairs<DT>][NR];
+    Acc lv[kSmallPairs<DT>][2];
+    auto issue = [&](int q0) {
+#pragma unroll
+        for (int e = 0; e < kSmallPairs<DT>; ++e) {
+            const int q = q0 + e * kSmallWaves;
+            if (q >= np) continue;
+            int c0, c1;
+            cols(q, c0, c1);
+            const int rows[3] = {q, NR == 3 ? P + c0 : jb.Rp + q, P + c1};
+            lv[e][0] = lam[NR == 3 ? c0 : q];
+            lv[e][1] = NR == 3 ? lam[c1] : 0;
+#pragma unroll
+            for (int h = 0; h < NR; ++h)
+                if (k < Np) {
+                    rv[e][h] = ld_plain<V * (int)sizeof(T)>(op + (size_t)rows[h] * Np + k);
+                    if constexpr (X3) rl[e][h] = ld_plain<V * (int)sizeof(T)>(jb.BCt_lo + (size_t)rows[h] * Np + k);
+                }
+        }
+    };
+    issue(w);
+    L.fill(jb.u_base, jb.N, Np);
+    if constexpr (NEGU && NR == 3) Ln.fill(jb.u_base, jb.N, Np, -1.0);
+    __syncthreads();
+    for (int q0 = w; q0 < np; q0 += kSmallPairs<DT> * kSmallWaves) {
+        if (q0 != w) issue(q0);
+#pragma unroll
+        for (int e = 0; e < kSmallPairs<DT>; ++e) {
+            const int q = q0 + e * kSmallWaves;
+            if (q >= np) continue;
+            Acc z[NR];
+#pragma unroll
+            for (int h = 0; h < NR; ++h) {
+                z[h] = 0;
+                if (k < Np) z[h] += dot_vec<DT, V>(rv[e][h], rl[e][h], NEGU && NR == 3 && h == 1 ? Ln : L, k);
+                z[h] = wave_sum(z[h]);
+            }
+            if (lane == 0) {
+                if constexpr (NR == 3) {
+                    int c0, c1;
+                    cols(q, c0, c1);
+                    W[c0] = lv[e][0] * z[0] * z[2];
+                    W[c1] = lv[e][1] * z[0] * (NEGU ? z[1] : -z[1]);
+                } else {
+                    W[q] = lv[e][0] * z[0] * z[1];
+                }
+            }
+        }
+    }
+    if (NR == 3 && (int)threadIdx.x < jb.Rp - jb.R) W[jb.R + threadIdx.x] = 0;   // padding past R
+}
+
+template <int DT, int V>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_cp_eval_small(Proj1Job pj, Scat1Job sj, double* __restrict__ y) {
+    typedef typename Store<DT>::T T;
+    typedef typename Store<DT>::Acc Acc;
+    constexpr bool X3 = (DT == DT_BF16X3), NEGU = (DT == DT_BF16 || DT == DT_BF16X3);
+    typedef typename RawT<V * (int)sizeof(T)>::T Raw;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const size_t ub = LdsU<DT>::bytes(pj.Np);
+    LdsU<DT> L, Ln;
+    L.bind(smem, pj.Np);
+    Ln.bind(smem + (NEGU ? ub : 0), pj.Np);
+    Acc* W = reinterpret_cast<Acc*>(smem + (NEGU ? 2 : 1) * ub);
+    const int lane = threadIdx.x % kWave, i = (int)blockIdx.x * kSmallWaves + threadIdx.x / kWave;
+    const int R = sj.Rp;
+    const bool live = i < sj.N;
+    // the wavefront's row of Af, ahead of the projections
+    Raw rv, rl;
+    const int r = lane * V;
+    if (live && r < R) {
+        rv = ld_plain<V * (int)sizeof(T)>(reinterpret_cast<const T*>(sj.Af) + (size_t)i * R + r);
+        if constexpr (X3) rl = ld_plain<V * (int)sizeof(T)>(sj.Af_lo + (size_t)i * R + r);
+    }
+    if (pj.layout) cp_w_in_lds<DT, V, 3>(pj, L, Ln, W);
+    else cp_w_in_lds<DT, V, 2>(pj, L, Ln, W);
+    __syncthreads();
+    if (!live) return;
+    Acc z = 0;
+    if (r < R) {
+        Acc cv[V];
+        Decode<DT, V>::run(rv, cv);
+        if constexpr (X3) {
+            float cl[V];
+            Decode<DT, V>::run(rl, cl);
+#pragma unroll
+            for (int v = 0; v < V; ++v) z += (cv[v] + cl[v]) * W[r + v];
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) z += cv[v] * W[r + v];
+        }
+    }
+    z = wave_sum(z);
+    if (lane == 0) y[i] = (double)z;
+}
+
 // ============================================================== Helmholtz apply and projections
 
 // One state: nh + np blocks and a last one that closes the previous level and advances
@@ -109,9 +236,8 @@ static void proj1_dispatch(int dt, const Proj1Job& jb, hipStream_t s) {
 // of the pair form, per block.
 int proj1_blocks(int Rp, SkewPairs sk) { return sk.layout ? (Rp / 2 + 3) / 4 : (Rp + 3) / 4; }
 
-int launch_cp_proj1(int dt, const void* BCt, const void* BCt_lo, const void* lam, int N, int Np, int Rp,
-                    SkewPairs sk, const double* u_base, const long long* stepp, long long slot_stride,
-                    void* w, hipStream_t s) {
+static Proj1Job proj1_job(const void* BCt, const void* BCt_lo, const void* lam, int N, int Np, int Rp, SkewPairs sk,
+                          const double* u_base, const long long* stepp, long long slot_stride, void* w) {
     Proj1Job jb{};
     jb.BCt = BCt;
     jb.BCt_lo = (const unsigned short*)BCt_lo;
@@ -127,8 +253,44 @@ int launch_cp_proj1(int dt, const void* BCt, const void* BCt_lo, const void* lam
     jb.slot_stride = slot_stride;
     jb.w = w;
     jb.nblk = proj1_blocks(Rp, sk);
-    proj1_dispatch(dt, jb, s);
+    return jb;
+}
+
+int launch_cp_proj1(int dt, const void* BCt, const void* BCt_lo, const void* lam, int N, int Np, int Rp,
+                    SkewPairs sk, const double* u_base, const long long* stepp, long long slot_stride,
+                    void* w, hipStream_t s) {
+    proj1_dispatch(dt, proj1_job(BCt, BCt_lo, lam, N, Np, Rp, sk, u_base, stepp, slot_stride, w), s);
     return 0;
+}
+
+template <int DT>
+static void eval_small_go(const Proj1Job& pj, const Scat1Job& sj, double* y, hipStream_t s) {
+    constexpr int V = 16 / (int)sizeof(typename Store<DT>::T);
+    const size_t lds = proj_lds<DT>(pj.Np) + sizeof(typename Store<DT>::Acc) * (size_t)pj.Rp;
+    hipLaunchKernelGGL((k_cp_eval_small<DT, V>), dim3((unsigned)((sj.N + kSmallWaves - 1) / kSmallWaves)),
+                       dim3(64 * kSmallWaves), lds, s, pj, sj, y);
+}
+
+bool launch_cp_eval_small(int dt, const void* BCt, const void* BCt_lo, const void* lam, const void* Af, const void* Af_lo,
+                          int N, int Np, int Rp, SkewPairs sk, const double* u, double* y, hipStream_t s) {
+    const int eb = dt == DT_F64 ? 8 : dt == DT_F32 ? 4 : 2, V = 16 / eb;
+    const size_t rows = sk.layout ? (size_t)sk.P + sk.R : (size_t)2 * Rp;
+    const size_t bytes = rows * Np * (dt == DT_BF16X3 ? 4 : eb);
+    // one lane vector per row
+    if (Np > kWave * V || Rp > kWave * V || (sk.layout ? sk.P : Rp) > kSmallMost || bytes > kSmallBytes) return false;
+    const Proj1Job pj = proj1_job(BCt, BCt_lo, lam, N, Np, Rp, sk, u, nullptr, 0, nullptr);
+    Scat1Job sj{};
+    sj.Af = Af;
+    sj.Af_lo = (const unsigned short*)Af_lo;
+    sj.N = N;
+    sj.Rp = Rp;
+    switch (dt) {
+        case DT_F64: eval_small_go<DT_F64>(pj, sj, y, s); break;
+        case DT_F32: eval_small_go<DT_F32>(pj, sj, y, s); break;
+        case DT_BF16: eval_small_go<DT_BF16>(pj, sj, y, s); break;
+        default: eval_small_go<DT_BF16X3>(pj, sj, y, s); break;
+    }
+    return true;
 }
 
 template <int DT, int MODE>

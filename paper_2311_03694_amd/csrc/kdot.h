@@ -37,7 +37,7 @@ template <int DT> struct LdsU {
     }
 
     // Entry q of the image from the FP64 value v.
-    __device__ __forceinline__ void put(int q, double v) {
+    __device__ __forceinline__ void put(int q, double v) const {
         if constexpr (DT == DT_F64) {
             uh[q] = v;
         } else if constexpr (DT == DT_F32) {
@@ -57,7 +57,7 @@ template <int DT> struct LdsU {
 
     // Convert sgn * u (FP64, N values, sgn = +1 or -1) into an image of Np >= N entries,
     // zero beyond N; call with the whole block, then __syncthreads.
-    __device__ void fill(const double* __restrict__ u, int N, int Np, double sgn = 1.0) {
+    __device__ void fill(const double* __restrict__ u, int N, int Np, double sgn = 1.0) const {
         staged_copy<8, double>(
             Np, [&](int q) { return q < N ? sgn * u[q] : 0.0; }, [&](int q, double v) { put(q, v); });
     }

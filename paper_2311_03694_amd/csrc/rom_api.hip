@@ -712,7 +712,9 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
         c->device = dev;
         HTRY(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
         size_t want = lds > 122880 ? 122880 : (size_t)lds;
-        if (want > 65536 && (kr_set_lds_limit(want) != hipSuccess || fold_set_lds_limit(want) != hipSuccess)) {
+        // (only the dense tensor's batched kernels ask for more than 64 KB)
+        const bool raise = want > 65536 && c->dense && c->max_batch > 1;
+        if (raise && (c->dtype == DT_BF16 ? kr_set_lds_limit(want) : fold_set_lds_limit(want)) != hipSuccess) {
             (void)hipGetLastError();
             want = 65536;
         }
@@ -1394,7 +1396,8 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
                                 ws + p.svdw_off, c->stream);
                 launch_dense_gemv(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, ws + p.svdw_off, u_dev, nullptr, 0,
                                   ws + p.part_off, p.nchunk, gemv_tile(c), c->stream);
-            } else {
+            } else if (!launch_cp_eval_small(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->Af, c->Af_lo, c->N, c->Np,
+                                             c->Rp, skew_of(c), u_dev, y_dev, c->stream)) {
                 launch_cp_proj1(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->N, c->Np, c->Rp, skew_of(c), u_dev,
                                 nullptr, 0, ws + p.part_off, c->stream);
                 launch_cp_scatter1(c->dtype, c->Af, c->Af_lo, c->N, c->Rp, ws + p.part_off, y_dev, nullptr, 0,

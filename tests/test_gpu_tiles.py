@@ -56,3 +56,35 @@ def test_cp_tiles(torch_gpu, dt, N, R, B):
             assert rel(u[b], r["u_hist"][0]) < TRAJ_TOL[dt]
         st.close()
         rom.close()
+
+
+@pytest.mark.parametrize("dt", ["fp64", "fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("N,R,skew", [(1, 1, False), (1, 2, True), (9, 5, False), (37, 40, True), (37, 39, False),
+                                      (64, 80, True), (64, 82, True), (40, 41, False), (130, 14, True)])
+def test_cp_small_evaluation(torch_gpu, dt, N, R, skew):
+    """One trajectory around the largest operator that is evaluated in one launch, general and
+    pair form (ranks whose padding the pair form writes itself)."""
+    torch = torch_gpu
+    print(f"[case] cp small N={N} R={R} {dt}", flush=True)
+    rng = np.random.default_rng(N * 100 + R)
+    if skew:
+        lam, Af, Bf, Cf = romsynth.skew_cp_factors(N, R // 2, seed=R, cfg=62)
+    else:
+        lam = 1.0 / np.arange(1, R + 1)
+        Af, Bf, Cf = (rng.standard_normal((N, R)) / np.sqrt(N) for _ in range(3))
+    u = romsynth.initial_u(N, [3], cfg=62)[0]
+    rom = rg.Rom(N, 1e-3, 1e-3, romsynth.stiffness_diag(N), lam=lam, Af=Af, Bf=Bf, Cf=Cf, dtype=dt)
+    ud = torch.tensor(u, device="cuda")
+    out = []
+    for form in ((-1, 0) if skew else (-1,)):
+        rg.rom_set_tile(rom.handle, 4, form)
+        yd = torch.empty_like(ud)
+        torch.cuda.synchronize()
+        rg.rom_nonlinear(rom.handle, 1, ud, yd)
+        torch.cuda.synchronize()
+        out.append(yd.cpu().numpy())
+    assert all(np.array_equal(out[0], y) for y in out)
+    ops = [lam, Af, Bf, Cf, u]
+    if dt == "bf16":
+        ops = [orc.round_bf16(a).reshape(np.shape(a)) for a in ops]
+    check_eval(dt, out[0], orc.nonlinear_cp(*ops), eval_bound_cp(dt, lam, Af, Bf, Cf, u))
