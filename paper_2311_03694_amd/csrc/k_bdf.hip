@@ -32,6 +32,16 @@ __global__ __launch_bounds__(256) void k_bdf_partials(StepArgs a, const ACC* __r
     }
 }
 
+// One trajectory: with DIAG a last block closes the previous level and advances the counter.
+template <class ACC, bool DIAG>
+__global__ __launch_bounds__(256) void k_bdf_partials1(StepArgs a, const ACC* __restrict__ part, int nchunk) {
+    if (DIAG && blockIdx.x == gridDim.x - 1) {
+        close_and_advance(a, *a.step, (int)gridDim.x - 1);
+        return;
+    }
+    bdf_partials1_body<ACC, DIAG>(a, *a.step, part, nchunk, blockIdx.x);
+}
+
 // ceil(N/4) row blocks plus a last block that closes the previous level and advances
 // the counter.
 template <bool EVEN>
@@ -68,6 +78,15 @@ __global__ void k_prep_ucv(StepArgs a, const double* __restrict__ u) {
 }
 
 template <class ACC>
+__global__ __launch_bounds__(256) void k_sum_partials1(const ACC* __restrict__ part, int nchunk, int N,
+                                                       double* __restrict__ y) {
+    __shared__ double red[4][kBdfRows];
+    const int i = blockIdx.x * kBdfRows + threadIdx.x % kWave;
+    const double s = sum_partials1(part, nchunk, N, i, red, []() {});
+    if (threadIdx.x < kWave && i < N) y[i] = s;
+}
+
+template <class ACC>
 __global__ void k_sum_partials(const ACC* __restrict__ part, int nchunk, int B, int N,
                                double* __restrict__ y, int pbstride) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y;
@@ -91,6 +110,17 @@ __global__ void k_sum_partials(const ACC* __restrict__ part, int nchunk, int B, 
 
 void launch_bdf_from_partials(const StepArgs& a, int acc_f64, const void* part, int nchunk,
                               int pb, int diag, hipStream_t s) {
+    if (a.B == 1) {
+        const dim3 g1(bdf1_blocks(a.N) + (diag ? 1 : 0));
+        if (acc_f64) {
+            if (diag) hipLaunchKernelGGL((k_bdf_partials1<double, true>), g1, dim3(256), 0, s, a, (const double*)part, nchunk);
+            else hipLaunchKernelGGL((k_bdf_partials1<double, false>), g1, dim3(256), 0, s, a, (const double*)part, nchunk);
+        } else {
+            if (diag) hipLaunchKernelGGL((k_bdf_partials1<float, true>), g1, dim3(256), 0, s, a, (const float*)part, nchunk);
+            else hipLaunchKernelGGL((k_bdf_partials1<float, false>), g1, dim3(256), 0, s, a, (const float*)part, nchunk);
+        }
+        return;
+    }
     dim3 grid((a.N + 255) / 256, a.B + (diag ? 1 : 0));
     if (acc_f64) {
         if (diag) hipLaunchKernelGGL((k_bdf_partials<double, true>), grid, dim3(256), 0, s, a, (const double*)part, nchunk, pb);
@@ -124,6 +154,12 @@ void launch_prep_ucv(const StepArgs& a, const double* u_src, hipStream_t s) {
 
 void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N,
                          double* y, hipStream_t s) {
+    if (B == 1) {
+        const dim3 g1(bdf1_blocks(N));
+        if (acc_f64) hipLaunchKernelGGL(k_sum_partials1<double>, g1, dim3(256), 0, s, (const double*)part, nchunk, N, y);
+        else hipLaunchKernelGGL(k_sum_partials1<float>, g1, dim3(256), 0, s, (const float*)part, nchunk, N, y);
+        return;
+    }
     dim3 grid((N + 255) / 256, B);
     if (acc_f64) hipLaunchKernelGGL(k_sum_partials<double>, grid, dim3(256), 0, s, (const double*)part, nchunk, B, N, y, pb);
     else hipLaunchKernelGGL(k_sum_partials<float>, grid, dim3(256), 0, s, (const float*)part, nchunk, B, N, y, pb);

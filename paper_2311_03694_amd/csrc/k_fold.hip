@@ -34,8 +34,9 @@ typedef __attribute__((address_space(3))) void* lptr_t;   // LDS pointer
 // Rows i0 .. i0 + ni - 1 of the FP64 tensor (src = C[i0][0][0], row-major) into the folded
 // storage.  Block (q-block of 32 slabs, chunk, row): both orientations of the 32 x kc patch
 // of C[i] are read along their rows, the transposed one through LDS.  *flag is raised when a
-// word of a folded tensor is not finite (the caller then stages it unfolded).
-template <int DT>
+// word of a folded tensor is not finite (the caller then stages it unfolded).  SVD: src holds
+// V[i][k][r], whose slabs are the r.
+template <int DT, bool SVD>
 __global__ __launch_bounds__(256) void k_fold_pack(const double* __restrict__ src, int i0, FoldLay l, void* dst,
                                                    unsigned short* dst_lo, int* flag) {
     typedef typename Store<DT>::T T;
@@ -45,16 +46,16 @@ __global__ __launch_bounds__(256) void k_fold_pack(const double* __restrict__ sr
     int js, len;
     fold_range(l, c, js, len);
     if (qb >= len) return;
-    const double* __restrict__ Ci = src + (size_t)blockIdx.z * l.N * l.N;
+    const double* __restrict__ Ci = src + (size_t)blockIdx.z * l.N * l.J;
     const int k0 = c * KC, N = l.N;
     auto jof = [&](int q) {
         const int j = js + q;
         return j < N ? j : j - N;
     };
-    if (l.fold) {
+    if (SVD || l.fold) {
         for (int e = threadIdx.x; e < KC * QB; e += 256) {
             const int kk = e / QB, q = e - kk * QB;
-            tr[kk][q] = (qb + q < len && k0 + kk < N) ? Ci[(size_t)(k0 + kk) * N + jof(qb + q)] : 0.0;
+            tr[kk][q] = (qb + q < len && k0 + kk < N) ? Ci[(size_t)(k0 + kk) * l.J + (SVD ? qb + q : jof(qb + q))] : 0.0;
         }
         __syncthreads();
     }
@@ -64,14 +65,16 @@ __global__ __launch_bounds__(256) void k_fold_pack(const double* __restrict__ sr
     for (int e = threadIdx.x; e < QB * (KC / VEC); e += 256) {
         const int q = e / (KC / VEC), ku = e - q * (KC / VEC);
         if (qb + q >= len || ku * VEC >= width) continue;
-        const int j = jof(qb + q);
+        const int j = SVD ? 0 : jof(qb + q);
         T hi[VEC];
         unsigned short lo[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             const int kk = ku * VEC + v, k = k0 + kk;
             double x = 0.0;
-            if (k < N) {
+            if (SVD) {
+                x = tr[kk][q];
+            } else if (k < N) {
                 const double a = Ci[(size_t)j * N + k];
                 if (!l.fold || k == j) x = a;
                 else if (j < k0 || j >= k0 + KC || k > j) x = a + tr[kk][q];
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(256) void k_fold_pack(const double* __restrict__ sr
             } else {
                 const float f = (float)x;
                 hi[v] = bf16_bits(f);
-                lo[v] = bf16_bits(f - bf16_f(hi[v]));
+                if constexpr (DT == DT_BF16X3) lo[v] = bf16_bits(f - bf16_f(hi[v]));
                 bad |= !isfinite(bf16_f(hi[v]));
             }
         }
@@ -97,11 +100,12 @@ __global__ __launch_bounds__(256) void k_fold_pack(const double* __restrict__ sr
     if (l.fold && bad) *flag = 1;
 }
 
-static int fold_kc(int dt) { return dt == DT_BF16X3 ? 64 : 32; }
+static int fold_kc(int dt) { return dt == DT_BF16 || dt == DT_BF16X3 ? 64 : 32; }
 
-FoldLay fold_layout(int dt, int N, bool fold) {
+FoldLay fold_layout(int dt, int N, int J, bool fold) {
     FoldLay l{};
     l.N = N;
+    l.J = J;
     l.kc = fold_kc(dt);
     l.nk = (N + l.kc - 1) / l.kc;
     l.fold = fold ? 1 : 0;
@@ -116,13 +120,23 @@ FoldLay fold_layout(int dt, int N, bool fold) {
 
 size_t fold_elems(const FoldLay& l) { return (size_t)((l.N + 15) / 16) * l.nk * l.lmax * l.kc * 16; }
 
-void launch_fold_pack(int dt, const double* src, int i0, int ni, const FoldLay& l, void* dst, void* dst_lo, int* flag,
-                      hipStream_t s) {
+template <int DT>
+static void fold_pack_go(bool svd, dim3 grid, hipStream_t s, const double* src, int i0, const FoldLay& l, void* dst,
+                         unsigned short* lo, int* flag) {
+    if (svd) hipLaunchKernelGGL((k_fold_pack<DT, true>), grid, dim3(256), 0, s, src, i0, l, dst, lo, flag);
+    else hipLaunchKernelGGL((k_fold_pack<DT, false>), grid, dim3(256), 0, s, src, i0, l, dst, lo, flag);
+}
+
+void launch_fold_pack(int dt, bool svd, const double* src, int i0, int ni, const FoldLay& l, void* dst, void* dst_lo,
+                      int* flag, hipStream_t s) {
     const dim3 grid((unsigned)((l.lmax + 31) / 32), (unsigned)l.nk, (unsigned)ni);
     unsigned short* lo = (unsigned short*)dst_lo;
-    if (dt == DT_F64) hipLaunchKernelGGL(k_fold_pack<DT_F64>, grid, dim3(256), 0, s, src, i0, l, dst, lo, flag);
-    else if (dt == DT_F32) hipLaunchKernelGGL(k_fold_pack<DT_F32>, grid, dim3(256), 0, s, src, i0, l, dst, lo, flag);
-    else hipLaunchKernelGGL(k_fold_pack<DT_BF16X3>, grid, dim3(256), 0, s, src, i0, l, dst, lo, flag);
+    switch (dt) {
+        case DT_F64: fold_pack_go<DT_F64>(svd, grid, s, src, i0, l, dst, lo, flag); break;
+        case DT_F32: fold_pack_go<DT_F32>(svd, grid, s, src, i0, l, dst, lo, flag); break;
+        case DT_BF16: fold_pack_go<DT_BF16>(svd, grid, s, src, i0, l, dst, lo, flag); break;
+        default: fold_pack_go<DT_BF16X3>(svd, grid, s, src, i0, l, dst, lo, flag); break;
+    }
 }
 
 // ---------------------------------------------------------------- one trajectory
@@ -136,7 +150,7 @@ __global__ __launch_bounds__(256) void k_fold_gemv(FoldJob jb) {
 // tensor streams past it with non-temporal loads (one trajectory, FP32 at N = 700: 110 us
 // against 125), a smaller one is read from it step after step (N = 400: 22 us against 25).
 static double fold_bytes(int dt, const FoldLay& l) {
-    return (double)l.N * l.nk * l.lmax * l.kc * (dt == DT_F64 ? 8 : 4);
+    return (double)l.N * l.nk * l.lmax * l.kc * (dt == DT_F64 ? 8 : dt == DT_BF16 ? 2 : 4);
 }
 static bool fold_streams(int dt, const FoldLay& l) { return fold_bytes(dt, l) > 200e6; }
 
@@ -149,12 +163,13 @@ int fold_gemv_njr(const FoldLay& l, int target) {
     return njr < 1 ? 1 : (int)njr;
 }
 
-FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, const double* u_base, const long long* stepp,
+FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, const void* wj, const double* u_base, const long long* stepp,
                       long long slot_stride, void* part, int njr) {
     FoldJob jb{};
     jb.C = C;
     jb.Clo = (const unsigned short*)Clo;
     jb.l = l;
+    jb.wj = wj;
     jb.u_base = u_base;
     jb.stepp = stepp;
     jb.slot_stride = slot_stride;
@@ -168,17 +183,20 @@ FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, 
 
 size_t fold_gemv_lds(int dt, const FoldJob& jb) { return (size_t)(jb.jc + 1) * (dt == DT_F64 ? 8 : 4); }
 
-void launch_fold_gemv(int dt, const FoldJob& jb, hipStream_t s) {
+template <int DT>
+static void fold_gemv_go(const FoldJob& jb, size_t lds, hipStream_t s) {
     const dim3 grid((unsigned)jb.nblk);
+    if (jb.stream) hipLaunchKernelGGL((k_fold_gemv<DT, true>), grid, dim3(256), lds, s, jb);
+    else hipLaunchKernelGGL((k_fold_gemv<DT, false>), grid, dim3(256), lds, s, jb);
+}
+
+void launch_fold_gemv(int dt, const FoldJob& jb, hipStream_t s) {
     const size_t lds = fold_gemv_lds(dt, jb);
-    if (jb.stream) {
-        if (dt == DT_F64) hipLaunchKernelGGL((k_fold_gemv<DT_F64, true>), grid, dim3(256), lds, s, jb);
-        else if (dt == DT_F32) hipLaunchKernelGGL((k_fold_gemv<DT_F32, true>), grid, dim3(256), lds, s, jb);
-        else hipLaunchKernelGGL((k_fold_gemv<DT_BF16X3, true>), grid, dim3(256), lds, s, jb);
-    } else {
-        if (dt == DT_F64) hipLaunchKernelGGL((k_fold_gemv<DT_F64, false>), grid, dim3(256), lds, s, jb);
-        else if (dt == DT_F32) hipLaunchKernelGGL((k_fold_gemv<DT_F32, false>), grid, dim3(256), lds, s, jb);
-        else hipLaunchKernelGGL((k_fold_gemv<DT_BF16X3, false>), grid, dim3(256), lds, s, jb);
+    switch (dt) {
+        case DT_F64: fold_gemv_go<DT_F64>(jb, lds, s); break;
+        case DT_F32: fold_gemv_go<DT_F32>(jb, lds, s); break;
+        case DT_BF16: fold_gemv_go<DT_BF16>(jb, lds, s); break;
+        default: fold_gemv_go<DT_BF16X3>(jb, lds, s); break;
     }
 }
 
@@ -317,15 +335,19 @@ __global__ __launch_bounds__(256) void k_fold_mm(FoldArgs p) {
                     }
                 }
 
-            // prefetch ring of PF slabs: no branches, loads never predicated (slabs past the
-            // end repeat the last one and meet the zero weight row), so the compiler waits
-            // for the slot it consumes only
+            // prefetch ring of PF slabs in rounds without branches whose loads are not predicated
+            // (slabs past the end repeat the last one and meet the zero weight row), so the
+            // compiler waits for the slot it consumes only.  With one column tile per block
+            // (small problems, few slabs) the last slabs are consumed without loads behind them
+            // (N = 64, B = 7: 3.4 us against 4.1); the wider tiles are bound by the matrix cores
+            // and ran slower with that second copy of the body (FP32 at N = 1000, B = 64: 642 us
+            // against 582).
             const size_t slab = (size_t)width * 16;
             const size_t base = fold_base(l, bx, c) + (size_t)lane * VEC;
             u32x4 ah[PF][NS], al[PF][NS];
-            int np = 0;
-            auto issue = [&](int d) {
-                int q = q0 + w + 4 * np;
+            const int cnt = nq > w ? (nq - w + 3) / 4 : 0;   // slabs of this wavefront
+            auto issue = [&](int d, int n) {
+                int q = q0 + w + 4 * n;
                 q = q < q1 ? q : q1 - 1;
                 const size_t o = base + (size_t)q * slab;
 #pragma unroll
@@ -333,38 +355,45 @@ __global__ __launch_bounds__(256) void k_fold_mm(FoldArgs p) {
                     ah[d][s] = ld_a<16, NT>(reinterpret_cast<const AT*>(p.C) + o + (size_t)s * 64 * VEC);
                     if constexpr (X3) al[d][s] = ld_a<16, NT>(p.Clo + o + (size_t)s * 64 * VEC);
                 }
-                ++np;
             };
 #pragma unroll
             for (int d = 0; d < PF; ++d) {
-                issue(d);
+                if (FN > 1 || d < cnt) issue(d, d);
                 __builtin_amdgcn_sched_barrier(0);       // slot order: slot 0 lands first
             }
-            // the weights are read one slab ahead
+            // the weights are read one slab ahead (row nq is zero)
             Acc svn[FN];
             lds_row<FN>(sl + (size_t)(w < nq ? w : nq) * NC + c16 * FN, svn);
-            const int cnt = (nq + 3) / 4;
-            for (int n0 = 0; n0 < cnt; n0 += PF) {
+            auto consume = [&](int d, int n) {
+                Acc sv[FN];
+#pragma unroll
+                for (int t = 0; t < FN; ++t) sv[t] = svn[t];
+                const int qn = w + 4 * (n + 1);
+                lds_row<FN>(sl + (size_t)(qn < nq ? qn : nq) * NC + c16 * FN, svn);
+                Acc4 Z[FN];
+#pragma unroll
+                for (int t = 0; t < FN; ++t) Z[t] = Acc4{0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int t = 0; t < FN; ++t) mfma_step<MKD>(Z[t], ah[d][s], al[d][s], xh[s][t], xl[s][t]);
+#pragma unroll
+                for (int t = 0; t < FN; ++t) Y[t] += sv[t] * Z[t];
+            };
+            int n0 = 0;
+            for (; FN > 1 ? n0 < (nq + 3) / 4 : n0 + PF < cnt; n0 += PF) {
 #pragma unroll
                 for (int d = 0; d < PF; ++d) {
-                    Acc sv[FN];
-#pragma unroll
-                    for (int t = 0; t < FN; ++t) sv[t] = svn[t];
-                    const int qn = w + 4 * (n0 + d + 1);
-                    lds_row<FN>(sl + (size_t)(qn < nq ? qn : nq) * NC + c16 * FN, svn);
-                    Acc4 Z[FN];
-#pragma unroll
-                    for (int t = 0; t < FN; ++t) Z[t] = Acc4{0, 0, 0, 0};
-#pragma unroll
-                    for (int s = 0; s < NS; ++s)
-#pragma unroll
-                        for (int t = 0; t < FN; ++t) mfma_step<MKD>(Z[t], ah[d][s], al[d][s], xh[s][t], xl[s][t]);
-#pragma unroll
-                    for (int t = 0; t < FN; ++t) Y[t] += sv[t] * Z[t];
-                    issue(d);
+                    consume(d, n0 + d);
+                    issue(d, n0 + PF + d);
                     // this slot's loads stay ahead of the next iterations
                     __builtin_amdgcn_sched_barrier(0x78F);
                 }
+            }
+            if constexpr (FN == 1) {
+#pragma unroll
+                for (int d = 0; d < PF; ++d)
+                    if (n0 + d < cnt) consume(d, n0 + d);
             }
         };
         if (width == l.kc) run(std::integral_constant<int, KW>{});

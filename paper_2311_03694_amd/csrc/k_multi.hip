@@ -21,13 +21,11 @@ __device__ __forceinline__ void mix_body(const MixJob& jb, int blk) {
     constexpr int V = 16 / (int)sizeof(T);
     switch (jb.kind) {
         case MIX_GEMV:
-            dense_gemv_body<DT, V, 4, 256>(jb.g, blk);
+            if constexpr (DT == DT_BF16) dense_gemv_body<4>(jb.g, blk);
             break;
         case MIX_FOLD:
-            if constexpr (DT != DT_BF16) {
-                if (jb.d.stream) fold_gemv_body<DT, kFoldU, true>(jb.d, blk);
-                else fold_gemv_body<DT, kFoldU, false>(jb.d, blk);
-            }
+            if (jb.d.stream) fold_gemv_body<DT, kFoldU, true>(jb.d, blk);
+            else fold_gemv_body<DT, kFoldU, false>(jb.d, blk);
             break;
         case MIX_PROJ:
             cp_proj_any_body<DT, V, 4>(jb.p, blk);
@@ -36,11 +34,9 @@ __device__ __forceinline__ void mix_body(const MixJob& jb, int blk) {
             const long long n = *jb.b.a.step;
             if (jb.mode == 1) {
                 if (blk == 0) close_and_advance(jb.b.a, n, jb.nblk);
-                bdf_partials_body<Acc, true>(jb.b.a, n, reinterpret_cast<const Acc*>(jb.b.part), jb.b.nchunk, jb.b.pb,
-                                             blk, 0, jb.nblk);
+                bdf_partials1_body<Acc, true>(jb.b.a, n, reinterpret_cast<const Acc*>(jb.b.part), jb.b.nchunk, blk);
             } else {
-                bdf_partials_body<Acc, false>(jb.b.a, n, reinterpret_cast<const Acc*>(jb.b.part), jb.b.nchunk, jb.b.pb,
-                                              blk, 0, jb.nblk);
+                bdf_partials1_body<Acc, false>(jb.b.a, n, reinterpret_cast<const Acc*>(jb.b.part), jb.b.nchunk, blk);
             }
             break;
         }
@@ -112,7 +108,7 @@ int mix_job_blocks(const MixJob& jb) {
 
 size_t mix_job_lds(const MixJob& jb) {
     switch (jb.kind) {
-        case MIX_GEMV: return lds_u(jb.dtype, jb.g.Np) + (jb.g.wj ? acc_size(jb.dtype) * (size_t)jb.g.J : 0);
+        case MIX_GEMV: return lds_u(jb.dtype, jb.g.Np);
         case MIX_FOLD: return fold_gemv_lds(jb.dtype, jb.d);
         case MIX_PROJ: return proj_lds_of(jb.dtype, jb.p.Np);
         case MIX_BDF: return 0;

@@ -1,5 +1,5 @@
 // kbody.h -- the per-block bodies of the one-trajectory step kernels: the dense
-// streaming contraction (and the SVD form's slab stream), the CP projections (general and
+// streaming contraction of large BF16 tensors, the CP projections (general and
 // pair form) and Hadamard-scatter, the Helmholtz apply with the next projections, the SVD
 // form's first product, the BDF update from contraction partials and the full form's
 // zeroth-mode and mass terms.  Each body runs one block's share of one state's work
@@ -15,38 +15,30 @@ namespace rom {
 
 // ============================================================== dense contraction, one trajectory
 
-template <int DT, int V, int UNR, int NT>
+template <int UNR>
 __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
-    typedef typename Store<DT>::T T;
-    typedef typename Store<DT>::Acc Acc;
-    typedef typename RawT<V * (int)sizeof(T)>::T Raw;
-    constexpr int BYTES = V * (int)sizeof(T);
-    constexpr bool X3 = (DT == DT_BF16X3);
+    constexpr int V = 8, NT = 256;                       // BF16 words per 16-byte load, threads
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ Acc red[NT / kWave];
+    __shared__ float red[NT / kWave];
     const int N = jb.N, Np = jb.Np, nchunk = jb.nchunk;
     const long long chunk_len = jb.chunk_len;
-    const T* __restrict__ C = reinterpret_cast<const T*>(jb.C);
-    LdsU<DT> L;
+    const unsigned short* __restrict__ C = reinterpret_cast<const unsigned short*>(jb.C);
+    LdsU<DT_BF16> L;
     L.bind(smem, Np);
-    // slab weights: u itself (its accumulation-format image), or jb.wj staged behind it
-    Acc* wl = reinterpret_cast<Acc*>(smem + LdsU<DT>::bytes(Np));
-    const Acc* wsrc = jb.wj ? wl : L.uw;
 
     const int i = blk / nchunk;
     const int c = blk - i * nchunk;
-    const long long NN = (long long)jb.J * Np;
+    const long long NN = (long long)N * Np;
     const long long m0 = (long long)c * chunk_len;
     const long long m1 = (m0 + chunk_len < NN) ? m0 + chunk_len : NN;
-    const T* row = C + (size_t)i * NN;
-    const unsigned short* rowlo = X3 ? jb.Clo + (size_t)i * NN : nullptr;
+    const unsigned short* row = C + (size_t)i * NN;
 
     constexpr int STEP = NT * V;
     const int dj = STEP / Np, dk = STEP - (STEP / Np) * Np;
     long long m = m0 + (long long)threadIdx.x * V;
     int j = (int)(m / Np), k = (int)(m - (long long)j * Np);
 
-    Raw r[UNR], rl[UNR];
+    u32x4 r[UNR];
     int jj[UNR], kk[UNR];
     auto issue = [&](long long mb) {
 #pragma unroll
@@ -54,10 +46,7 @@ __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
             const long long mq = mb + (long long)q * STEP;
             jj[q] = j;
             kk[q] = k;
-            if (mq < m1) {
-                r[q] = ld_stream<BYTES>(row + mq);
-                if constexpr (X3) rl[q] = ld_stream<BYTES>(rowlo + mq);
-            }
+            if (mq < m1) r[q] = ld_stream<16>(row + mq);
             k += dk;
             j += dj;
             if (k >= Np) { k -= Np; ++j; }
@@ -66,23 +55,19 @@ __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
 
     if (m < m1) issue(m);
     L.fill(jb.u_base + (jb.stepp ? (size_t)slot_of(*jb.stepp) * jb.slot_stride : 0), N, Np);
-    if (jb.wj) {
-        const Acc* wg = reinterpret_cast<const Acc*>(jb.wj);
-        for (int q = threadIdx.x; q < jb.J; q += NT) wl[q] = wg[q];
-    }
     __syncthreads();
 
-    Acc acc = 0;
+    float acc = 0;
     while (m < m1) {
 #pragma unroll
         for (int q = 0; q < UNR; ++q) {
-            if (m + (long long)q * STEP < m1) acc += wsrc[jj[q]] * dot_vec<DT, V>(r[q], rl[q], L, kk[q]);
+            if (m + (long long)q * STEP < m1) acc += L.uw[jj[q]] * dot_vec<DT_BF16, V>(r[q], r[q], L, kk[q]);
         }
         m += (long long)STEP * UNR;
         if (m < m1) issue(m);
     }
-    const Acc s = block_sum(acc, red);
-    if (threadIdx.x == 0) reinterpret_cast<Acc*>(jb.part)[(size_t)c * N + i] = s;
+    const float s = block_sum(acc, red);
+    if (threadIdx.x == 0) reinterpret_cast<float*>(jb.part)[(size_t)c * N + i] = s;
 }
 
 
@@ -542,7 +527,7 @@ __device__ __forceinline__ void helm_proj_body(const HelmJob& jb, long long n, i
 
 // First product of the SVD-ROM (Sec. 4.4): w_r = sigma_r sum_j U[j][r] u_j over the rows
 // of Ut [Rsp][Np] (rows past the rank are zero, so w is zero there).  One wavefront per
-// row, four per block; the second product is the streaming kernel with R weighted slabs.
+// row, four per block; the second product is the stream of R weighted slabs (kfold.h).
 
 template <int DT, int V, int U>
 __device__ __forceinline__ void svd_proj_body(const SvdProj& a, int blk) {
@@ -593,7 +578,79 @@ __device__ __forceinline__ void svd_proj_body(const SvdProj& a, int blk) {
 
 // ============================================================== BDF update from partials
 
-// y^n from contraction partials part[c][b][i] (summed over c in order), then either
+// One trajectory: the sum over the nchunk partials part[c][i] of row i = 64 bx + lane.
+// Wavefront g of the block's four adds the g-th quarter of them in order, and wavefront 0 the
+// four sums in order (valid there): an eighth of the loads in one chain that one thread per row
+// had, which keeps the update at 4.8 us with the 30 to 50 partials of the tiled streams.
+// `between` runs once the first loads are on their way.
+template <class ACC, class Between>
+__device__ __forceinline__ double sum_partials1(const ACC* __restrict__ part, int nchunk, int N, int i,
+                                                double (&red)[4][kBdfRows], Between between) {
+    constexpr int U = 12;                                // loads in flight
+    const int g = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int per = (nchunk + 3) / 4, c1 = per * (g + 1) < nchunk ? per * (g + 1) : nchunk;
+    const bool live = i < N;
+    double y = 0.0;
+    int q = per * g;
+    ACC v[U];
+    auto load = [&]() {
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+            if (live && q + e < c1) v[e] = part[(size_t)(q + e) * N + i];
+    };
+    load();
+    between();
+    while (q < c1) {
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+            if (live && q + e < c1) y += (double)v[e];
+        q += U;
+        if (q < c1) load();
+    }
+    red[g][lane] = y;
+    __syncthreads();
+    return ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+}
+
+// y^n from the contraction partials of one trajectory, then either the diagonal-stiffness
+// update u^{n+1} = rhs / H_ii with its energy partials, or the right-hand side for the dense
+// solve.  Block bx covers rows 64 bx .. 64 bx + 63; its first wavefront loads their history
+// behind the partials and finishes them.
+template <class ACC, bool DIAG>
+__device__ __forceinline__ void bdf_partials1_body(const StepArgs& a, long long n, const ACC* __restrict__ part, int nchunk,
+                                                   int bx) {
+    __shared__ double red[4][kBdfRows];
+    const int k = bdf_order(n);
+    const BdfCoef c = bdf_coef(k);
+    const int lane = threadIdx.x % kWave, i = bx * kBdfRows + lane;
+    const bool first = threadIdx.x < kWave, live = i < a.N;
+    BdfHist hist{};
+    double hd = 0.0;
+    const double y = sum_partials1(part, nchunk, a.N, i, red, [&]() {
+        if (first && live) {
+            hist = bdf_hist_point(a, n, k, 0, i);
+            if constexpr (DIAG) hd = a.hdiag[(size_t)(k - 1) * a.N + i];
+        }
+    });
+    if (!first) return;
+    double e = 0.0;
+    if (live) {
+        const double rhs = bdf_rhs_hist(a, n, c, k, 0, i, y, hist);
+        if constexpr (DIAG) {
+            const double un = rhs * hd;
+            write_level(a, n + 1, 0, i, un);
+            e = un * un;
+        } else {
+            a.rhs[i] = rhs;
+        }
+    }
+    if constexpr (DIAG) {
+        e = wave_sum(e);
+        if (lane == 0) epart_of(a, n + 1)[bx] = e;
+    }
+}
+
+// Batches: y^n from contraction partials part[c][b][i] (summed over c in order), then either
 // the diagonal-stiffness update u^{n+1} = rhs / H_ii with its energy partials, or the
 // right-hand side for the dense solve.  Block (bx, b) covers rows 256 bx .. 256 bx + 255
 // of trajectory b (nbx blocks per trajectory).
@@ -625,7 +682,7 @@ __device__ __forceinline__ void bdf_partials_body(const StepArgs& a, long long n
             write_level(a, n + 1, b, i, un);
             e = un * un;
         } else {
-            a.rhs[a.batched ? tile_off<8, 2>(a.Np, b, i) : (size_t)i] = rhs;
+            a.rhs[tile_off<8, 2>(a.Np, b, i)] = rhs;
         }
     }
     if (DIAG) {

@@ -1,18 +1,19 @@
-// kfold.h -- the folded dense tensor and its one-trajectory contraction.
+// kfold.h -- the folded dense tensor and the one-trajectory contraction of tensor slabs.
 //
 // C(u)u (Sec. 2.2, eq. Cu) contracts C[i][j][k] with the symmetric u_j u_k, so
 //     y_i = sum_{ {j,k} } (C[i][j][k] + C[i][k][j]) u_j u_k,
 // one sum of two entries per unordered pair (the entry itself for j = k): half the words
 // and half the products of the unfolded form.  The sums are formed from the FP64 entries
 // at staging and rounded once, so a pair carries one rounding instead of two.  (The BF16
-// format rounds every entry for itself and stays unfolded, k_dense1.hip and k_kr.hip.)
+// format rounds every entry for itself and stays unfolded.)
 //
 // Which of j, k is the weight and which the contracted index is free per pair.  k is cut
 // into chunks of kc; chunk c contracts the j of a cyclic run of chunks ending at c itself
 // (about half of them), so every chunk has the same amount of work and its j are one
 // consecutive (wrapping) range.  Inside the diagonal chunk the pairs sit at k >= j, zeros
-// below.  An unfolded tensor (one whose sums would overflow the format) uses the same
-// storage with every chunk contracting all j.
+// below.  Unfolded tensors (BF16, and those whose sums would overflow the format) use the
+// same storage with every chunk contracting all j, and so do the slabs of the SVD form (Sec.
+// 4.4; y_i = sum_r w_r sum_k V[i][k][r] u_k), whose j is the SVD index with weights of its own.
 //
 // Storage: [row tile of 16][chunk][q = index in the chunk's j range][k / VEC][16 rows][VEC]
 // (VEC = elements per 16 bytes): one lane vector of a wavefront (16 rows x 4 k-groups x 16
@@ -28,6 +29,7 @@ namespace rom {
 template <int DT> struct FoldT;
 template <> struct FoldT<DT_F64> { static constexpr int KS = 8, VEC = 2, KW = 4; };
 template <> struct FoldT<DT_F32> { static constexpr int KS = 16, VEC = 4, KW = 2; };
+template <> struct FoldT<DT_BF16> { static constexpr int KS = 32, VEC = 8, KW = 2; };
 template <> struct FoldT<DT_BF16X3> { static constexpr int KS = 32, VEC = 8, KW = 2; };
 
 // Elements of chunk c's slabs along k: kc, or for the last chunk the 1/2 or all of it that
@@ -40,7 +42,7 @@ __host__ __device__ inline int fold_width(const FoldLay& l, int c) {
 __host__ __device__ inline void fold_range(const FoldLay& l, int c, int& js, int& len) {
     if (!l.fold) {
         js = 0;
-        len = l.N;
+        len = l.J;
         return;
     }
     const int back = (l.nk - 1) / 2 + (l.nk % 2 == 0 && c >= l.nk / 2 ? 1 : 0);
@@ -58,16 +60,18 @@ __host__ __device__ inline size_t fold_base(const FoldLay& l, int it, int c) {
 // One trajectory: partial sums part[c * njr + jr][i] of the 16 rows of a tile over piece jr
 // of chunk c's j range.  A stream over HBM: the lane keeps the u_k of its k-group in
 // registers for the whole piece, so a slab costs its loads, one FMA per element and one
-// weight u_j (LDS, the same for the whole wavefront).  The 4 wavefronts take every fourth
-// slab; U slabs are in flight per wavefront, the loads never predicated (slabs past the end
-// repeat the last one with weight zero), so the wait is for the slot consumed only.
+// weight u_j or w_j (LDS, the same for the whole wavefront).  The 4 wavefronts take every fourth
+// slab (a chunk each, where all chunks run over the same j, was no faster); U slabs are in flight per wavefront, in whole rounds whose loads are not predicated
+// (slabs past the end repeat the last one), so the wait is for the slot consumed only; the
+// slabs left in the ring are consumed without loads behind them (a ring refilled to its end
+// cost the 25 slabs of a wavefront 4 more: N = 1000, 100 SVD slabs BF16X3 66.4 -> 63.9 us).
 // NT: non-temporal loads, for a tensor larger than the last-level cache.
 template <int DT, int U, bool NT>
 __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {
     typedef typename Store<DT>::T T;
     typedef typename Store<DT>::Acc Acc;
     constexpr int KS = FoldT<DT>::KS, VEC = FoldT<DT>::VEC, KW = FoldT<DT>::KW;
-    constexpr bool X3 = (DT == DT_BF16X3);
+    constexpr bool X3 = (DT == DT_BF16X3), BF = (DT == DT_BF16 || X3);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ Acc red[4 * 16];
     const FoldLay& l = jb.l;
@@ -81,7 +85,7 @@ __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int width = fold_width(l, c);
     const double* __restrict__ u = jb.u_base + (jb.stepp ? (size_t)slot_of(*jb.stepp) * jb.slot_stride : 0);
-    Acc* wl = reinterpret_cast<Acc*>(smem);              // [nq + 1] weights u_j, the last zero
+    Acc* wl = reinterpret_cast<Acc*>(smem);              // [nq] weights
     Acc acc = 0;
 
     auto run = [&](auto nsc) {
@@ -91,20 +95,18 @@ __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {
         const T* __restrict__ C = reinterpret_cast<const T*>(jb.C) + base;
         const unsigned short* __restrict__ Cl = X3 ? jb.Clo + base : nullptr;
         u32x4 r[U][NS], rl[U][NS];
+        const int cnt = nq > w ? (nq - w + 3) / 4 : 0;   // slabs of this wavefront
         auto issue = [&](int d, int n) {
-            int q = q0 + w + 4 * n;
-            q = q < q1 ? q : q1 - 1;
-            const size_t o = (size_t)q * slab;
+            const size_t o = (size_t)(q0 + w + 4 * (n < cnt ? n : cnt - 1)) * slab;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 r[d][s] = ld_a<16, NT>(C + o + (size_t)s * 64 * VEC);
                 if constexpr (X3) rl[d][s] = ld_a<16, NT>(Cl + o + (size_t)s * 64 * VEC);
             }
         };
-        if (nq > 0) {
 #pragma unroll
-            for (int d = 0; d < U; ++d) issue(d, d);
-        }
+        for (int d = 0; d < U; ++d)
+            if (d < cnt) issue(d, d);
         // the lane's u_k (fixed over the piece) and the piece's weights u_j
         Acc uf[NS][VEC];
         u32x4 uh[NS], ul[NS];
@@ -115,7 +117,7 @@ __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {
                 const int k = c * l.kc + s * KS + g * VEC + v;
                 uf[s][v] = (Acc)(k < l.N ? u[k] : 0.0);
             }
-        if constexpr (X3) {
+        if constexpr (BF) {
 #pragma unroll
             for (int s = 0; s < NS; ++s)
 #pragma unroll
@@ -127,40 +129,53 @@ __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {
                     ul[s][p] = (unsigned)l0 | ((unsigned)l1 << 16);
                 }
         }
-        for (int q = threadIdx.x; q <= nq; q += 256) {
+        for (int q = threadIdx.x; q < nq; q += 256) {
             int j = js + q0 + q;
-            j = j < l.N ? j : j - l.N;
-            wl[q] = q < nq ? (Acc)u[j] : (Acc)0;
+            Acc wj;
+            if (jb.wj) {
+                wj = reinterpret_cast<const Acc*>(jb.wj)[j];
+            } else {
+                j = j < l.N ? j : j - l.N;
+                wj = (Acc)u[j];
+                if constexpr (DT == DT_BF16) wj = bf16_f(bf16_bits(wj));
+            }
+            wl[q] = wj;
         }
         __syncthreads();
-        if (nq <= 0) return;
-        const int cnt = (nq + 3) / 4;                    // slabs per wavefront (the last ones may be padding)
-        for (int n0 = 0; n0 < cnt; n0 += U) {
+        auto consume = [&](int d, int n) {
+            const Acc wj = wl[w + 4 * n];
+            Acc z = 0;
 #pragma unroll
-            for (int d = 0; d < U; ++d) {
-                const int qr = w + 4 * (n0 + d);
-                const Acc wj = wl[qr < nq ? qr : nq];
-                Acc z = 0;
+            for (int s = 0; s < NS; ++s) {
+                if constexpr (BF) {
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    if constexpr (X3) {
-#pragma unroll
-                        for (int p = 0; p < 4; ++p) {
-                            z = dot2_bf16(r[d][s][p], uh[s][p], z);
+                    for (int p = 0; p < 4; ++p) {
+                        z = dot2_bf16(r[d][s][p], uh[s][p], z);
+                        if constexpr (X3) {
                             z = dot2_bf16(r[d][s][p], ul[s][p], z);
                             z = dot2_bf16(rl[d][s][p], uh[s][p], z);
                         }
-                    } else {
-                        Acc cv[VEC];
-                        Decode<DT, VEC>::run(r[d][s], cv);
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) z += cv[v] * uf[s][v];
                     }
+                } else {
+                    Acc cv[VEC];
+                    Decode<DT, VEC>::run(r[d][s], cv);
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) z += cv[v] * uf[s][v];
                 }
-                acc += wj * z;
-                issue(d, n0 + d + U);
+            }
+            acc += wj * z;
+        };
+        int n0 = 0;
+        for (; n0 + U < cnt; n0 += U) {
+#pragma unroll
+            for (int d = 0; d < U; ++d) {
+                consume(d, n0 + d);
+                issue(d, n0 + U + d);
             }
         }
+#pragma unroll
+        for (int d = 0; d < U; ++d)
+            if (n0 + d < cnt) consume(d, n0 + d);
     };
     if (width == l.kc) run(std::integral_constant<int, KW>{});
     else run(std::integral_constant<int, KW / 2>{});

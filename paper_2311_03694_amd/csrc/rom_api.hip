@@ -79,7 +79,8 @@ struct rom_ctx_s {
     // (contracted indices padded with zeros: Np, Rp = N, R rounded up to multiples of 8)
     void* C = nullptr;                         // dense BF16 [N][N][Np]
     void* Ct = nullptr;                        // dense BF16, max_batch > 1: tiled copy for k_kr
-    // dense FP64, FP32, BF16X3: the folded tensor (kfold.h), for one trajectory and batches
+    // dense FP64, FP32, BF16X3: the folded tensor (kfold.h), for one trajectory and batches;
+    // small dense BF16: the unfolded one, for one trajectory; SVD form: the slabs of V
     FoldLay fl{};
     FoldPlan fplan{};                          // the latest unbounded batch plan, of fplan_B columns and
     int fplan_B = 0, fplan_v = 0;              // variant fplan_v (planning is a search of some 100 splits)
@@ -99,11 +100,10 @@ struct rom_ctx_s {
     double* hinvg = nullptr;
     void *SK = nullptr, *SK_lo = nullptr;
     void *Msk = nullptr, *Msk_lo = nullptr;
-    // SVD form (svd): Ut [Rsp][Np] (columns of U as rows), sigma [Rsp] (accumulation
-    // type), Vt [N][Rs][Np] (V[i][k][r] as slab r of row i)
+    // SVD form (svd): Ut [Rsp][Np] (columns of U as rows), sigma [Rsp] (accumulation type)
     bool svd = false;
     int Rs = 0, Rsp = 0;
-    void *Ut = nullptr, *Ut_lo = nullptr, *sig = nullptr, *Vt = nullptr, *Vt_lo = nullptr;
+    void *Ut = nullptr, *Ut_lo = nullptr, *sig = nullptr;
     double* hdiag = nullptr;                    // [3][N]
     double* hinv = nullptr;                     // [3][N][N]
     // full form of eq. nse_d1 (mass matrix, zeroth-mode terms): G = [L | M - I]
@@ -186,10 +186,13 @@ namespace {
 
 GemvTile gemv_tile(rom_ctx c) { return dense_gemv_variant(c->tile[0] < 0 ? 0 : c->tile[0]); }
 // The folded stream's pieces per chunk: its blocks (16 rows each) are an eighth of the
-// unfolded kernel's target, 1024 by default (FP32 at N = 300: 11.7 us, with 2048 blocks 15.5).
-int fold_njr(rom_ctx c) { return fold_gemv_njr(c->fl, gemv_tile(c).chunk_target / 8); }
-FoldJob fold_job(rom_ctx c, const double* u_base, const long long* stepp, long long slot_stride, void* part) {
-    return make_fold_job(c->dtype, c->F, c->F_lo, c->fl, u_base, stepp, slot_stride, part, fold_njr(c));
+// unfolded kernel's target, 1024 by default (FP32 at N = 300: 11.7 us, with 2048 blocks 15.5);
+// in FP64 half of it (100 SVD slabs at N = 1000: 118 us against 122, dense N = 400 42 against
+// 44).
+int fold_njr(rom_ctx c) { return fold_gemv_njr(c->fl, gemv_tile(c).chunk_target / (c->dtype == DT_F64 ? 2 : 8)); }
+FoldJob fold_job(rom_ctx c, const void* wj, const double* u_base, const long long* stepp, long long slot_stride,
+                 void* part) {
+    return make_fold_job(c->dtype, c->F, c->F_lo, c->fl, wj, u_base, stepp, slot_stride, part, fold_njr(c));
 }
 // kinds 2 (CP projections) and 3 (CP scatter): k_gemm variants first, then the LDS-tile
 // kernel's
@@ -304,7 +307,7 @@ WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
         const size_t eb = elem_bytes(c->dtype);
         size_t part_end = 0;
         if (c->dense) {
-            if (c->F) {
+            if (c->dtype != DT_BF16) {
                 if (splits > 0) {
                     p.pf = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, splits);
                 } else {
@@ -373,7 +376,7 @@ size_t noalloc_bytes(rom_ctx c, int B) {
 // The batched dense contraction of plan p: partial tiles in `part`.
 void launch_dense_term(rom_ctx c, const WsPlan& p, const void* X, const void* Xlo, const void* S, void* part,
                        hipStream_t s) {
-    if (c->F) launch_fold_batched(c->dtype, p.pf, c->F, c->F_lo, c->fl, c->Np, p.Bpad, X, Xlo, S, part, s);
+    if (c->dtype != DT_BF16) launch_fold_batched(c->dtype, p.pf, c->F, c->F_lo, c->fl, c->Np, p.Bpad, X, Xlo, S, part, s);
     else launch_dense_batched(p.pd, c->C, c->Ct, c->N, c->Np, p.Bpad, X, S, part, s);
 }
 
@@ -426,12 +429,14 @@ static rom_status upload_convert(rom_ctx c, const double* host, size_t rows, int
 // may run up to one k-step past the last row (they meet zero weights).
 static constexpr size_t kSlack = 256;
 
-// The dense tensor in the folded storage (kfold.h): uploaded whole rows i at a time (the
-// stage holds at least one) and folded on the device.  A tensor whose folded words are not
-// all finite (an entry that is not, or a sum of two that overflows the format) is staged
-// unfolded instead, so its evaluations meet the entries themselves.
-static rom_status stage_folded(rom_ctx c, const double* host, double* stage, size_t stage_elems) {
-    const size_t nn = (size_t)c->N * c->N, eb = elem_bytes(c->dtype);
+// The dense tensor (J = N) in the folded storage (kfold.h), or the slabs V[i][k][r] of the
+// SVD form (svd, J = R): uploaded whole rows i at a time (the stage holds at least one) and
+// arranged on the device.  A tensor whose folded words are not all finite (an entry that is
+// not, or a sum of two that overflows the format) is staged unfolded instead, so its
+// evaluations meet the entries themselves; BF16 tensors and SVD slabs are never folded.  With
+// c->C allocated (BF16 batches) the same upload also fills the row-major copy.
+static rom_status stage_folded(rom_ctx c, const double* host, int J, bool svd, double* stage, size_t stage_elems) {
+    const size_t nn = (size_t)c->N * J, eb = elem_bytes(c->dtype);
     const int per = (int)std::max<size_t>(1, stage_elems / nn);
     int* flag = nullptr;
     HIPCHK(hipMalloc((void**)&flag, sizeof(int)));
@@ -439,8 +444,8 @@ static rom_status stage_folded(rom_ctx c, const double* host, double* stage, siz
         int* p;
         ~Guard() { hipFree(p); }
     } guard{flag};
-    for (int fold = 1; fold >= 0; --fold) {
-        c->fl = fold_layout(c->dtype, c->N, fold != 0);
+    for (int fold = svd || c->dtype == DT_BF16 ? 0 : 1; fold >= 0; --fold) {
+        c->fl = fold_layout(c->dtype, c->N, J, fold != 0);
         const size_t n = fold_elems(c->fl);
         const size_t bytes0 = c->bytes, list0 = c->allocs.size();
         TRYS(dmalloc(&c->F, n * eb + kSlack, &c->bytes, &c->allocs));
@@ -454,7 +459,10 @@ static rom_status stage_folded(rom_ctx c, const double* host, double* stage, siz
             const int ni = std::min(per, c->N - i0);
             HIPCHK(hipMemcpyAsync(stage, host + (size_t)i0 * nn, (size_t)ni * nn * sizeof(double), hipMemcpyHostToDevice,
                                   c->stream));
-            launch_fold_pack(c->dtype, stage, i0, ni, c->fl, c->F, c->F_lo, flag, c->stream);
+            launch_fold_pack(c->dtype, svd, stage, i0, ni, c->fl, c->F, c->F_lo, flag, c->stream);
+            if (c->C)
+                launch_cvt_f64_to(c->dtype, stage, (char*)c->C + (size_t)i0 * J * c->Np * eb, nullptr, (long long)ni * J, c->N,
+                                  c->Np, c->stream);
             HIPCHK(hipGetLastError());
             HIPCHK(hipStreamSynchronize(c->stream));
         }
@@ -470,6 +478,12 @@ static rom_status stage_folded(rom_ctx c, const double* host, double* stage, siz
     }
     return ROM_OK;
 }
+
+// BF16 tensors up to this size also take the tiled storage (one trajectory: instead of the
+// row-major one): fewer, longer blocks (N = 100: 4.9 us against 12.2, N = 300: 13.0 against
+// 18.5).  Larger ones stream at the memory's rate either way, and their rows are padded less
+// (to 8 elements instead of 32: N = 450 29.2 us against 34.3).
+constexpr double kBf16TileBytes = 100e6;
 
 // Column pairs of CP factors that keep the partial skew-symmetry (Sec. 3.3, eq.
 // skew_abc_struct): pair p = (c0, c1) with lam[c0] == lam[c1], Bf[:,c0] == Bf[:,c1],
@@ -731,7 +745,8 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
     const size_t stage_elems = (size_t)1 << 25;   // 256 MB of FP64 per upload chunk
     double* stage = nullptr;
     const size_t nn = (size_t)N * N;
-    HTRY(hipMalloc((void**)&stage, sizeof(double) * (nn > stage_elems ? nn : stage_elems)));
+    const size_t row_elems = sv ? std::max((size_t)N * sv->R, nn) : nn;   // the largest whole row i, or A
+    HTRY(hipMalloc((void**)&stage, sizeof(double) * std::max(row_elems, stage_elems)));
     struct StageGuard {
         double* p;
         ~StageGuard() { if (p) hipFree(p); }
@@ -812,19 +827,15 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
     const bool lo = dt == DT_BF16X3;
     const size_t Np = c->Np;
     if (sv) {
-        // SVD form (Sec. 4.4): Ut rows are the columns of U, Vt[i][r][k] = V[i][k][r]
+        // SVD form (Sec. 4.4): Ut rows are the columns of U, V's slabs r in the tiled storage
         const size_t Rs = (size_t)sv->R, Rsp = (Rs + 7) / 8 * 8;
         c->Rs = (int)Rs;
         c->Rsp = (int)Rsp;
         TRY(dmalloc(&c->Ut, Rsp * Np * eb + kSlack, &c->bytes, &c->allocs));
         HTRY(hipMemsetAsync(c->Ut, 0, Rsp * Np * eb + kSlack, c->stream));
-        TRY(dmalloc(&c->Vt, (size_t)N * Rs * Np * eb + kSlack, &c->bytes, &c->allocs));
-        HTRY(hipMemsetAsync(c->Vt, 0, (size_t)N * Rs * Np * eb + kSlack, c->stream));
         if (lo) {
             TRY(dmalloc(&c->Ut_lo, Rsp * Np * 2 + kSlack, &c->bytes, &c->allocs));
             HTRY(hipMemsetAsync(c->Ut_lo, 0, Rsp * Np * 2 + kSlack, c->stream));
-            TRY(dmalloc(&c->Vt_lo, (size_t)N * Rs * Np * 2 + kSlack, &c->bytes, &c->allocs));
-            HTRY(hipMemsetAsync(c->Vt_lo, 0, (size_t)N * Rs * Np * 2 + kSlack, c->stream));
         }
         TRY(dmalloc(&c->sig, Rsp * acc_bytes(dt), &c->bytes, &c->allocs));
         HTRY(hipMemsetAsync(c->sig, 0, Rsp * acc_bytes(dt), c->stream));
@@ -832,28 +843,21 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
         for (size_t n = 0; n < (size_t)N; ++n)
             for (size_t r = 0; r < Rs; ++r) t[r * N + n] = sv->U[n * Rs + r];
         TRY(upload_convert(c, t.data(), Rs, (int)N, (int)Np, c->Ut, c->Ut_lo, stage, stage_elems));
-        for (size_t i = 0; i < (size_t)N; ++i) {
-            const double* Vi = sv->V + i * (size_t)N * Rs;           // [k][r] of row i
-            for (size_t k = 0; k < (size_t)N; ++k)
-                for (size_t r = 0; r < Rs; ++r) t[r * N + k] = Vi[k * Rs + r];
-            TRY(upload_convert(c, t.data(), Rs, (int)N, (int)Np, (char*)c->Vt + i * Rs * Np * eb,
-                               lo ? (char*)c->Vt_lo + i * Rs * Np * 2 : nullptr, stage, stage_elems));
-        }
+        TRY(stage_folded(c, sv->V, (int)Rs, true, stage, stage_elems));
         HTRY(hipMemcpyAsync(stage, sv->sigma, sizeof(double) * Rs, hipMemcpyHostToDevice, c->stream));
         launch_cvt_lambda(dt, stage, c->sig, (long long)Rs, c->stream);
         HTRY(hipGetLastError());
     } else
     if (c->dense) {
-        if (dt != DT_BF16) {
-            st = stage_folded(c, d->C, stage, stage_elems);
-            if (st != ROM_OK) {
-                rom_destroy(c);
-                return st;
-            }
-        } else {
+        const bool tiles = dt != DT_BF16 || 2.0 * nn * N <= kBf16TileBytes;
+        if (dt == DT_BF16 && (!tiles || c->max_batch > 1)) {
             const size_t n3 = nn * Np;
             TRY(dmalloc(&c->C, n3 * eb + kSlack, &c->bytes, &c->allocs));
             HTRY(hipMemsetAsync(c->C, 0, n3 * eb + kSlack, c->stream));
+        }
+        if (tiles) {
+            TRY(stage_folded(c, d->C, (int)N, false, stage, stage_elems));
+        } else {
             TRY(upload_convert(c, d->C, nn, (int)N, (int)Np, c->C, nullptr, stage, stage_elems));
         }
         if (dt == DT_BF16 && c->max_batch > 1) {
@@ -1295,16 +1299,16 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
         char* ws = (char*)s->scratch;
         if (c->dense) {
             if (c->F)
-                launch_fold_gemv(c->dtype, fold_job(c, a.uring, a.step, (long long)c->N, ws + p.part_off), stream);
+                launch_fold_gemv(c->dtype, fold_job(c, nullptr, a.uring, a.step, (long long)c->N, ws + p.part_off), stream);
             else
-                launch_dense_gemv(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, a.uring, a.step, (long long)c->N,
-                                  ws + p.part_off, p.nchunk, gemv_tile(c), stream);
+                launch_dense_gemv(c->C, c->N, c->Np, a.uring, a.step, (long long)c->N, ws + p.part_off, p.nchunk,
+                                  gemv_tile(c), stream);
             launch_bdf_from_partials(a, accf, ws + p.part_off, p.nchunk, 1, diag, stream);
         } else if (c->svd) {
             launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, a.uring, a.step, (long long)c->N,
                             ws + p.svdw_off, stream);
-            launch_dense_gemv(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, ws + p.svdw_off, a.uring, a.step,
-                              (long long)c->N, ws + p.part_off, p.nchunk, gemv_tile(c), stream);
+            launch_fold_gemv(c->dtype, fold_job(c, ws + p.svdw_off, a.uring, a.step, (long long)c->N, ws + p.part_off),
+                             stream);
             launch_bdf_from_partials(a, accf, ws + p.part_off, p.nchunk, 1, diag, stream);
         } else {
             // a.st holds w = lam .* s .* t of level n: computed here with a diagonal
@@ -1387,15 +1391,14 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
         if (batch == 1) {
             if (c->dense) {
                 if (c->F)
-                    launch_fold_gemv(c->dtype, fold_job(c, u_dev, nullptr, 0, ws + p.part_off), c->stream);
+                    launch_fold_gemv(c->dtype, fold_job(c, nullptr, u_dev, nullptr, 0, ws + p.part_off), c->stream);
                 else
-                    launch_dense_gemv(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, u_dev, nullptr, 0,
-                                      ws + p.part_off, p.nchunk, gemv_tile(c), c->stream);
+                    launch_dense_gemv(c->C, c->N, c->Np, u_dev, nullptr, 0, ws + p.part_off, p.nchunk, gemv_tile(c),
+                                      c->stream);
             } else if (c->svd) {
                 launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, u_dev, nullptr, 0,
                                 ws + p.svdw_off, c->stream);
-                launch_dense_gemv(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, ws + p.svdw_off, u_dev, nullptr, 0,
-                                  ws + p.part_off, p.nchunk, gemv_tile(c), c->stream);
+                launch_fold_gemv(c->dtype, fold_job(c, ws + p.svdw_off, u_dev, nullptr, 0, ws + p.part_off), c->stream);
             } else if (!launch_cp_eval_small(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->Af, c->Af_lo, c->N, c->Np,
                                              c->Rp, skew_of(c), u_dev, y_dev, c->stream)) {
                 launch_cp_proj1(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->N, c->Np, c->Rp, skew_of(c), u_dev,
@@ -2294,13 +2297,10 @@ void pair_jobs(rom_ctx c, rom_state st, long long lev, std::vector<MixJob> (&ph)
         MixJob jg{};
         if (c->F) {
             jg.kind = MIX_FOLD;
-            jg.d = fold_job(c, sa.uring, sa.step, c->N, scr + p.part_off);
+            jg.d = fold_job(c, wj, sa.uring, sa.step, c->N, scr + p.part_off);
         } else {
             jg.kind = MIX_GEMV;
-            jg.g = c->svd ? make_gemv_job(c->dtype, c->Vt, c->Vt_lo, c->N, c->Np, c->Rs, wj, sa.uring, sa.step, c->N,
-                                          scr + p.part_off, p.nchunk, gemv_tile(c))
-                          : make_gemv_job(c->dtype, c->C, nullptr, c->N, c->Np, c->N, nullptr, sa.uring, sa.step, c->N,
-                                          scr + p.part_off, p.nchunk, gemv_tile(c));
+            jg.g = make_gemv_job(c->C, c->N, c->Np, sa.uring, sa.step, c->N, scr + p.part_off, p.nchunk, gemv_tile(c));
         }
         add(1, jg);
         MixJob jb{};
@@ -2310,7 +2310,7 @@ void pair_jobs(rom_ctx c, rom_state st, long long lev, std::vector<MixJob> (&ph)
         jb.b.part = scr + p.part_off;
         jb.b.nchunk = p.nchunk;
         jb.b.pb = 1;
-        jb.b.nblk = (c->N + 255) / 256;
+        jb.b.nblk = bdf1_blocks(c->N);
         add(2, jb);
     } else {
         // with a dense stiffness the projections come from the previous step's Helmholtz

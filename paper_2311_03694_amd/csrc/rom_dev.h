@@ -69,12 +69,9 @@ struct StepArgs {
 
 // A job is one kernel's work for one (context, state) pair; grouped launches run the
 // jobs of many pairs (uneven N, R) in one grid, job p owning blocks [blk0, blk0+nblk).
-struct GemvJob {           // dense contraction, one trajectory
-    const void* C;                 // [N][J][Np]
-    const unsigned short* Clo;
+struct GemvJob {           // dense contraction of a large BF16 tensor, one trajectory
+    const void* C;                 // [N][N][Np]
     int N, Np;
-    int J;                         // slabs per row: N (dense tensor), or the SVD rank
-    const void* wj;                // slab weights [J] (accumulation type); null: u itself
     const double* u_base;
     const long long* stepp;
     long long slot_stride;
@@ -84,13 +81,14 @@ struct GemvJob {           // dense contraction, one trajectory
     int blk0, nblk;
 };
 // Layout of the folded dense tensor (kfold.h): nk chunks of kc contracted indices, at most
-// lmax j per chunk; fold 0: every chunk contracts all N j.
-struct FoldLay { int N, kc, nk, lmax, fold; };
+// lmax j per chunk; fold 0: every chunk contracts all J j.
+struct FoldLay { int N, J, kc, nk, lmax, fold; };
 constexpr int kFoldU = 4;          // slabs in flight per wavefront of the one-trajectory stream
 struct FoldJob {           // folded dense contraction, one trajectory
     const void* C;
     const unsigned short* Clo;
     FoldLay l;
+    const void* wj;                // slab weights [J] (accumulation type); null: u itself
     const double* u_base;
     const long long* stepp;
     long long slot_stride;
@@ -195,22 +193,20 @@ void launch_cvt_f64_to(int dt, const double* src, void* dst, void* dst_lo, long 
 // Scaled-weight copy: out[r] = lambda[r] rounded as the dtype prescribes.
 void launch_cvt_lambda(int dt, const double* src, void* dst, long long n, hipStream_t s);
 
-// Dense contraction, one trajectory: partial sums part[c][i] of
+// Dense contraction of a large BF16 tensor, one trajectory: partial sums part[c][i] of
 // y_i = sum_j u_j sum_k C[i][j][k] u_k over chunk c of the (j,k) plane.
 struct GemvTile { int threads, unroll, chunk_target; };
 int dense_gemv_variants();
 GemvTile dense_gemv_variant(int idx);
 int dense_gemv_nchunk(int N, GemvTile t);
-int launch_dense_gemv(int dt, const void* C, const void* Clo, int N, int Np, int J, const void* wj,
-                      const double* u_base, const long long* stepp, long long slot_stride, void* part, int nchunk,
-                      GemvTile t, hipStream_t s);
+void launch_dense_gemv(const void* C, int N, int Np, const double* u_base, const long long* stepp, long long slot_stride,
+                       void* part, int nchunk, GemvTile t, hipStream_t s);
 // SVD-ROM first product: w_r = sigma_r U[:,r]^T u over the rows of Ut [Rsp][Np]
 void launch_svd_proj(int dt, const void* Ut, const void* Ut_lo, const void* sigma, int N, int Np, int Rs,
                      const double* u_base, const long long* stepp, long long slot_stride, void* w, hipStream_t s);
 
-GemvJob make_gemv_job(int dt, const void* C, const void* Clo, int N, int Np, int J, const void* wj,
-                      const double* u_base, const long long* stepp, long long slot_stride, void* part, int nchunk,
-                      GemvTile t);
+GemvJob make_gemv_job(const void* C, int N, int Np, const double* u_base, const long long* stepp, long long slot_stride,
+                      void* part, int nchunk, GemvTile t);
 // Dense-stiffness apply of a step with, for CP states (np > 0), the projections of the
 // new level (k_contract.hip), one state.
 void launch_helm_proj(int dt, const HelmJob& jb, hipStream_t s);
@@ -321,6 +317,9 @@ hipError_t res_attr(int dt, int N, size_t cap, size_t lds, int* blocks_per_cu);
 // BDF update from contraction partials part[c][b][i] (row stride pb trajectories) in
 // the accumulation type (FP64 for DT_F64, FP32 otherwise).  diag = 1: diagonal
 // stiffness (update, energy partials, step close); diag = 0: right-hand side only.
+// One trajectory: blocks of kBdfRows rows (one-trajectory jobs of a mixed launch too).
+constexpr int kBdfRows = 64;
+inline int bdf1_blocks(int N) { return (N + kBdfRows - 1) / kBdfRows; }
 void launch_bdf_from_partials(const StepArgs& a, int acc_f64, const void* part, int nchunk,
                               int pb, int diag, hipStream_t s);
 // Dense stiffness, one trajectory: u^{n+1} = Hinv_k rhs, energy partials, step close.
@@ -395,15 +394,15 @@ int dense_partials(int dt, int N, int Np, int Bpad, int variant, size_t lds_max)
 void launch_dense_batched(const DensePlan& pl, const void* C, const void* Ct, int N, int Np, int Bpad, const void* X,
                           const void* S, void* part, hipStream_t s);
 
-// The dense contraction over the folded tensor (k_fold.hip; FP64, FP32 and BF16X3): staging
-// of ni rows of the FP64 tensor from row i0 on, the one-trajectory stream and the batched
-// product.  *flag (device) is raised when a word of a folded tensor is not finite.
-FoldLay fold_layout(int dt, int N, bool fold);
+// The dense contraction over the folded tensor (k_fold.hip): staging of ni rows of the FP64
+// tensor (svd: of V[i][k][r]) from row i0 on, the one-trajectory stream and (not BF16) the
+// batched product.  *flag (device) is raised when a word of a folded tensor is not finite.
+FoldLay fold_layout(int dt, int N, int J, bool fold);
 size_t fold_elems(const FoldLay& l);
-void launch_fold_pack(int dt, const double* src, int i0, int ni, const FoldLay& l, void* dst, void* dst_lo, int* flag,
+void launch_fold_pack(int dt, bool svd, const double* src, int i0, int ni, const FoldLay& l, void* dst, void* dst_lo, int* flag,
                       hipStream_t s);
 int fold_gemv_njr(const FoldLay& l, int target);
-FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, const double* u_base, const long long* stepp,
+FoldJob make_fold_job(int dt, const void* C, const void* Clo, const FoldLay& l, const void* wj, const double* u_base, const long long* stepp,
                       long long slot_stride, void* part, int njr);
 size_t fold_gemv_lds(int dt, const FoldJob& jb);
 void launch_fold_gemv(int dt, const FoldJob& jb, hipStream_t s);
