@@ -7,20 +7,21 @@
 namespace rom {
 
 // Unfolding of C [N][N][N] into U [N^2][np] (zero padding past column N): layout 0 rows
-// (i, j) and columns k, layout 1 rows (i, k) and columns j.
+// (i, j) and columns k, layout 1 rows (j, k) and columns i.
 void launch_als_unfold(int N, int np, int layout, const double* C, double* U, hipStream_t s);
 // Ft [R][np] = F^T for F [N][R], zero padding.
 void launch_als_transpose(int N, int R, int np, const double* F, double* Ft, hipStream_t s);
-// T [Bn][R] = U Ft^T in FP64 for U [Bn][np] and Ft [R][np] (np a multiple of 8, Ft with at
-// least 8 readable elements past its end): the plan stages 32 (else 16) rows of U per block
-// in at most lds_cap bytes of LDS; ok is false when neither fits or the allowance is refused.
+// T [Bn][R] = U F in FP64 for U [Bn][np] (16-byte aligned, Bn = N^2, np a multiple of 8; its
+// columns past N are finite) and F [N][R]: ncg groups of g 16-column tiles and nrr row
+// ranges.  ok is false when a tile's columns do not fit in LDS (np > 1000) or the allowance
+// is refused.
 struct AlsProductPlan {
-    int kc, kcp, nbt;
+    int g, ncg, nrr;
     size_t lds;
     bool ok;
 };
-AlsProductPlan als_product_plan(int np, int lds_cap);
-void launch_als_product(const AlsProductPlan& pl, int R, int np, long long Bn, const double* U, const double* Ft,
+AlsProductPlan als_product_plan(int N, int R, int np);
+void launch_als_product(const AlsProductPlan& pl, int N, int R, int np, long long Bn, const double* U, const double* F,
                         double* T, hipStream_t s);
 // M[p][r] (pitch ldm) = sum_q T[row][r] F[q][r] with row = p N + q (keep_first) or q N + p.
 void launch_als_reduce(int N, int R, int keep_first, const double* T, const double* F, double* M, int ldm,
@@ -45,8 +46,10 @@ void launch_gemm_f64_rows(const GemmPlan& pl, const double* A, long long lda, co
                           double* Y, int M, int K, int Bpad, int rows, hipStream_t s);
 // Hinv [n][np] = H^{-1} for SPD H [n][n] by blocked Gauss-Jordan sweeps, one kernel per
 // 32-column panel, with L and X as the two buffers the panels alternate between (each
-// n x n); columns past n of Hinv are left as they are.  *info becomes 1 if a pivot is not
-// positive.
-void spd_inverse_gj(int n, int np, const double* H, double* L, double* X, double* Hinv, int* info, hipStream_t s);
+// n x n) and piv for their inverted pivot blocks (kGjPivots doubles); columns past n of Hinv
+// are left as they are.  *info becomes 1 if a pivot is not positive.
+constexpr size_t kGjPivots = 2 * 32 * 32;
+void spd_inverse_gj(int n, int np, const double* H, double* L, double* X, double* piv, double* Hinv, int* info,
+                    hipStream_t s);
 
 }  // namespace rom

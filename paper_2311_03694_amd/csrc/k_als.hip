@@ -11,32 +11,54 @@
 
 namespace rom {
 
-// The right-hand sides go through two unfoldings of the tensor, each a padded copy
-// [N^2 (rows, padded to bpad)][np] with zero padding:
-//   layout 0: row (i, j), column k = C[i][j][k];   layout 1: row (i, k), column j = C[i][j][k].
-// A product with one factor (FP64 MFMA, k_gemm.hip) then gives T[(a, b)][r], and an
-// elementwise reduction with a second factor the right-hand side.
-__global__ __launch_bounds__(256) void k_als_unfold(int N, int np, int layout, const double* __restrict__ C,
+// The right-hand sides go through two unfoldings of the tensor, rows of pitch np with zero
+// padding:
+//   layout 0: row (i, j), column k = C[i][j][k]   (C itself where N = np and it is aligned);
+//   layout 1: row (j, k), column i = C[i][j][k].
+// A product with one factor (FP64 MFMA) gives T[row][r], and an elementwise reduction with
+// a second factor the right-hand side.
+__global__ __launch_bounds__(256) void k_als_unfold(int N, int np, const double* __restrict__ C,
                                                     double* __restrict__ U, long long total) {
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= total) return;
     const long long row = q / np;
     const int c = (int)(q % np);
-    double v = 0.0;
-    if (c < N) {
-        const long long a = row / N, b = row % N;
-        v = layout == 0 ? C[row * N + c] : C[(a * N + c) * N + b];
+    U[q] = c < N ? C[row * N + c] : 0.0;
+}
+
+// Layout 1 is the transpose of the N x N^2 matrix C[i][(j, k)]: tiles of 32 i x 64 (j, k)
+// through LDS, so both sides are read and written in runs of at least 256 bytes (read
+// without the tiles, N = 200: 73 us; the copy of 2 x 64 MB itself 27).
+__global__ __launch_bounds__(256) void k_als_unfold_t(int N, int np, const double* __restrict__ C,
+                                                      double* __restrict__ U) {
+    __shared__ double tile[32][65];
+    const long long n2 = (long long)N * N, r0 = (long long)blockIdx.x * 64;
+    const int i0 = blockIdx.y * 32, t = threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int i = t / 64 + 4 * e;
+        const long long jk = r0 + t % 64;
+        tile[i][t % 64] = i0 + i < N && jk < n2 ? C[(size_t)(i0 + i) * n2 + jk] : 0.0;
     }
-    U[q] = v;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int r = t / 32 + 8 * e, i = i0 + t % 32;
+        if (r0 + r < n2 && i < np) U[(size_t)(r0 + r) * np + i] = tile[t % 32][r];
+    }
 }
 
 void launch_als_unfold(int N, int np, int layout, const double* C, double* U, hipStream_t s) {
+    if (layout == 1) {
+        const unsigned gx = (unsigned)(((long long)N * N + 63) / 64);
+        hipLaunchKernelGGL(k_als_unfold_t, dim3(gx, (unsigned)((np + 31) / 32)), dim3(256), 0, s, N, np, C, U);
+        return;
+    }
     const long long total = (long long)N * N * np;
-    hipLaunchKernelGGL(k_als_unfold, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, N, np, layout, C, U,
-                       total);
+    hipLaunchKernelGGL(k_als_unfold, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, N, np, C, U, total);
 }
 
-// Ft [R][np] = F^T with zero padding (the product's operand rows).
+// Ft [R][np] = F^T with zero padding (the skinny product's operand rows).
 __global__ __launch_bounds__(256) void k_als_transpose(int N, int R, int np, const double* __restrict__ F,
                                                        double* __restrict__ Ft) {
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -50,151 +72,176 @@ void launch_als_transpose(int N, int R, int np, const double* F, double* Ft, hip
     hipLaunchKernelGGL(k_als_transpose, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, N, R, np, F, Ft);
 }
 
-// T[b][m] = sum_k U[b][k] Ft[m][k] in FP64: the unfolding times one factor, T [Bn][R].
-// A block stages 16 NBT rows of U [Bn][np] in LDS (zeros past np, up to kc = np rounded up
-// to 16, and past Bn; an odd number of 16-byte units per row, so the fragment reads meet
-// no bank conflicts) and forms those rows of T for every m: its four wavefronts take the
-// 16 x 16 tiles (b-tile t % NBT, m-tile t / NBT) for t = w, w + 4, ..., up to four at a
-// time.  A wavefront's U fragment of a step is shared by its tiles; the factor fragments
-// stream from global memory (the factor stays in L2) two steps ahead.  Lane l feeds row
-// l % 16 and the k group l / 16 of a 16-k step, two consecutive k per half-step in both
-// operands; accumulator element v of lane l is row b = l / 16 + 4 v and column
-// m = l % 16.  Rows of Ft past R are clamped for the loads and not stored; k in
-// [np, kc) meets the LDS zeros (the factor rows are finite and the last one has
-// zeroed slack past its end).
+// T[b][m] = sum_k U[b][k] F[k][m] in FP64: the unfolding [Bn][np] times one factor [N][R],
+// T [Bn][R].  A block keeps the factor's columns of G 16-column tiles in LDS for its whole
+// life, in fragment order (one 16-byte vector per lane and 8-k step, zeros past N and R),
+// and its eight wavefronts walk the 16-row tiles of the block's row range, w, w + 8, ...: a
+// wavefront streams its U fragments straight from memory, four steps ahead and on into its
+// next tile, and meets each with G tiles of the panel.  There is one block per compute unit
+// (less those left to the inverse, see als_product_plan), ncg column groups x nrr row ranges
+// (a row range's groups next to each other, so that one XCD's L2 serves them the same rows).
+// Lane l feeds row l % 16 and, of an 8-k step, k = 2 (l / 16) + {0, 1} in both operands;
+// accumulator element v of lane l is row l / 16 + 4 v and column l % 16.  Rows past Bn are
+// clamped for the loads and not stored.
+//
+// Bound by the FP64 matrix rate.  With the rows in LDS and the factor streamed from L2 the
+// product took 146 us on all compute units (N = 200, R = 400: 6.4 GFLOP), on 220 of 256 it
+// takes 131; and the inverse's panels no longer wait for its blocks to retire (35 to 54 us
+// each instead of 8).
 template <int G>
-__device__ __forceinline__ void als_product_round(const double* xs, int kcp, int nsteps, const double* __restrict__ Ft,
-                                                  int np, int R, int mt0, int dm, int bt, long long b0, long long Bn,
-                                                  double* __restrict__ T) {
-    const int lane = threadIdx.x % kWave, g = lane >> 4, c16 = lane & 15;
-    size_t off[G];
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const int m = min((mt0 + i * dm) * 16 + c16, R - 1);
-        off[i] = (size_t)m * np + 4 * g;
-    }
-    const double* xrow = xs + (size_t)(bt * 16 + c16) * kcp + 4 * g;
-    f64x4 acc[G];
-#pragma unroll
-    for (int i = 0; i < G; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
-    // two-step ring of factor fragments; loads past the last step reload it
-    double2 ring[2][G][2];
-    auto issue = [&](int slot, int st) {
-        st = min(st, nsteps - 1);
-#pragma unroll
-        for (int i = 0; i < G; ++i)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) ring[slot][i][h] = *reinterpret_cast<const double2*>(Ft + off[i] + 16 * st + 2 * h);
-    };
-    auto consume = [&](int slot, int st) {
-        double2 a[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) a[h] = *reinterpret_cast<const double2*>(xrow + 16 * st + 2 * h);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h].x, ring[slot][i][h].x, acc[i], 0, 0, 0);
-                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h].y, ring[slot][i][h].y, acc[i], 0, 0, 0);
-            }
-    };
-    issue(0, 0);
-    issue(1, 1);
-    int st = 0;
-    for (; st + 2 <= nsteps; st += 2) {
-        consume(0, st);
-        issue(0, st + 2);
-        consume(1, st + 1);
-        issue(1, st + 3);
-    }
-    if (st < nsteps) consume(0, st);
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const int m = (mt0 + i * dm) * 16 + c16;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const long long b = b0 + bt * 16 + g + 4 * v;
-            if (b < Bn && m < R) T[b * R + m] = acc[i][v];
-        }
-    }
-}
-
-template <int NBT>
-__global__ __launch_bounds__(256) void k_als_product(int R, int np, int kc, int kcp, long long Bn,
-                                                     const double* __restrict__ U, const double* __restrict__ Ft,
+__global__ __launch_bounds__(512) void k_als_product(int N, int R, int np, long long Bn, int ncg, int nrr,
+                                                     const double* __restrict__ U, const double* __restrict__ F,
                                                      double* __restrict__ T) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    double* xs = reinterpret_cast<double*>(smem);
-    const long long b0 = (long long)blockIdx.x * (16 * NBT);
-    const int vr = kc / 2;      // 16-byte vectors per staged row
-    staged_copy<4, double2>(
-        16 * NBT * vr,
+    double2* fs = reinterpret_cast<double2*>(smem);      // [G][ks][64]
+    const int per = (int)gridDim.x / 8, id = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    const int cg = id % ncg, rr = id / ncg;
+    if (rr >= nrr) return;
+    const int ks = np / 8, w = threadIdx.x / kWave, lane = threadIdx.x % kWave, g = lane >> 4, c16 = lane & 15;
+    const int m0 = cg * G * 16;
+    staged_copy<16, double2>(
+        G * ks * kWave,
         [&](int q) {
-            const int r = q / vr, k = (q - r * vr) * 2;
+            const int ln = q % kWave, st = (q / kWave) % ks, t = q / (kWave * ks);
+            const int k = 8 * st + 2 * (ln / 16), m = m0 + 16 * t + ln % 16;
             double2 v = {0.0, 0.0};
-            if (b0 + r < Bn && k < np) v = *reinterpret_cast<const double2*>(U + (size_t)(b0 + r) * np + k);
+            if (m < R && k < N) v.x = F[(size_t)k * R + m];
+            if (m < R && k + 1 < N) v.y = F[(size_t)(k + 1) * R + m];
             return v;
         },
-        [&](int q, const double2& v) {
-            const int r = q / vr, k = (q - r * vr) * 2;
-            *reinterpret_cast<double2*>(xs + (size_t)r * kcp + k) = v;
-        });
+        [&](int q, const double2& v) { fs[q] = v; });
     __syncthreads();
-    const int w = threadIdx.x / kWave, nmt = (R + 15) / 16, bt = w % NBT, dm = 4 / NBT;
-    const int nsteps = kc / 16;
-    int mt0 = w / NBT;
-    int left = mt0 < nmt ? (nmt - mt0 + dm - 1) / dm : 0;
-    // rounds of at most four tiles, as even as possible (13 tiles as 4, 3, 3, 3), so no
-    // round is left with a single accumulator chain
-    for (int rounds = (left + 3) / 4; rounds > 0; --rounds) {
-        const int gsz = (left + rounds - 1) / rounds;
-        if (gsz == 4) als_product_round<4>(xs, kcp, nsteps, Ft, np, R, mt0, dm, bt, b0, Bn, T);
-        else if (gsz == 3) als_product_round<3>(xs, kcp, nsteps, Ft, np, R, mt0, dm, bt, b0, Bn, T);
-        else if (gsz == 2) als_product_round<2>(xs, kcp, nsteps, Ft, np, R, mt0, dm, bt, b0, Bn, T);
-        else als_product_round<1>(xs, kcp, nsteps, Ft, np, R, mt0, dm, bt, b0, Bn, T);
-        left -= gsz;
-        mt0 += gsz * dm;
+
+    const long long tiles = (Bn + 15) / 16, tb = tiles * rr / nrr, te = tiles * (rr + 1) / nrr;
+    constexpr int D = 4;                                 // steps in flight
+    double2 ring[D];
+    auto rowp = [&](long long u) {
+        const long long b = u * 16 + c16;
+        return U + (size_t)(b < Bn ? b : Bn - 1) * np + 2 * g;
+    };
+    long long u = tb + w;
+    if (u >= te) return;
+    const double* row = rowp(u);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        if (d < ks) ring[d] = *reinterpret_cast<const double2*>(row + 8 * d);
+    }
+    for (; u < te; u += 8) {
+        f64x4 acc[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+        auto step = [&](int st, const double2& a) {
+            double2 f[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) f[i] = fs[(i * ks + st) * kWave + lane];
+#pragma unroll
+            for (int i = 0; i < G; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, f[i].x, acc[i], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < G; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, f[i].y, acc[i], 0, 0, 0);
+        };
+        // whole rounds that refill every slot they consume (no branches), then the rest
+        int s0 = 0;
+        for (; s0 + 2 * D <= ks; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const double2 a = ring[d];
+                ring[d] = *reinterpret_cast<const double2*>(row + 8 * (s0 + D + d));
+                step(s0 + d, a);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 2 * D - 1; ++d) {
+            if (s0 + d >= ks) break;
+            const double2 a = ring[d % D];
+            if (s0 + D + d < ks) ring[d % D] = *reinterpret_cast<const double2*>(row + 8 * (s0 + D + d));
+            step(s0 + d, a);
+        }
+        // the next tile's first steps, in flight behind this one's stores
+        if (u + 8 < te) {
+            row = rowp(u + 8);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (d < ks) ring[d] = *reinterpret_cast<const double2*>(row + 8 * d);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int m = m0 + 16 * i + c16;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const long long b = u * 16 + g + 4 * v;
+                if (b < Bn && m < R) T[b * R + m] = acc[i][v];
+            }
+        }
     }
 }
 
-// Each block reserves at least kProductLdsFloor bytes of LDS: two blocks then fill at most
-// 128 KB of a compute unit's 160 KB, which leaves room for a block of the SPD inverse
-// (k_gj_step, 35 KB) that runs beside the product on a side stream; at three blocks per
-// compute unit the inverse's panels wait for product blocks to retire (measured at
-// N = 200, R = 400: 4-7% slower sweeps, and the product itself no faster).
-constexpr size_t kProductLdsFloor = 57344;
+namespace {
 
-AlsProductPlan als_product_plan(int np, int lds_cap) {
+constexpr int kPanelTiles = 6;           // column tiles of a block, at most
+// A panel may take a compute unit's whole LDS.  It reserves at least kPanelReserve, which
+// leaves too little for a block of k_gj_step (27 KB): the inverse beside a product then runs
+// on the compute units that the product's grid leaves it and never shares a unit with it.
+// A product wavefront holds the SIMD's FP64 units 64 cycles an instruction, and a panel of
+// the inverse beside it took 29 us instead of 8 (N = 200, R = 400: 6.9 ms for ten sweeps
+// where they share the units, 5.8 where they don't; 8.4 with the product that staged rows).
+constexpr size_t kPanelLds = 163840, kPanelReserve = 139264;
+
+// the allowance of every plan: calls of different sizes may run at the same time
+template <int G>
+bool panel_ready() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_als_product<G>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPanelLds) == hipSuccess;
+}
+
+template <int G>
+void panel_go(const AlsProductPlan& pl, int N, int R, int np, long long Bn, const double* U, const double* F, double* T,
+              hipStream_t s) {
+    const unsigned blocks = (unsigned)((pl.ncg * pl.nrr + 7) / 8 * 8);
+    hipLaunchKernelGGL(k_als_product<G>, dim3(blocks), dim3(512), pl.lds, s, N, R, np, Bn, pl.ncg, pl.nrr, U, F, T);
+}
+
+}  // namespace
+
+AlsProductPlan als_product_plan(int N, int R, int np) {
     AlsProductPlan pl{};
-    pl.kc = (np + 15) / 16 * 16;
-    int units = pl.kc / 2;                  // 16-byte units of a staged row
-    if (units % 2 == 0) units += 1;
-    pl.kcp = units * 2;
-    for (int nbt = 2; nbt >= 1; --nbt) {
-        const size_t lds = (size_t)nbt * 16 * pl.kcp * sizeof(double);
-        if (lds <= (size_t)lds_cap) {
-            pl.nbt = nbt;
-            pl.lds = std::max(lds, std::min(kProductLdsFloor, (size_t)lds_cap));
-            break;
-        }
+    const int nmt = (R + 15) / 16, ks = np / 8;
+    const int gmax = (int)std::min<size_t>(kPanelTiles, kPanelLds / ((size_t)ks * kWave * sizeof(double2)));
+    // one tile of columns is the least (the skinny GEMM that is left past it took three times as
+    // long where both can run: N = R = 500, three sweeps 62 ms, here 21)
+    if (gmax < 1) return pl;
+    pl.ncg = (nmt + gmax - 1) / gmax;
+    pl.g = (nmt + pl.ncg - 1) / pl.ncg;
+    const long long tiles = ((long long)N * N + 15) / 16;
+    // compute units per XCD left to the inverse: its nb^2 tiles in two rounds of three blocks a
+    // unit (only one tile of a panel has more to do than two 32 x 32 products).  Ten sweeps at
+    // N = 200, R = 400 (nb = 13): 7.4 ms with three units, 5.75 with 4 or 5, 5.9 with 6, 6.1
+    // with 8.
+    const int nb = (R + 31) / 32, cus = 32 - std::min(8, ((nb * nb + 7) / 8 + 5) / 6);
+    pl.nrr = (int)std::max<long long>(1, std::min<long long>(tiles, 8 * cus / pl.ncg));
+    pl.lds = std::max((size_t)pl.g * ks * kWave * sizeof(double2), kPanelReserve);
+    switch (pl.g) {
+        case 1: pl.ok = panel_ready<1>(); break;
+        case 2: pl.ok = panel_ready<2>(); break;
+        case 3: pl.ok = panel_ready<3>(); break;
+        case 4: pl.ok = panel_ready<4>(); break;
+        case 5: pl.ok = panel_ready<5>(); break;
+        case 6: pl.ok = panel_ready<6>(); break;
     }
-    if (pl.nbt == 2)
-        pl.ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_als_product<2>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds) == hipSuccess;
-    else if (pl.nbt == 1)
-        pl.ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_als_product<1>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds) == hipSuccess;
     if (!pl.ok) (void)hipGetLastError();    // a refused allowance is not the caller's error
     return pl;
 }
 
-void launch_als_product(const AlsProductPlan& pl, int R, int np, long long Bn, const double* U, const double* Ft,
+void launch_als_product(const AlsProductPlan& pl, int N, int R, int np, long long Bn, const double* U, const double* F,
                         double* T, hipStream_t s) {
-    const unsigned blocks = (unsigned)((Bn + 16 * pl.nbt - 1) / (16 * pl.nbt));
-    if (pl.nbt == 2)
-        hipLaunchKernelGGL(k_als_product<2>, dim3(blocks), dim3(256), pl.lds, s, R, np, pl.kc, pl.kcp, Bn, U, Ft, T);
-    else
-        hipLaunchKernelGGL(k_als_product<1>, dim3(blocks), dim3(256), pl.lds, s, R, np, pl.kc, pl.kcp, Bn, U, Ft, T);
+    switch (pl.g) {
+        case 1: panel_go<1>(pl, N, R, np, Bn, U, F, T, s); break;
+        case 2: panel_go<2>(pl, N, R, np, Bn, U, F, T, s); break;
+        case 3: panel_go<3>(pl, N, R, np, Bn, U, F, T, s); break;
+        case 4: panel_go<4>(pl, N, R, np, Bn, U, F, T, s); break;
+        case 5: panel_go<5>(pl, N, R, np, Bn, U, F, T, s); break;
+        case 6: panel_go<6>(pl, N, R, np, Bn, U, F, T, s); break;
+    }
 }
 
 // M[p][r] (pitch ldm) = sum_q T[row(p, q)][r] F[q][r], row = p N + q (first index
@@ -238,7 +285,7 @@ constexpr int kGramParts = 4;
 __global__ __launch_bounds__(256 * kGramParts) void k_gram_hadamard(int N, int R, const double* __restrict__ Fa,
                                                                    const double* __restrict__ Fb,
                                                                    double* __restrict__ V) {
-    __shared__ f64x4 part[kGramParts - 1][4][kWave][2];
+    __shared__ f64x4 part[kGramParts - 1][4][kWave];
     const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave, qd = w % 4, kp = w / 4;
     const int r0 = blockIdx.y * 32 + (qd / 2) * 16, c0 = blockIdx.x * 32 + (qd % 2) * 16;
     const int rr = min(r0 + lane % 16, R - 1), cc = min(c0 + lane % 16, R - 1);
@@ -254,17 +301,18 @@ __global__ __launch_bounds__(256 * kGramParts) void k_gram_hadamard(int N, int R
         ga = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, ac, ga, 0, 0, 0);
         gb = __builtin_amdgcn_mfma_f64_16x16x4f64(br, bc, gb, 0, 0, 0);
     }
-    if (kp > 0) {
-        part[kp - 1][qd][lane][0] = ga;
-        part[kp - 1][qd][lane][1] = gb;
+    if (kp > 0) part[kp - 1][qd][lane] = ga;
+    __syncthreads();
+    if (kp == 0) {
+#pragma unroll
+        for (int q = 0; q < kGramParts - 1; ++q) ga += part[q][qd][lane];
     }
+    __syncthreads();
+    if (kp > 0) part[kp - 1][qd][lane] = gb;
     __syncthreads();
     if (kp > 0) return;
 #pragma unroll
-    for (int q = 0; q < kGramParts - 1; ++q) {
-        ga += part[q][qd][lane][0];
-        gb += part[q][qd][lane][1];
-    }
+    for (int q = 0; q < kGramParts - 1; ++q) gb += part[q][qd][lane];
     // accumulator element v of lane l: row l / 16 + 4 v, column l % 16
 #pragma unroll
     for (int v = 0; v < 4; ++v) {

@@ -376,13 +376,18 @@ int helm_setup_dense(int N, int Np, double nu, double dt, const double* A_dev, c
 // from k0, b of them) maps the matrix out of place:
 //   A'_KK = P^-1,  A'_KJ = P^-1 A_KJ,  A'_IK = -A_IK P^-1,  A'_IJ = A_IJ - A_IK P^-1 A_KJ,
 // P = A_KK; after every panel the matrix is A^-1.  One kernel per panel, one block per
-// 32 x 32 tile of the result.  Every block inverts P itself, by sweeps of the same
-// formulas over its 2 x 2 diagonal blocks in registers (thread t holds column t % 32 of
-// rows 4 (t / 32) .. +3; the pivot rows and columns go through LDS, one barrier per
-// sweep) while its tile operands are in flight; then the block's four waves form the
-// tile's 16 x 16 quarters with FP64 MFMA.  The old matrix is only read, so no block waits
-// for another.  The block of tile (K, K) raises *info on a pivot block that is not
-// positive definite.
+// 32 x 32 tile of the result, whose four waves form the tile's 16 x 16 quarters with FP64
+// MFMA.  The old matrix is only read, so no block waits for another.
+//
+// P^-1 comes from the kernel before: the block of tile (K + 1, K + 1), the first one of the
+// grid, holds the next pivot block as soon as it has formed its tile; it inverts it, by
+// sweeps of the same formulas over its 2 x 2 diagonal blocks in registers (thread t holds
+// column t % 32 of rows 4 (t / 32) .. +3; the pivot rows and columns go through LDS, one
+// barrier per sweep), and raises *info if it is not positive definite.  Only the first
+// panel's blocks invert P themselves.  With every block of every panel inverting P, a panel
+// took the same 8.3 us alone (the chain is load, products, sweeps, store either way), but
+// 15 us beside a product on other compute units, where the blocks that share a compute
+// unit share its FP64 units (169 tiles, N = 200, R = 400).
 constexpr int kGjNb = 32;
 
 namespace {
@@ -412,50 +417,15 @@ __device__ __forceinline__ double gj_recip(double d) {
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_gj_step(int n, int k0, const double* __restrict__ src, int sp,
-                                                 double* __restrict__ dst, int dp, int* info) {
-    __shared__ double Pi[kGjNb][kGjNb + 1], Aik[kGjNb][kGjNb + 1], Akj[kGjNb][kGjNb + 1], Rkj[kGjNb][kGjNb + 1];
-    __shared__ __attribute__((aligned(16))) double rowb[2][2][kGjNb], colb[2][2][kGjNb];
-    const int b = n - k0 < kGjNb ? n - k0 : kGjNb;
-    const int i0 = blockIdx.y * kGjNb, j0 = blockIdx.x * kGjNb;
-    const bool ik = i0 == k0, jk = j0 == k0;          // tiles are aligned with the panels
-    const int bi = n - i0 < kGjNb ? n - i0 : kGjNb, bj = n - j0 < kGjNb ? n - j0 : kGjNb;
+// x (this thread's entries of the kGjNb x kGjNb block P, see above) -> P^-1, by the map of
+// the panels with 2 x 2 pivot blocks Q (SPD as principal blocks of the Schur complements),
+// pivots c0 = 2s, c1 = 2s + 1: rows c0, c1 become Q^-1 (rows c0, c1), columns c0, c1 become
+// -(columns c0, c1) Q^-1, the pivot block Q^-1, the rest x - (columns c0, c1) Q^-1 (rows
+// c0, c1).  Rows and columns c0, c1 pass through LDS (double buffered: one barrier per pivot
+// block).  Returns whether a pivot was not positive.
+typedef double GjLine[2][kGjNb];
+static __device__ __forceinline__ bool gj_invert(double (&x)[4], GjLine* rowb, GjLine* colb) {
     const int t = threadIdx.x, cc = t % kGjNb, rg = t / kGjNb;
-    const int w = t / kWave, lane = t % kWave;
-    const int rq = (w / 2) * 16, cq = (w % 2) * 16;    // this wave's quarter of the tile
-
-    // P, extended by the identity beyond b (pivots of 1 with zero rows and columns: their
-    // sweeps change nothing, so every block sweeps all kGjNb of them).  The tile operands
-    // (zero beyond the tile) stay in registers until the sweeps are done.  Every load is
-    // issued (addresses clamped into the matrix) and its value selected afterwards, so the
-    // sweeps wait for P's loads alone.
-    const int nm = n - 1;
-    auto at = [&](int r, int c) { return src[(size_t)(r < nm ? r : nm) * sp + (c < nm ? c : nm)]; };
-    double x[4], aik[4], akj[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = at(k0 + 4 * rg + e, k0 + cc);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int q = t + e * 256, r = q / kGjNb, c = q % kGjNb;
-        aik[e] = at(i0 + r, k0 + c);
-        akj[e] = at(k0 + r, j0 + c);
-    }
-    f64x4 acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = at(i0 + rq + lane / 16 + 4 * v, j0 + cq + lane % 16);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int r = 4 * rg + e;
-        x[e] = (r < b && cc < b) ? x[e] : (r == cc ? 1.0 : 0.0);
-    }
-
-    // P -> P^-1 by the same map with 2 x 2 pivot blocks Q (SPD as principal blocks of the
-    // Schur complements), pivots c0 = 2s, c1 = 2s + 1: rows c0, c1 become Q^-1 (rows c0, c1),
-    // columns c0, c1 become -(columns c0, c1) Q^-1, the pivot block Q^-1, the rest
-    // x - (columns c0, c1) Q^-1 (rows c0, c1).  Rows and columns c0, c1 pass through LDS
-    // (double buffered: one barrier per pivot block).
     bool bad = false;
 #pragma unroll
     for (int st = 0; st < kGjNb / 2; ++st) {
@@ -501,8 +471,62 @@ __global__ __launch_bounds__(256) void k_gj_step(int n, int k0, const double* __
             x[e] = v;
         }
     }
+    return bad;
+}
+
+// The panel from k0: pin holds P^-1 [kGjNb][kGjNb] (FIRST: inverted here), the next panel's
+// goes to pout.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_gj_step(int n, int k0, const double* __restrict__ src, int sp,
+                                                 double* __restrict__ dst, int dp, const double* __restrict__ pin,
+                                                 double* __restrict__ pout, int* info) {
+    __shared__ double Pi[kGjNb][kGjNb + 1], Aik[kGjNb][kGjNb + 1], Akj[kGjNb][kGjNb + 1];
+    __shared__ __attribute__((aligned(16))) GjLine rowb[2], colb[2];
+    // the panels are the serial chain of the inverse: their wavefronts go first where they
+    // share a SIMD
+    __builtin_amdgcn_s_setprio(3);
+    const int nb = gridDim.x, kb = k0 / kGjNb, next = kb + 1 < nb ? (kb + 1) * (nb + 1) : 0;
+    int id = blockIdx.y * nb + blockIdx.x;
+    id = id == 0 ? next : id == next ? 0 : id;          // tile (K + 1, K + 1) first
+    const int b = n - k0 < kGjNb ? n - k0 : kGjNb;
+    const int i0 = id / nb * kGjNb, j0 = id % nb * kGjNb;
+    const bool ik = i0 == k0, jk = j0 == k0;          // tiles are aligned with the panels
+    const bool pivot = kb + 1 < nb && id == next;
+    const int bi = n - i0 < kGjNb ? n - i0 : kGjNb, bj = n - j0 < kGjNb ? n - j0 : kGjNb;
+    const int t = threadIdx.x, cc = t % kGjNb, rg = t / kGjNb;
+    const int w = t / kWave, lane = t % kWave;
+    const int rq = (w / 2) * 16, cq = (w % 2) * 16;    // this wave's quarter of the tile
+
+    // P (or P^-1) and the tile operands (zero beyond the tile).  Every load is issued
+    // (addresses clamped into the matrix) and its value selected afterwards.
+    const int nm = n - 1;
+    auto at = [&](int r, int c) { return src[(size_t)(r < nm ? r : nm) * sp + (c < nm ? c : nm)]; };
+    double x[4], aik[4], akj[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = FIRST ? at(k0 + 4 * rg + e, k0 + cc) : pin[(4 * rg + e) * kGjNb + cc];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int q = t + e * 256, r = q / kGjNb, c = q % kGjNb;
+        aik[e] = at(i0 + r, k0 + c);
+        akj[e] = at(k0 + r, j0 + c);
+    }
+    f64x4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = at(i0 + rq + lane / 16 + 4 * v, j0 + cq + lane % 16);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FIRST) {
+        // extended by the identity beyond b (pivots of 1 with zero rows and columns: their
+        // sweeps change nothing, so every block sweeps all kGjNb of them)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = 4 * rg + e;
+            x[e] = (r < b && cc < b) ? x[e] : (r == cc ? 1.0 : 0.0);
+        }
+        const bool bad = gj_invert(x, rowb, colb);
+        if (ik && jk && t == 0 && bad) atomicMax(info, 1);
+    }
     if (ik && jk) {
-        if (t == 0 && bad) atomicMax(info, 1);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int r = 4 * rg + e;
@@ -531,19 +555,36 @@ __global__ __launch_bounds__(256) void k_gj_step(int n, int k0, const double* __
     } else {
         f64x4 rk = {0.0, 0.0, 0.0, 0.0};
         gj_quarter(rk, Pi, rq, Akj, cq, 1.0);                   // R = P^-1 A_KJ
+        __syncthreads();                                        // (every wave has read A_KJ)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Rkj[rq + lane / 16 + 4 * v][cq + lane % 16] = rk[v];
+        for (int v = 0; v < 4; ++v) Akj[rq + lane / 16 + 4 * v][cq + lane % 16] = rk[v];
         __syncthreads();
-        gj_quarter(acc, Aik, rq, Rkj, cq, -1.0);                // A_IJ - A_IK R
+        gj_quarter(acc, Aik, rq, Akj, cq, -1.0);                // A_IJ - A_IK R
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int r = rq + lane / 16 + 4 * v, c = cq + lane % 16;
         if (r < bi && c < bj) dst[(size_t)(i0 + r) * dp + j0 + c] = acc[v];
     }
+    if (!pivot) return;
+    // the next pivot block, extended by the identity, inverted (Pi is free: its last reads
+    // lie before the barriers of R)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int r = rq + lane / 16 + 4 * v, c = cq + lane % 16;
+        Pi[r][c] = (r < bi && c < bi) ? acc[v] : (r == c ? 1.0 : 0.0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = Pi[4 * rg + e][cc];
+    const bool bad = gj_invert(x, rowb, colb);
+    if (t == 0 && bad) atomicMax(info, 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pout[(4 * rg + e) * kGjNb + cc] = x[e];
 }
 
-void spd_inverse_gj(int n, int np, const double* H, double* L, double* X, double* Hinv, int* info, hipStream_t s) {
+void spd_inverse_gj(int n, int np, const double* H, double* L, double* X, double* piv, double* Hinv, int* info,
+                    hipStream_t s) {
     const int nb = (n + kGjNb - 1) / kGjNb;
     const dim3 grid((unsigned)nb, (unsigned)nb);
     const double* src = H;
@@ -552,7 +593,12 @@ void spd_inverse_gj(int n, int np, const double* H, double* L, double* X, double
         const bool last = q == nb - 1;
         double* dst = last ? Hinv : (q % 2 == 0 ? L : X);
         const int dp = last ? np : n;
-        hipLaunchKernelGGL(k_gj_step, grid, dim3(256), 0, s, n, q * kGjNb, src, sp, dst, dp, info);
+        const double* pin = piv + (q % 2) * kGjNb * kGjNb;
+        double* pout = piv + (1 - q % 2) * kGjNb * kGjNb;
+        if (q == 0)
+            hipLaunchKernelGGL(k_gj_step<true>, grid, dim3(256), 0, s, n, 0, src, sp, dst, dp, pin, pout, info);
+        else
+            hipLaunchKernelGGL(k_gj_step<false>, grid, dim3(256), 0, s, n, q * kGjNb, src, sp, dst, dp, pin, pout, info);
         src = dst;
         sp = dp;
     }

@@ -947,59 +947,105 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
 }
 
 extern "C" rom_status rom_create(const rom_desc* d, rom_ctx* out) { return create_ctx(d, nullptr, nullptr, out); }
-// The tensor-factor product of the ALS sweeps on its own FP64 MFMA kernel (k_als.hip)
-// when 16 or 32 rows of the unfolding fit in 64 KB of LDS (N up to 496; the allowance is
-// set here, before any capture), else on the skinny GEMM.  The transposed factor it reads
-// gets kProductSlack zeroed elements past its end.
-constexpr size_t kProductSlack = 16;
-constexpr int kProductLds = 65536;
+// Workspace of an ALS call: one allocation cut into arrays of doubles (256-byte aligned).
+struct AlsSlab {
+    double* base = nullptr;
+    size_t words = 0;
+    size_t add(size_t n) {
+        const size_t at = words;
+        words += (n + 31) / 32 * 32;
+        return at;
+    }
+    hipError_t alloc() { return hipMalloc((void**)&base, sizeof(double) * words); }
+    double* at(size_t o) const { return base + o; }
+    ~AlsSlab() {
+        if (base) hipFree(base);
+    }
+};
 
-// Streams and graph of an ALS call: the capture stream cs (ordered after the caller's
-// stream), a side stream for the SPD inverses, and one fork / join event pair per inverse
-// of a sweep (kPairs - 1 for ALS-skew's subiterations, taken in turn, and the last for
-// its tied system).  fork(q) makes the side stream wait for cs; join_mark(q) records the side
-// stream's work; join(q) makes cs wait for it.  The side stream joins the capture through
-// the fork and leaves it through the join, so the graph holds the inverse as a branch.
+// The tensor-factor product of the ALS sweeps, T[row][m] = sum_c U[row][c] F[c][m]: on its own
+// FP64 MFMA kernel (k_als.hip; its LDS allowance is set here, before any capture), else
+// (np > 1000) on the skinny GEMM with the transposed factor.  The skinny GEMM reads whole
+// 16-row tiles of padded rows; the kernel reads a tensor whose rows are whole 8-k steps, and
+// 16-byte aligned, in place.
+struct AlsProduct {
+    int N, R, np, n2pad;
+    AlsProductPlan plan;
+    GemmPlan skinny;
+    double* Ft = nullptr;                  // skinny: [R][np]
+    AlsProduct(int N_, int R_, int np_)
+        : N(N_), R(R_), np(np_), n2pad((int)(((size_t)N_ * N_ + 15) / 16 * 16)), plan(als_product_plan(N_, R_, np_)),
+          skinny(gemm_plan(R_, n2pad, 0)) {}
+    bool in_place(const double* C) const { return plan.ok && N == np && ((uintptr_t)C & 15) == 0; }
+    size_t unfolded() const { return (plan.ok ? (size_t)N * N : (size_t)n2pad) * np; }
+    size_t transposed() const { return plan.ok ? 0 : (size_t)R * np; }
+    hipError_t unfold(int layout, const double* C, double* U, hipStream_t s) const {
+        launch_als_unfold(N, np, layout, C, U, s);
+        const size_t rows = (size_t)N * N * np;
+        return rows < unfolded() ? hipMemsetAsync(U + rows, 0, sizeof(double) * (unfolded() - rows), s) : hipSuccess;
+    }
+    void operator()(const double* U, const double* F, double* T, hipStream_t s) const {
+        if (plan.ok) {
+            launch_als_product(plan, N, R, np, (long long)N * N, U, F, T, s);
+            return;
+        }
+        launch_als_transpose(N, R, np, F, Ft, s);
+        launch_gemm_f64(skinny, Ft, (long long)np, U, (long long)np, T, R, np, n2pad, s);
+    }
+};
+
+// The two streams of an ALS call: the caller's carries the chain of a sweep (Gram products,
+// SPD inverses, solves), a second one the products with the tensor and the right-hand sides.
+// post(q) / wait(q): the second stream waits for the chain; done(q) / join(q): the chain
+// waits for the second stream.  The sweeps are launched directly: a graph of a sweep submits
+// a whole branch before the next one (N = 200, R = 400: a product was submitted 80 us after
+// it could have run, behind the panels of the inverse beside it), and its capture,
+// instantiation and release cost 0.4 ms a call.
 struct SweepStreams {
-    static constexpr int kPairs = 9;
-    hipStream_t cs = nullptr, side = nullptr;
-    hipEvent_t start = nullptr, evf[kPairs] = {}, evj[kPairs] = {};
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    bool init(hipStream_t caller) {
-        if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess ||
-            hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&start, hipEventDisableTiming) != hipSuccess)
-            return false;
+    static constexpr int kPairs = 3;
+    hipStream_t chain, rhs = nullptr;
+    hipEvent_t evp[kPairs] = {}, evd[kPairs] = {};
+    bool ok = false;
+    explicit SweepStreams(hipStream_t s) : chain(s) {
+        ok = hipStreamCreateWithFlags(&rhs, hipStreamNonBlocking) == hipSuccess;
         for (int q = 0; q < kPairs; ++q)
-            if (hipEventCreateWithFlags(&evf[q], hipEventDisableTiming) != hipSuccess ||
-                hipEventCreateWithFlags(&evj[q], hipEventDisableTiming) != hipSuccess)
-                return false;
-        return hipEventRecord(start, caller) == hipSuccess && hipStreamWaitEvent(cs, start, 0) == hipSuccess;
+            ok = ok && hipEventCreateWithFlags(&evp[q], hipEventDisableTiming) == hipSuccess &&
+                 hipEventCreateWithFlags(&evd[q], hipEventDisableTiming) == hipSuccess;
     }
-    bool fork(int q) {
-        return q < kPairs && hipEventRecord(evf[q], cs) == hipSuccess && hipStreamWaitEvent(side, evf[q], 0) == hipSuccess;
-    }
-    bool join_mark(int q) { return q < kPairs && hipEventRecord(evj[q], side) == hipSuccess; }
-    bool join(int q) { return q < kPairs && hipStreamWaitEvent(cs, evj[q], 0) == hipSuccess; }
+    void post(int q) { ok = ok && hipEventRecord(evp[q], chain) == hipSuccess; }
+    void wait(int q) { ok = ok && hipStreamWaitEvent(rhs, evp[q], 0) == hipSuccess; }
+    void done(int q) { ok = ok && hipEventRecord(evd[q], rhs) == hipSuccess; }
+    void join(int q) { ok = ok && hipStreamWaitEvent(chain, evd[q], 0) == hipSuccess; }
     ~SweepStreams() {
-        if (gexec) hipGraphExecDestroy(gexec);
-        if (graph) hipGraphDestroy(graph);
-        if (cs) {
-            hipStreamSynchronize(cs);
-            hipStreamDestroy(cs);
+        // the workspace is given back next
+        hipStreamSynchronize(chain);
+        if (rhs) {
+            hipStreamSynchronize(rhs);
+            hipStreamDestroy(rhs);
         }
-        if (side) {
-            hipStreamSynchronize(side);
-            hipStreamDestroy(side);
-        }
-        if (start) hipEventDestroy(start);
         for (int q = 0; q < kPairs; ++q) {
-            if (evf[q]) hipEventDestroy(evf[q]);
-            if (evj[q]) hipEventDestroy(evj[q]);
+            if (evp[q]) hipEventDestroy(evp[q]);
+            if (evd[q]) hipEventDestroy(evd[q]);
         }
     }
 };
+
+// The end of an ALS call: waits for the sweeps and reports a pivot that was not positive.
+static rom_status als_finish(const SweepStreams& ss, const int* info, const char* what) {
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && !ss.ok) e = hipErrorUnknown;
+    int hinfo = 0;
+    if (e == hipSuccess) e = hipMemcpyWithStream(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, ss.chain);
+    if (e != hipSuccess) return fail(ROM_E_DEVICE, "%s failed: %s", what, hipGetErrorString(e));
+    if (hinfo) return fail(ROM_E_INVALID, "%s normal equations not positive definite (rank-deficient factors)", what);
+    return ROM_OK;
+}
+
+// An ALS call ends with a synchronization, so it is refused on a stream under capture.
+static bool als_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
 
 extern "C" rom_status rom_cp_als(int32_t N, int32_t R, const double* C, double* A1, double* A2, double* A3,
                                   int32_t sweeps, void* stream) {
@@ -1009,92 +1055,76 @@ extern "C" rom_status rom_cp_als(int32_t N, int32_t R, const double* C, double* 
     if (!C || !A1 || !A2 || !A3) return fail(ROM_E_INVALID, "a tensor or factor pointer is NULL");
     if (sweeps == 0) return ROM_OK;
     hipStream_t s = (hipStream_t)stream;
+    if (als_capturing(s)) return fail(ROM_E_DEVICE, "CP-ALS cannot run on a stream under capture");
     const size_t n = (size_t)N, r = (size_t)R, rp = (r + 7) / 8 * 8, npad = (n + 15) / 16 * 16;
-    const size_t np = (n + 7) / 8 * 8, n2pad = (n * n + 15) / 16 * 16;
-    // V and the two panel buffers of its inverse [R][R]; Vinv [R][Rp] and the right-hand
-    // side Mb [Npad][Rp] with zero padding (the product's K = Rp; the product M V^-1 is
-    // written straight into the factor's N rows); the two unfoldings of C [N^2 padded][Np],
-    // a transposed factor [R][Np] and the tensor-factor product T [N^2 padded][R]
-    constexpr int kBufs = 9;
-    const size_t sizes[kBufs] = {r * r, r * r, r * r, r * rp, npad * rp, n2pad * np, n2pad * np,
-                                 r * np + kProductSlack, n2pad * r};
-    double* buf[kBufs] = {};
-    int* info = nullptr;
-    struct Guard {
-        double** b;
-        int** info;
-        ~Guard() {
-            for (int q = 0; q < kBufs; ++q)
-                if (b[q]) hipFree(b[q]);
-            if (*info) hipFree(*info);
-        }
-    } guard{buf, &info};
-    for (int q = 0; q < kBufs; ++q) {
-        const hipError_t e = hipMalloc((void**)&buf[q], sizeof(double) * sizes[q]);
-        if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? ROM_E_NOMEM : ROM_E_DEVICE, "CP-ALS workspace: %s",
-                                         hipGetErrorString(e));
-    }
-    if (hipMalloc((void**)&info, sizeof(int)) != hipSuccess) return fail(ROM_E_NOMEM, "CP-ALS workspace");
-    double *V = buf[0], *L = buf[1], *X = buf[2], *Vinv = buf[3], *Mb = buf[4];
-    double *U0 = buf[5], *U1 = buf[6], *Ft = buf[7], *T = buf[8];
-    if (hipMemsetAsync(Vinv, 0, sizeof(double) * sizes[3], s) != hipSuccess ||
-        hipMemsetAsync(Mb, 0, sizeof(double) * sizes[4], s) != hipSuccess ||
-        hipMemsetAsync(U0, 0, sizeof(double) * sizes[5], s) != hipSuccess ||
-        hipMemsetAsync(U1, 0, sizeof(double) * sizes[6], s) != hipSuccess ||
-        hipMemsetAsync(Ft, 0, sizeof(double) * sizes[7], s) != hipSuccess ||
-        hipMemsetAsync(info, 0, sizeof(int), s) != hipSuccess)
-        return fail(ROM_E_DEVICE, "CP-ALS workspace clear failed");
-    launch_als_unfold(N, (int)np, 0, C, U0, s);     // rows (i, j), columns k
-    launch_als_unfold(N, (int)np, 1, C, U1, s);     // rows (i, k), columns j
-    // one sweep (about 3 R / 16 + 30 launches) is captured once into a graph on a stream of
-    // this call, ordered after the caller's stream, and replayed `sweeps` times; each
-    // inverse runs on a side stream beside the right-hand side of its update (a branch of
-    // the graph)
-    SweepStreams ss;
-    if (!ss.init(s)) return fail(ROM_E_DEVICE, "CP-ALS stream setup failed");
-    hipStream_t cs = ss.cs;
-    hipGraph_t& graph = ss.graph;
-    hipGraphExec_t& gexec = ss.gexec;
-    double* F[3] = {A1, A2, A3};
-    const GemmPlan pl = gemm_plan(R, (int)npad, 0), plt = gemm_plan(R, (int)n2pad, 0);
-    const AlsProductPlan prod = als_product_plan((int)np, kProductLds);
-    // T[row][m] = sum_c Ft[m][c] U[row][c]: the unfolding times one factor
-    auto tensor_times = [&](const double* Uf, const double* Fk) {
-        launch_als_transpose(N, R, (int)np, Fk, Ft, s);
-        if (prod.ok) launch_als_product(prod, R, (int)np, (long long)n2pad, Uf, Ft, T, s);
-        else launch_gemm_f64(plt, Ft, (long long)np, Uf, (long long)np, T, R, (int)np, (int)n2pad, s);
+    const size_t np = (n + 7) / 8 * 8;
+    AlsProduct times(N, R, (int)np);
+    // Vinv [R][Rp] and the right-hand side Mb [Npad][Rp] with zero padding (the product's
+    // K = Rp; the product M V^-1 is written straight into the factor's N rows); V and the two
+    // panel buffers of its inverse [R][R]; the two unfoldings of C, and the tensor-factor
+    // product T [N^2 padded][R]
+    const bool in_place = times.in_place(C);
+    AlsSlab ws;
+    const size_t o_vinv = ws.add(r * rp), o_mb = ws.add(npad * rp), o_info = ws.add(1), cleared = ws.words;
+    const size_t o_v = ws.add(r * r), o_l = ws.add(r * r), o_x = ws.add(r * r), o_ft = ws.add(times.transposed());
+    const size_t o_piv = ws.add(kGjPivots);
+    const size_t o_u0 = ws.add(in_place ? 0 : times.unfolded()), o_u1 = ws.add(times.unfolded());
+    const size_t o_t = ws.add((size_t)times.n2pad * r);
+    const hipError_t me = ws.alloc();
+    if (me != hipSuccess)
+        return fail(me == hipErrorOutOfMemory ? ROM_E_NOMEM : ROM_E_DEVICE, "CP-ALS workspace: %s", hipGetErrorString(me));
+    double *V = ws.at(o_v), *L = ws.at(o_l), *X = ws.at(o_x), *Vinv = ws.at(o_vinv), *Mb = ws.at(o_mb);
+    double *U1 = ws.at(o_u1), *T = ws.at(o_t);
+    const double* U0 = in_place ? C : ws.at(o_u0);
+    double* piv = ws.at(o_piv);
+    int* info = reinterpret_cast<int*>(ws.at(o_info));
+    times.Ft = ws.at(o_ft);
+    if (hipMemsetAsync(ws.base, 0, sizeof(double) * cleared, s) != hipSuccess ||
+        (!in_place && times.unfold(0, C, ws.at(o_u0), s) != hipSuccess) || times.unfold(1, C, U1, s) != hipSuccess)
+        return fail(ROM_E_DEVICE, "CP-ALS workspace setup failed");
+    // The serial chain of a sweep is that of its three inverses (one kernel per 32 columns of
+    // V), each behind the Gram product of the factors it takes and followed by the solve.
+    // The right-hand sides run beside them: T = C x_3 A3 (rows (i, j)) serves the first two;
+    // the third takes T = C x_1 A1 (rows (j, k)), which needs the first factor only, so that
+    // it can run beside both inverses that follow that factor's update.
+    SweepStreams ss(s);
+    hipStream_t q = ss.rhs;
+    const GemmPlan pl = gemm_plan(R, (int)npad, 0);
+    auto normal = [&](const double* Fa, const double* Fb) {
+        launch_gram_hadamard(N, R, Fa, Fb, V, s);
+        spd_inverse_gj(R, (int)rp, V, L, X, piv, Vinv, info, s);
     };
-    s = cs;   // every launch below (tensor_times included) goes to the capture stream
-    if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess)
-        return fail(ROM_E_DEVICE, "CP-ALS graph capture failed to start");
-    bool cap_ok = true;
-    for (int mode = 0; mode < 3; ++mode) {
-            const int a = mode == 0 ? 1 : 0, b = mode == 2 ? 1 : 2;
-            launch_gram_hadamard(N, R, F[a], F[b], V, s);
-            cap_ok = ss.fork(mode) && cap_ok;
-            spd_inverse_gj(R, (int)rp, V, L, X, Vinv, info, ss.side);
-            cap_ok = ss.join_mark(mode) && cap_ok;
-            // right-hand side: modes 1 and 2 share T = C x_k A3 (A3 is fixed until mode 3);
-            // mode 3 uses C x_j A2 over rows (i, k)
-            if (mode == 0) tensor_times(U0, F[2]);
-            if (mode == 2) tensor_times(U1, F[1]);
-            if (mode == 0) launch_als_reduce(N, R, 1, T, F[1], Mb, (int)rp, s);       // sum_j T[(i,j)] A2[j]
-            else launch_als_reduce(N, R, 0, T, F[0], Mb, (int)rp, s);                 // sum_i T[(i,.)] A1[i]
-            cap_ok = ss.join(mode) && cap_ok;
-            // F[mode][i][m] = sum_k Vinv[m][k] Mb[i][k]  (V symmetric)
-            launch_gemm_f64_rows(pl, Vinv, (long long)rp, Mb, (long long)rp, F[mode], R, (int)rp, (int)npad, N, s);
+    // F[i][m] = sum_k Vinv[m][k] Mb[i][k]  (V symmetric)
+    auto solve = [&](double* F) {
+        launch_gemm_f64_rows(pl, Vinv, (long long)rp, Mb, (long long)rp, F, R, (int)rp, (int)npad, N, s);
+    };
+    ss.post(0);
+    for (int sw = 0; sw < sweeps && ss.ok; ++sw) {
+        ss.wait(0);                                                // A3
+        times(U0, A3, T, q);
+        launch_als_reduce(N, R, 1, T, A2, Mb, (int)rp, q);        // sum_j T[(i, j)] A2[j]
+        ss.done(0);
+        normal(A2, A3);
+        ss.join(0);
+        solve(A1);
+        ss.post(1);
+        ss.wait(1);
+        launch_als_reduce(N, R, 0, T, A1, Mb, (int)rp, q);        // sum_i T[(i, j)] A1[i]
+        ss.done(1);
+        times(U1, A1, T, q);
+        normal(A1, A3);
+        ss.join(1);
+        solve(A2);
+        ss.post(2);
+        ss.wait(2);
+        launch_als_reduce(N, R, 0, T, A2, Mb, (int)rp, q);        // sum_j T[(j, k)] A2[j]
+        ss.done(2);
+        normal(A1, A2);
+        ss.join(2);
+        solve(A3);
+        ss.post(0);
     }
-    hipError_t e = hipStreamEndCapture(cs, &graph);
-    if (e == hipSuccess && !cap_ok) e = hipErrorInvalidValue;
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess) e = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-    for (int sw = 0; sw < sweeps && e == hipSuccess; ++sw) e = hipGraphLaunch(gexec, cs);
-    if (e == hipSuccess) e = hipStreamSynchronize(cs);
-    int hinfo = 0;
-    if (e == hipSuccess) e = hipMemcpy(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(ROM_E_DEVICE, "CP-ALS failed: %s", hipGetErrorString(e));
-    if (hinfo) return fail(ROM_E_INVALID, "CP-ALS normal equations not positive definite (rank-deficient factors)");
-    return ROM_OK;
+    return als_finish(ss, info, "CP-ALS");
 }
 
 extern "C" rom_status rom_cp_als_skew(int32_t N, int32_t P, const double* C, double* A11, double* A12, double* B1,
@@ -1106,105 +1136,72 @@ extern "C" rom_status rom_cp_als_skew(int32_t N, int32_t P, const double* C, dou
     if (!C || !A11 || !A12 || !B1) return fail(ROM_E_INVALID, "a tensor or factor pointer is NULL");
     if (sweeps == 0) return ROM_OK;
     hipStream_t s = (hipStream_t)stream;
+    if (als_capturing(s)) return fail(ROM_E_DEVICE, "ALS-skew cannot run on a stream under capture");
     const int R = 2 * P;
     const size_t n = (size_t)N, r = (size_t)R, rp = (r + 7) / 8 * 8, p = (size_t)P, pp = (p + 7) / 8 * 8;
-    const size_t npad = (n + 15) / 16 * 16, np = (n + 7) / 8 * 8, n2pad = (n * n + 15) / 16 * 16;
-    // factors A1, A2, A3 [N][R]; the untied normal system V, L, X [R][R], Vinv [R][Rp],
-    // right-hand side Mb [Npad][Rp], solution Yb [Npad][R]; the tied system Vt, Lt, Xt
-    // [P][P], Vtinv [P][Pp], Mt [Npad][Pp], Yt [Npad][P]; the unfolding U0 [N^2 padded][Np],
-    // a transposed factor Ft [R][Np] and the product T [N^2 padded][R]
-    constexpr int kBufs = 17;
-    const size_t sizes[kBufs] = {n * r, n * r, n * r, r * r, r * r, r * r, r * rp, npad * rp, npad * r,
-                                 p * p, p * p, p * p, p * pp, npad * pp, npad * p, n2pad * np, r * np + kProductSlack};
-    const size_t tsize = n2pad * r;
-    double* buf[kBufs + 1] = {};
-    int* info = nullptr;
-    struct Guard {
-        double** b;
-        int** info;
-        ~Guard() {
-            for (int q = 0; q <= kBufs; ++q)
-                if (b[q]) hipFree(b[q]);
-            if (*info) hipFree(*info);
-        }
-    } guard{buf, &info};
-    for (int q = 0; q <= kBufs; ++q) {
-        const hipError_t e = hipMalloc((void**)&buf[q], sizeof(double) * (q < kBufs ? sizes[q] : tsize));
-        if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? ROM_E_NOMEM : ROM_E_DEVICE, "ALS-skew workspace: %s",
-                                         hipGetErrorString(e));
-    }
-    if (hipMalloc((void**)&info, sizeof(int)) != hipSuccess) return fail(ROM_E_NOMEM, "ALS-skew workspace");
-    double *A1 = buf[0], *A2 = buf[1], *A3 = buf[2], *V = buf[3], *L = buf[4], *X = buf[5], *Vinv = buf[6];
-    double *Mb = buf[7], *Yb = buf[8], *Vt = buf[9], *Lt = buf[10], *Xt = buf[11], *Vtinv = buf[12], *Mt = buf[13];
-    double *Yt = buf[14], *U0 = buf[15], *Ft = buf[16], *T = buf[17];
-    if (hipMemsetAsync(Vinv, 0, sizeof(double) * sizes[6], s) != hipSuccess ||
-        hipMemsetAsync(Mb, 0, sizeof(double) * sizes[7], s) != hipSuccess ||
-        hipMemsetAsync(Vtinv, 0, sizeof(double) * sizes[12], s) != hipSuccess ||
-        hipMemsetAsync(Mt, 0, sizeof(double) * sizes[13], s) != hipSuccess ||
-        hipMemsetAsync(U0, 0, sizeof(double) * sizes[15], s) != hipSuccess ||
-        hipMemsetAsync(Ft, 0, sizeof(double) * sizes[16], s) != hipSuccess ||
-        hipMemsetAsync(info, 0, sizeof(int), s) != hipSuccess)
-        return fail(ROM_E_DEVICE, "ALS-skew workspace clear failed");
-    launch_als_unfold(N, (int)np, 0, C, U0, s);     // rows (i, j), columns k
+    const size_t npad = (n + 15) / 16 * 16, np = (n + 7) / 8 * 8;
+    AlsProduct times(N, R, (int)np);
+    // the untied normal system's inverse Vinv [R][Rp] and right-hand side Mb [Npad][Rp] and the
+    // tied one's Vtinv [P][Pp] and Mt [Npad][Pp], with zero padding; factors A1, A2, A3
+    // [N][R]; V, L, X [R][R], solution Yb [Npad][R]; Vt, Lt, Xt [P][P], Yt [Npad][P]; the
+    // unfolding U0 of C and the product T [N^2 padded][R]
+    const bool in_place = times.in_place(C);
+    AlsSlab ws;
+    const size_t o_vinv = ws.add(r * rp), o_mb = ws.add(npad * rp), o_vtinv = ws.add(p * pp), o_mt = ws.add(npad * pp);
+    const size_t o_info = ws.add(1), cleared = ws.words;
+    const size_t o_a1 = ws.add(n * r), o_a2 = ws.add(n * r), o_a3 = ws.add(n * r), o_v = ws.add(r * r);
+    const size_t o_l = ws.add(r * r), o_x = ws.add(r * r), o_yb = ws.add(npad * r), o_vt = ws.add(p * p);
+    const size_t o_lt = ws.add(p * p), o_xt = ws.add(p * p), o_yt = ws.add(npad * p), o_ft = ws.add(times.transposed());
+    const size_t o_piv = ws.add(kGjPivots), o_u0 = ws.add(in_place ? 0 : times.unfolded()), o_t = ws.add((size_t)times.n2pad * r);
+    const hipError_t me = ws.alloc();
+    if (me != hipSuccess)
+        return fail(me == hipErrorOutOfMemory ? ROM_E_NOMEM : ROM_E_DEVICE, "ALS-skew workspace: %s",
+                    hipGetErrorString(me));
+    double *A1 = ws.at(o_a1), *A2 = ws.at(o_a2), *A3 = ws.at(o_a3), *V = ws.at(o_v), *L = ws.at(o_l), *X = ws.at(o_x);
+    double *Vinv = ws.at(o_vinv), *Mb = ws.at(o_mb), *Yb = ws.at(o_yb), *Vt = ws.at(o_vt), *Lt = ws.at(o_lt);
+    double *Xt = ws.at(o_xt), *Vtinv = ws.at(o_vtinv), *Mt = ws.at(o_mt), *Yt = ws.at(o_yt), *T = ws.at(o_t);
+    const double* U0 = in_place ? C : ws.at(o_u0);        // rows (i, j), columns k
+    double* piv = ws.at(o_piv);
+    int* info = reinterpret_cast<int*>(ws.at(o_info));
+    times.Ft = ws.at(o_ft);
+    if (hipMemsetAsync(ws.base, 0, sizeof(double) * cleared, s) != hipSuccess ||
+        (!in_place && times.unfold(0, C, ws.at(o_u0), s) != hipSuccess))
+        return fail(ROM_E_DEVICE, "ALS-skew workspace setup failed");
     launch_skew_assemble(N, P, A11, A12, B1, A1, A2, A3, s);
-    SweepStreams ss;
-    if (!ss.init(s)) return fail(ROM_E_DEVICE, "ALS-skew stream setup failed");
-    hipStream_t cs = ss.cs;
-    hipGraph_t& graph = ss.graph;
-    hipGraphExec_t& gexec = ss.gexec;
-    const GemmPlan plt = gemm_plan(R, (int)n2pad, 0), plr = gemm_plan(R, (int)npad, 0),
-                   plp = gemm_plan(P, (int)npad, 0);
-    const AlsProductPlan prod = als_product_plan((int)np, kProductLds);
-    s = cs;
-    if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess)
-        return fail(ROM_E_DEVICE, "ALS-skew graph capture failed to start");
-    // T[(i, j)][m] = sum_k C[i][j][k] A3[k][m]: the unfolding times the third factor
-    auto tensor_times_a3 = [&]() {
-        launch_als_transpose(N, R, (int)np, A3, Ft, s);
-        if (prod.ok) launch_als_product(prod, R, (int)np, (long long)n2pad, U0, Ft, T, s);
-        else launch_gemm_f64(plt, Ft, (long long)np, U0, (long long)np, T, R, (int)np, (int)n2pad, s);
-    };
+    SweepStreams ss(s);
+    hipStream_t q = ss.rhs;
+    const GemmPlan plr = gemm_plan(R, (int)npad, 0), plp = gemm_plan(P, (int)npad, 0);
     // one sweep: the tied second factor (least squares with A2 = B1 [I I]), then the
     // subiterations of the first factor with A3 fixed, each followed by the momentum
-    // update and A3 = [A12 -A11]
-    bool cap_ok = true;
-    launch_gram_hadamard(N, R, A1, A3, V, s);
-    // the tied system's inverse on the side stream, beside the product and the reduction
-    const int qt = SweepStreams::kPairs - 1;
-    launch_skew_tie(N, P, V, Vt, nullptr, (int)rp, Mt, (int)pp, s);   // Vt
-    cap_ok = ss.fork(qt) && cap_ok;
-    spd_inverse_gj(P, (int)pp, Vt, Lt, Xt, Vtinv, info, ss.side);
-    cap_ok = ss.join_mark(qt) && cap_ok;
-    tensor_times_a3();
-    launch_als_reduce(N, R, 0, T, A1, Mb, (int)rp, s);                 // sum_i T[(i, j)] A1[i]
-    launch_skew_tie(N, P, nullptr, Vt, Mb, (int)rp, Mt, (int)pp, s);  // Mt
-    cap_ok = ss.join(qt) && cap_ok;
-    launch_gemm_f64(plp, Vtinv, (long long)pp, Mt, (long long)pp, Yt, P, (int)pp, (int)npad, s);
-    launch_skew_set_b(N, P, Yt, P, B1, A2, s);
-    for (int it = 0; it < subiters; ++it) {
-        launch_gram_hadamard(N, R, A2, A3, V, s);
-        // the inverse on the side stream, beside the right-hand side
-        const int q = it % (SweepStreams::kPairs - 1);
-        cap_ok = ss.fork(q) && cap_ok;
-        spd_inverse_gj(R, (int)rp, V, L, X, Vinv, info, ss.side);
-        cap_ok = ss.join_mark(q) && cap_ok;
-        if (it > 0) tensor_times_a3();                                 // A3 moved with A1
-        launch_als_reduce(N, R, 1, T, A2, Mb, (int)rp, s);             // sum_j T[(i, j)] A2[j]
-        cap_ok = ss.join(q) && cap_ok;
-        launch_gemm_f64(plr, Vinv, (long long)rp, Mb, (long long)rp, Yb, R, (int)rp, (int)npad, s);
-        launch_skew_momentum(N, P, momentum, Yb, R, A1, A3, A11, A12, s);
+    // update and A3 = [A12 -A11]; the right-hand sides run beside the inverses
+    ss.post(0);
+    for (int sw = 0; sw < sweeps && ss.ok; ++sw) {
+        ss.wait(0);                                                        // A1, A3
+        times(U0, A3, T, q);                                               // sum_k C[i][j][k] A3[k]
+        launch_als_reduce(N, R, 0, T, A1, Mb, (int)rp, q);                 // sum_i T[(i, j)] A1[i]
+        launch_skew_tie(N, P, nullptr, Vt, Mb, (int)rp, Mt, (int)pp, q);   // Mt
+        ss.done(0);
+        launch_gram_hadamard(N, R, A1, A3, V, s);
+        launch_skew_tie(N, P, V, Vt, nullptr, (int)rp, Mt, (int)pp, s);    // Vt
+        spd_inverse_gj(P, (int)pp, Vt, Lt, Xt, piv, Vtinv, info, s);
+        ss.join(0);
+        launch_gemm_f64(plp, Vtinv, (long long)pp, Mt, (long long)pp, Yt, P, (int)pp, (int)npad, s);
+        launch_skew_set_b(N, P, Yt, P, B1, A2, s);
+        ss.post(0);
+        for (int it = 0; it < subiters; ++it) {
+            ss.wait(0);                                                    // A2, or A1 and A3
+            if (it > 0) times(U0, A3, T, q);                               // A3 moved with A1
+            launch_als_reduce(N, R, 1, T, A2, Mb, (int)rp, q);             // sum_j T[(i, j)] A2[j]
+            ss.done(1);
+            launch_gram_hadamard(N, R, A2, A3, V, s);
+            spd_inverse_gj(R, (int)rp, V, L, X, piv, Vinv, info, s);
+            ss.join(1);
+            launch_gemm_f64(plr, Vinv, (long long)rp, Mb, (long long)rp, Yb, R, (int)rp, (int)npad, s);
+            launch_skew_momentum(N, P, momentum, Yb, R, A1, A3, A11, A12, s);
+            ss.post(0);
+        }
     }
-    hipError_t e = hipStreamEndCapture(cs, &graph);
-    if (e == hipSuccess && !cap_ok) e = hipErrorInvalidValue;
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess) e = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-    for (int sw = 0; sw < sweeps && e == hipSuccess; ++sw) e = hipGraphLaunch(gexec, cs);
-    if (e == hipSuccess) e = hipStreamSynchronize(cs);
-    int hinfo = 0;
-    if (e == hipSuccess) e = hipMemcpy(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(ROM_E_DEVICE, "ALS-skew failed: %s", hipGetErrorString(e));
-    if (hinfo) return fail(ROM_E_INVALID, "ALS-skew normal equations not positive definite (rank-deficient factors)");
-    return ROM_OK;
+    return als_finish(ss, info, "ALS-skew");
 }
 
 extern "C" rom_status rom_create_full(const rom_desc* d, const rom_full_terms* f, rom_ctx* out) {
