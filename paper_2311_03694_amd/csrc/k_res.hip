@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kNT) void k_cp_resident(ResJob jb) {
                     st_msg_f64(jb.xmsg + 2 * i, tx, rhs);
                 } else {
                     const double un = rhs * hd[lg][wv];
-                    write_level(a, n + 1, 0, i, un);
+                    write_level<true>(a, n + 1, 0, i, un);
                     e = un * un;
                     st_msg_f64(jb.xmsg + 2 * i, tx, un);
                 }
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kNT) void k_cp_resident(ResJob jb) {
                 }
                 s = wave_sum(s);
                 if (lane == 0) {
-                    write_level(a, n + 1, 0, i, s);
+                    write_level<true>(a, n + 1, 0, i, s);
                     e = s * s;
                 }
             }

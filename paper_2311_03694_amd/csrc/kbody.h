@@ -476,7 +476,7 @@ __device__ __forceinline__ void cp_scatter1_body(const Scat1Job& jb, double* __r
             const double rhs = bdf_rhs_hist<FULL>(a, n, c, k, 0, i, (double)z, hist, zf);
             if constexpr (MODE == 1) {
                 const double un = rhs * hd;
-                write_level(a, n + 1, 0, i, un);
+                write_level<true>(a, n + 1, 0, i, un);
                 e = un * un;
             } else {
                 a.rhs[i] = rhs;
@@ -638,7 +638,7 @@ __device__ __forceinline__ void bdf_partials1_body(const StepArgs& a, long long 
         const double rhs = bdf_rhs_hist(a, n, c, k, 0, i, y, hist);
         if constexpr (DIAG) {
             const double un = rhs * hd;
-            write_level(a, n + 1, 0, i, un);
+            write_level<true>(a, n + 1, 0, i, un);
             e = un * un;
         } else {
             a.rhs[i] = rhs;
