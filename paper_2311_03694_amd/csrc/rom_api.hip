@@ -999,10 +999,13 @@ struct AlsProduct {
 // right-hand sides.  Both are made by the call, one after the other, and so on hardware queues
 // of their own; a single one beside the caller's can share that one's queue, and then nothing
 // overlaps (N = 200, R = 400, ten sweeps: 8.6 ms instead of 6.0 after one more stream had been
-// made).  post(q) / wait(q): rhs waits for the chain; done(q) / join(q): the chain waits for
-// rhs.  The sweeps are launched directly: a graph of a sweep submits a whole branch before the
-// next one (a product was submitted 80 us after it could have run, behind the panels of the
-// inverse beside it), and its capture, instantiation and release cost 0.4 ms a call.
+// made).  All work on the workspace is theirs, the set-up too: the runtime keeps memory that the
+// last commands of a living stream refer to, also past its hipFree (with the set-up on the
+// caller's stream every call left its workspace behind).  post(q) / wait(q): rhs waits for the
+// chain; done(q) / join(q): the chain waits for rhs.  The sweeps are launched directly: a graph
+// of a sweep submits a whole branch before the next one (a product was submitted 80 us after it
+// could have run, behind the panels of the inverse beside it), and its capture, instantiation
+// and release cost 0.4 ms a call.
 struct SweepStreams {
     static constexpr int kPairs = 3;
     hipStream_t chain = nullptr, rhs = nullptr;
@@ -1083,6 +1086,9 @@ extern "C" rom_status rom_cp_als(int32_t N, int32_t R, const double* C, double* 
     double* piv = ws.at(o_piv);
     int* info = reinterpret_cast<int*>(ws.at(o_info));
     times.Ft = ws.at(o_ft);
+    SweepStreams ss(s);
+    if (!ss.ok) return fail(ROM_E_DEVICE, "CP-ALS stream setup failed");
+    s = ss.chain;
     if (hipMemsetAsync(ws.base, 0, sizeof(double) * cleared, s) != hipSuccess ||
         (!in_place && times.unfold(0, C, ws.at(o_u0), s) != hipSuccess) || times.unfold(1, C, U1, s) != hipSuccess)
         return fail(ROM_E_DEVICE, "CP-ALS workspace setup failed");
@@ -1091,9 +1097,6 @@ extern "C" rom_status rom_cp_als(int32_t N, int32_t R, const double* C, double* 
     // The right-hand sides run beside them: T = C x_3 A3 (rows (i, j)) serves the first two;
     // the third takes T = C x_1 A1 (rows (j, k)), which needs the first factor only, so that
     // it can run beside both inverses that follow that factor's update.
-    SweepStreams ss(s);
-    if (!ss.ok) return fail(ROM_E_DEVICE, "CP-ALS stream setup failed");
-    s = ss.chain;
     hipStream_t q = ss.rhs;
     const GemmPlan pl = gemm_plan(R, (int)npad, 0);
     auto normal = [&](const double* Fa, const double* Fb) {
@@ -1170,13 +1173,13 @@ extern "C" rom_status rom_cp_als_skew(int32_t N, int32_t P, const double* C, dou
     double* piv = ws.at(o_piv);
     int* info = reinterpret_cast<int*>(ws.at(o_info));
     times.Ft = ws.at(o_ft);
+    SweepStreams ss(s);
+    if (!ss.ok) return fail(ROM_E_DEVICE, "ALS-skew stream setup failed");
+    s = ss.chain;
     if (hipMemsetAsync(ws.base, 0, sizeof(double) * cleared, s) != hipSuccess ||
         (!in_place && times.unfold(0, C, ws.at(o_u0), s) != hipSuccess))
         return fail(ROM_E_DEVICE, "ALS-skew workspace setup failed");
     launch_skew_assemble(N, P, A11, A12, B1, A1, A2, A3, s);
-    SweepStreams ss(s);
-    if (!ss.ok) return fail(ROM_E_DEVICE, "ALS-skew stream setup failed");
-    s = ss.chain;
     hipStream_t q = ss.rhs;
     const GemmPlan plr = gemm_plan(R, (int)npad, 0), plp = gemm_plan(P, (int)npad, 0);
     // one sweep: the tied second factor (least squares with A2 = B1 [I I]), then the
