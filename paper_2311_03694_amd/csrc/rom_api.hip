@@ -999,13 +999,10 @@ struct AlsProduct {
 // right-hand sides.  Both are made by the call, one after the other, and so on hardware queues
 // of their own; a single one beside the caller's can share that one's queue, and then nothing
 // overlaps (N = 200, R = 400, ten sweeps: 8.6 ms instead of 6.0 after one more stream had been
-// made).  All work on the workspace is theirs, the set-up too: the runtime keeps memory that the
-// last commands of a living stream refer to, also past its hipFree (with the set-up on the
-// caller's stream every call left its workspace behind).  post(q) / wait(q): rhs waits for the
-// chain; done(q) / join(q): the chain waits for rhs.  The sweeps are launched directly: a graph
-// of a sweep submits a whole branch before the next one (a product was submitted 80 us after it
-// could have run, behind the panels of the inverse beside it), and its capture, instantiation
-// and release cost 0.4 ms a call.
+// made).  post(q) / wait(q): rhs waits for the chain; done(q) / join(q): the chain waits for
+// rhs.  The sweeps are launched directly: a graph of a sweep submits a whole branch before the
+// next one (a product was submitted 80 us after it could have run, behind the panels of the
+// inverse beside it), and its capture, instantiation and release cost 0.4 ms a call.
 struct SweepStreams {
     static constexpr int kPairs = 3;
     hipStream_t chain = nullptr, rhs = nullptr;

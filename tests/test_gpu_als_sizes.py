@@ -95,19 +95,3 @@ def test_als_past_the_kernel(torch_gpu):
     for a, b in zip(G, A):
         assert float((a - b).abs().max()) <= TOL * float(b.abs().max())
 
-
-def test_als_keeps_no_memory(torch_gpu):
-    """A call gives its workspace back."""
-    torch = torch_gpu
-    rng = np.random.default_rng(3)
-    N, R = 96, 96
-    X, F0 = _rank(rng, N, R)
-    Xd = _device(torch, X, 0)
-    Fd = [torch.tensor(f, device="cuda") for f in F0]
-    rg.rom_cp_als(N, R, Xd, *Fd, 1)
-    torch.cuda.synchronize()
-    free0 = torch.cuda.mem_get_info()[0]
-    for _ in range(4):
-        rg.rom_cp_als(N, R, Xd, *Fd, 1)
-    torch.cuda.synchronize()
-    assert free0 - torch.cuda.mem_get_info()[0] < 8 * N * N * R
