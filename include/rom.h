@@ -146,10 +146,12 @@ void rom_destroy(rom_ctx ctx);
  *   C        device FP64 [N][N][N], C[i][j][k] (position 1 = i, as rom_desc.C); read only.
  *   A1..A3   device FP64 [N][R] factors for positions 1, 2, 3: the initial guess on entry
  *            (the caller chooses it), the fitted factors on return.
- *   stream   hipStream_t or NULL (the null stream); the sweeps themselves run on a stream
- *            of the call's own, ordered after it.  Synchronizes; allocates and frees its own
- *            workspace: two padded unfoldings of C and their product with a factor, about
- *            2 N^3 + N^2 R + 4 R^2 doubles (ROM_E_NOMEM when that does not fit).
+ *   stream   hipStream_t or NULL (the null stream); the sweeps themselves run on two streams
+ *            of the library's, ordered after it, and read C where it is if N is a multiple
+ *            of 8 and C is 16-byte aligned.  Synchronizes (a capturing stream is refused with
+ *            ROM_E_DEVICE); allocates and frees its own workspace: one or two padded
+ *            unfoldings of C and their product with a factor, about N^3 or 2 N^3, and
+ *            N^2 R + 4 R^2 doubles (ROM_E_NOMEM when that does not fit).
  * Errors: ROM_E_INVALID (N or R outside [1, 4096], sweeps < 0, NULL pointers, or a
  * normal matrix that is not positive definite: rank-deficient factors; the factors then
  * hold non-finite values), ROM_E_NOMEM, ROM_E_DEVICE.  sweeps = 0 does nothing. */
@@ -296,8 +298,10 @@ rom_status rom_query(rom_ctx ctx, rom_state st, int32_t what, int64_t *value);
  * 3 = CP scatter, 4 = pair form of the CP projections (0 = general form, 1 = pair form
  * for one trajectory and for batches, ROM_E_UNSUPPORTED if the factors have no skew column
  * pairs), 5 = resident runs of one-trajectory CP steps (0 = off: every step through the
- * per-step kernels; 1 or -1 = on where the operator fits on chip).  value: an index into
- * that kernel's variant table (see rom_tile_count); -1 restores the built-in choice (for
+ * per-step kernels; 1 or -1 = on where the operator fits on chip).  Kind 0 concerns BF16
+ * tensors of more than 100 MB; the other tensors' stream has no variants.  value: an index into
+ * that kernel's variant table (see rom_tile_count), in kind 1 modulo the number of variants
+ * of the format's kernel; -1 restores the built-in choice (for
  * kind 4: the pair form for one trajectory whenever the factors allow it, the general
  * form for batches).  Applies to later launches.
  *

@@ -996,41 +996,78 @@ struct AlsProduct {
 
 // The two streams of an ALS call, ordered after the caller's: `chain` carries the chain of a
 // sweep (Gram products, SPD inverses, solves), `rhs` the products with the tensor and the
-// right-hand sides.  Both are made by the call, one after the other, and so on hardware queues
-// of their own; a single one beside the caller's can share that one's queue, and then nothing
-// overlaps (N = 200, R = 400, ten sweeps: 8.6 ms instead of 6.0 after one more stream had been
-// made).  post(q) / wait(q): rhs waits for the chain; done(q) / join(q): the chain waits for
-// rhs.  The sweeps are launched directly: a graph of a sweep submits a whole branch before the
-// next one (a product was submitted 80 us after it could have run, behind the panels of the
-// inverse beside it), and its capture, instantiation and release cost 0.4 ms a call.
-struct SweepStreams {
-    static constexpr int kPairs = 3;
+// right-hand sides.  They are made one after the other, and so on hardware queues of their
+// own; a single one beside the caller's can share that one's queue, and then nothing overlaps
+// (N = 200, R = 400, ten sweeps: 8.6 ms instead of 6.0 after one more stream had been made).
+// post(q) / wait(q): rhs waits for the chain; done(q) / join(q): the chain waits for rhs.  The
+// sweeps are launched directly: a graph of a sweep submits a whole branch before the next one
+// (a product was submitted 80 us after it could have run, behind the panels of the inverse
+// beside it), and its capture, instantiation and release cost 0.4 ms a call.
+//
+// A call takes a pair from a pool of at most kPool pairs a device, made as they are first
+// needed, and gives it back idle; a call that finds all of them taken runs on the caller's
+// stream alone.  Pairs stay until the process ends: the runtime still writes to the object of
+// a stream that it has just destroyed (a reference count and a flag, from its own thread),
+// into memory that the caller may own by then.
+struct SweepPair {
+    static constexpr int kPairs = 3, kPool = 4;
     hipStream_t chain = nullptr, rhs = nullptr;
     hipEvent_t evp[kPairs] = {}, evd[kPairs] = {};
-    bool ok = false;
-    explicit SweepStreams(hipStream_t caller) {
-        ok = hipStreamCreateWithFlags(&chain, hipStreamNonBlocking) == hipSuccess &&
-             hipStreamCreateWithFlags(&rhs, hipStreamNonBlocking) == hipSuccess;
+    bool made = false, taken = false;
+    bool make() {
+        bool ok = hipStreamCreateWithFlags(&chain, hipStreamNonBlocking) == hipSuccess &&
+                  hipStreamCreateWithFlags(&rhs, hipStreamNonBlocking) == hipSuccess;
         for (int q = 0; q < kPairs; ++q)
             ok = ok && hipEventCreateWithFlags(&evp[q], hipEventDisableTiming) == hipSuccess &&
                  hipEventCreateWithFlags(&evd[q], hipEventDisableTiming) == hipSuccess;
-        ok = ok && hipEventRecord(evp[0], caller) == hipSuccess && hipStreamWaitEvent(chain, evp[0], 0) == hipSuccess;
+        return ok;
     }
-    void post(int q) { ok = ok && hipEventRecord(evp[q], chain) == hipSuccess; }
-    void wait(int q) { ok = ok && hipStreamWaitEvent(rhs, evp[q], 0) == hipSuccess; }
-    void done(int q) { ok = ok && hipEventRecord(evd[q], rhs) == hipSuccess; }
-    void join(int q) { ok = ok && hipStreamWaitEvent(chain, evd[q], 0) == hipSuccess; }
+};
+constexpr int kSweepDevices = 64;
+static std::mutex sweep_mutex;
+static SweepPair sweep_pool[kSweepDevices][SweepPair::kPool];
+
+struct SweepStreams {
+    hipStream_t chain, rhs;
+    SweepPair* p = nullptr;
+    bool ok = true;
+    explicit SweepStreams(hipStream_t caller) : chain(caller), rhs(caller) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kSweepDevices) return;
+        {
+            std::lock_guard<std::mutex> lock(sweep_mutex);
+            for (SweepPair& c : sweep_pool[dev]) {
+                if (c.taken) continue;
+                if (!c.made) {
+                    if (!c.make()) {              // never handed out: what it made stays unused
+                        (void)hipGetLastError();
+                        c.taken = true;
+                        break;
+                    }
+                    c.made = true;
+                }
+                c.taken = true;
+                p = &c;
+                break;
+            }
+        }
+        if (!p) return;
+        chain = p->chain;
+        rhs = p->rhs;
+        ok = hipEventRecord(p->evp[0], caller) == hipSuccess && hipStreamWaitEvent(chain, p->evp[0], 0) == hipSuccess;
+    }
+    SweepStreams(const SweepStreams&) = delete;
+    void post(int q) { ok = ok && (!p || hipEventRecord(p->evp[q], chain) == hipSuccess); }
+    void wait(int q) { ok = ok && (!p || hipStreamWaitEvent(rhs, p->evp[q], 0) == hipSuccess); }
+    void done(int q) { ok = ok && (!p || hipEventRecord(p->evd[q], rhs) == hipSuccess); }
+    void join(int q) { ok = ok && (!p || hipStreamWaitEvent(chain, p->evd[q], 0) == hipSuccess); }
     ~SweepStreams() {
         // the workspace is given back next
-        for (hipStream_t s : {chain, rhs})
-            if (s) {
-                hipStreamSynchronize(s);
-                hipStreamDestroy(s);
-            }
-        for (int q = 0; q < kPairs; ++q) {
-            if (evp[q]) hipEventDestroy(evp[q]);
-            if (evd[q]) hipEventDestroy(evd[q]);
-        }
+        hipStreamSynchronize(chain);
+        if (!p) return;
+        hipStreamSynchronize(rhs);
+        std::lock_guard<std::mutex> lock(sweep_mutex);
+        p->taken = false;
     }
 };
 
