@@ -105,7 +105,6 @@ CSRC = os.path.join(ROOT, "paper_2311_03694_amd", "csrc")
 # the sources each profiled kernel is compiled from (its counter record is valid only
 # while their combined hash is unchanged)
 KERNEL_SOURCES = {
-    "dense_gemv": ["k_dense1.hip", "kdot.h", "kcommon.h", "rom_dev.h"],
     "fold_gemv": ["k_fold.hip", "kfold.h", "kdot.h", "kcommon.h", "rom_dev.h"],
     "kr": ["k_kr.hip", "kmfma.h", "kcommon.h", "rom_dev.h"],
 }

@@ -3,6 +3,8 @@ panels: every number of column tiles a block can hold, ranks that fill the last 
 group or do not, tensors read in place and unfolded (ragged N, an address that is not a
 multiple of 16 bytes), inverses of one to five panels, and the product past the kernel's
 range (rows of more than 1000 columns)."""
+import concurrent.futures as cf
+
 import numpy as np
 import pytest
 
@@ -95,3 +97,26 @@ def test_als_past_the_kernel(torch_gpu):
     for a, b in zip(G, A):
         assert float((a - b).abs().max()) <= TOL * float(b.abs().max())
 
+
+
+def test_als_from_several_threads(torch_gpu):
+    """Eight calls at once, more than there are stream pairs: those beyond run on the caller's
+    stream alone, with the same results to the bit."""
+    torch = torch_gpu
+    rng = np.random.default_rng(9)
+    N, R = 48, 70
+    X, F0 = _rank(rng, N, R)
+    Xd = _device(torch, X, 0)
+
+    def fit(stream):
+        G = [torch.tensor(f, device="cuda") for f in F0]
+        torch.cuda.synchronize()
+        rg.rom_cp_als(N, R, Xd, *G, 4, stream=stream)
+        return G
+
+    ref = fit(None)
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        out = list(ex.map(fit, [torch.cuda.Stream() for _ in range(8)]))
+    torch.cuda.synchronize()
+    for G in out:
+        assert all(torch.equal(a, b) for a, b in zip(G, ref))
