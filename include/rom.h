@@ -179,7 +179,8 @@ rom_status rom_cp_als_skew(int32_t N, int32_t P, const double *C, double *A11, d
                            int32_t sweeps, int32_t subiters, double momentum, void *stream);
 
 /* y = C(u)u for `batch` coefficient vectors (Sec. 2.2, eq. Cu; CP form: eq. tc_ap).
- * u_dev, y_dev: device FP64 [batch][N], caller-owned; 1 <= batch <= max_batch.
+ * u_dev, y_dev: device FP64 [batch][N], caller-owned; 1 <= batch <= max_batch.  They may be
+ * the same array, or overlap: all of u is read before y is written.
  * The contraction runs in the context's dtype; y is returned in FP64.  Asynchronous. */
 rom_status rom_nonlinear(rom_ctx ctx, int32_t batch, const double *u_dev, double *y_dev);
 

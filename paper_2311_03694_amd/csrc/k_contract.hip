@@ -43,7 +43,8 @@ __global__ __launch_bounds__(256) void k_cp_scatter1(Scat1Job jb, double* y_out)
 // by latency: N = 37, R = 40 in FP64 took 3.7 us on the device against 5.3, and 4.8 us per
 // call against 8.1.  A pair costs a wavefront about 0.5 us of reductions, so it is taken up to
 // kSmallMost pairs (R = 80 in pair form) and kSmallBytes of projection rows: N = R = 64 in
-// FP64 4.8 against 5.3 us, N = 50, R = 100 6.5 against 5.3.
+// FP64 4.8 against 5.3 us, N = 50, R = 100 6.5 against 5.3.  Blocks write y while others read u,
+// so the two arrays must not share memory (the two launches serve those that do).
 constexpr size_t kSmallBytes = 48 << 10;
 constexpr int kSmallWaves = 16, kSmallMost = 40;
 template <int DT> constexpr int kSmallPairs = DT == DT_BF16X3 ? 2 : 4;

@@ -1385,6 +1385,12 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
     return ROM_OK;
 }
 
+// Whether n doubles at a and n doubles at b share memory.
+static bool overlap(const double* a, const double* b, size_t n) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b, len = n * sizeof(double);
+    return x < y + len && y < x + len;
+}
+
 // Shared body of rom_nonlinear and rom_nonlinear_timed: operand copies (batches), the
 // contraction kernels, and the sum of the partial results into y.  With kernel_us the
 // contraction is captured `reps` times into a HIP graph, launched once to warm up and
@@ -1429,6 +1435,9 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
         a.uj = ws + p.usc_off;
         launch_prep_ucv(a, u_dev, c->stream);
     }
+    // the single launch of a small CP operator has blocks writing their rows of y while others
+    // still read u: in place (or with arrays that overlap) the two launches run instead
+    const bool apart = !overlap(u_dev, y_dev, (size_t)c->N);
     auto contract = [&]() {
         if (batch == 1) {
             if (c->dense) {
@@ -1441,8 +1450,8 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
                 launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, u_dev, nullptr, 0,
                                 ws + p.svdw_off, c->stream);
                 launch_fold_gemv(c->dtype, fold_job(c, ws + p.svdw_off, u_dev, nullptr, 0, ws + p.part_off), c->stream);
-            } else if (!launch_cp_eval_small(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->Af, c->Af_lo, c->N, c->Np,
-                                             c->Rp, skew_of(c), u_dev, y_dev, c->stream)) {
+            } else if (!apart || !launch_cp_eval_small(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->Af, c->Af_lo, c->N,
+                                                       c->Np, c->Rp, skew_of(c), u_dev, y_dev, c->stream)) {
                 launch_cp_proj1(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->N, c->Np, c->Rp, skew_of(c), u_dev,
                                 nullptr, 0, ws + p.part_off, c->stream);
                 launch_cp_scatter1(c->dtype, c->Af, c->Af_lo, c->N, c->Rp, ws + p.part_off, y_dev, nullptr, 0,

@@ -233,8 +233,9 @@ struct SkewPairs { int layout, P, R; };   // layout 0: general factors
 int launch_cp_proj1(int dt, const void* BCt, const void* BCt_lo, const void* lam, int N, int Np, int Rp,
                     SkewPairs sk, const double* u_base, const long long* stepp, long long slot_stride,
                     void* w, hipStream_t s);
-// Projections and scatter of a small operator in one launch; false (nothing launched) when the
-// operator is not small enough.
+// Projections and scatter of a small operator in one launch, u and y apart (no block waits for
+// another before it writes its rows of y); false (nothing launched) when the operator is not
+// small enough.
 bool launch_cp_eval_small(int dt, const void* BCt, const void* BCt_lo, const void* lam, const void* Af, const void* Af_lo,
                           int N, int Np, int Rp, SkewPairs sk, const double* u, double* y, hipStream_t s);
 int proj1_blocks(int Rp, SkewPairs sk);
