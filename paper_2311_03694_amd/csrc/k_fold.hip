@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void k_fold_mm(FoldArgs p) {
                     if constexpr (X3) xl[s][t] = ld_plain<16>(p.Xlo + o);
                     else xl[s][t] = u32x4{0u, 0u, 0u, 0u};
                 }
-            __syncthreads();                             // the weights are in LDS
+            lds_loads_done();                            // the weights
 #pragma unroll
             for (int s = 0; s < NS; ++s)
 #pragma unroll

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
     // The copies above must land before any wavefront reads the j-weights; the
     // tensor ring is issued after the barrier, so this wait covers only the small
     // L2-resident loads and the ring's HBM traffic starts right behind it.
-    __syncthreads();
+    lds_loads_done();
 #pragma unroll
     for (int s = 0; s < KW; ++s)
 #pragma unroll
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(512) void k_krs(KrArgs p) {
             const size_t o = (size_t)(b < p.Bpad ? b : p.Bpad - 1) * p.Kx + (k < p.Kx ? k : p.Kx - VEC);
             xh[s][t] = ld_plain<16>(reinterpret_cast<const XT*>(p.X) + o);
         }
-    __syncthreads();                                     // j-weights published
+    lds_loads_done();                                    // j-weights published
 #pragma unroll
     for (int s = 0; s < KC; ++s)
 #pragma unroll

@@ -108,12 +108,10 @@ __device__ bool res_wait(const ResJob& jb, const unsigned long long* src, int ne
     return __syncthreads_or(ok ? 0 : 1) == 0;
 }
 
-// Whole block: copy nrows rows of row_bytes (a multiple of 16) to dst (rows
-// back to back); src(r) is row r's address, or null for a row past the operator (zeros).
 // nrows rows of row_bytes (a multiple of 16) into LDS at dst, a row whose src(r) is null as
 // zeros.  16-byte direct loads from memory into LDS (no registers in between), all of the
 // block's loads in flight at once: a wave's 64 lanes fill 1 KB of consecutive LDS per
-// load.  The caller waits for them (lds_rows_done) before any wave reads the rows.
+// load.  The caller waits for them (lds_loads_done) before any wave reads the rows.
 template <class SrcF>
 __device__ void lds_rows(char* dst, int nrows, size_t row_bytes, SrcF src) {
     const int cpr = (int)(row_bytes / 16), n = nrows * cpr;
@@ -124,12 +122,6 @@ __device__ void lds_rows(char* dst, int nrows, size_t row_bytes, SrcF src) {
         if (s) __builtin_amdgcn_global_load_lds(s + (size_t)c * 16, dst + (size_t)base * 16, 16, 0, 0);
         else if (q < n) *reinterpret_cast<u32x4*>(dst + (size_t)q * 16) = u32x4{0u, 0u, 0u, 0u};
     }
-}
-
-// The direct loads of lds_rows have landed (this wave's), then every wave's (barrier).
-__device__ __forceinline__ void lds_rows_done() {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
 }
 
 // Groups g = b, b + G, ... below n owned by block b.
@@ -206,7 +198,7 @@ __global__ __launch_bounds__(kNT) void k_cp_resident(ResJob jb) {
             });
         }
     }
-    lds_rows_done();
+    lds_loads_done();
 
     const unsigned seq0 = *jb.seq;
     const BdfCoef cf = bdf_coef(3);

@@ -96,6 +96,15 @@ __host__ __device__ __forceinline__ size_t tile_off(int kt, int row, int k) {
     return ((size_t)(row >> 4) * kt + (k / KS) * KS) * 16 + (size_t)((k % KS / VEC * 16 + (row & 15)) * VEC + k % VEC);
 }
 
+// ---------------------------------------------------------------- direct loads into LDS
+
+// The wave's direct loads into LDS have landed, then every wave's (barrier).  A barrier alone
+// does not promise it for loads in flight.
+__device__ __forceinline__ void lds_loads_done() {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------- reductions
 
 // Lane exchange within rows of 16 lanes (DPP row_ror:K, K = 1..15) and lane reads.
