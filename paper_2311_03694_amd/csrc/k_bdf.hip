@@ -86,12 +86,13 @@ __global__ __launch_bounds__(256) void k_sum_partials1(const ACC* __restrict__ p
     if (threadIdx.x < kWave && i < N) y[i] = s;
 }
 
+// add: behind y's own sum of earlier partials.
 template <class ACC>
-__global__ void k_sum_partials(const ACC* __restrict__ part, int nchunk, int B, int N,
+__global__ void k_sum_partials(const ACC* __restrict__ part, int nchunk, int B, int N, int add,
                                double* __restrict__ y, int pbstride) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y;
     if (i >= N) return;
-    double s = 0.0;
+    double s = add ? y[(size_t)b * N + i] : 0.0;
     const size_t cs = (size_t)pbstride * N;
     const ACC* pp = part + (size_t)b * N + i;
     int q = 0;
@@ -152,17 +153,17 @@ void launch_prep_ucv(const StepArgs& a, const double* u_src, hipStream_t s) {
                        s, a, u_src);
 }
 
-void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N,
-                         double* y, hipStream_t s) {
-    if (B == 1) {
-        const dim3 g1(bdf1_blocks(N));
-        if (acc_f64) hipLaunchKernelGGL(k_sum_partials1<double>, g1, dim3(256), 0, s, (const double*)part, nchunk, N, y);
-        else hipLaunchKernelGGL(k_sum_partials1<float>, g1, dim3(256), 0, s, (const float*)part, nchunk, N, y);
-        return;
-    }
+void launch_sum_partials1(int acc_f64, const void* part, int nchunk, int N, double* y, hipStream_t s) {
+    const dim3 g1(bdf1_blocks(N));
+    if (acc_f64) hipLaunchKernelGGL(k_sum_partials1<double>, g1, dim3(256), 0, s, (const double*)part, nchunk, N, y);
+    else hipLaunchKernelGGL(k_sum_partials1<float>, g1, dim3(256), 0, s, (const float*)part, nchunk, N, y);
+}
+
+void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N, int add, double* y,
+                         hipStream_t s) {
     dim3 grid((N + 255) / 256, B);
-    if (acc_f64) hipLaunchKernelGGL(k_sum_partials<double>, grid, dim3(256), 0, s, (const double*)part, nchunk, B, N, y, pb);
-    else hipLaunchKernelGGL(k_sum_partials<float>, grid, dim3(256), 0, s, (const float*)part, nchunk, B, N, y, pb);
+    if (acc_f64) hipLaunchKernelGGL(k_sum_partials<double>, grid, dim3(256), 0, s, (const double*)part, nchunk, B, N, add, y, pb);
+    else hipLaunchKernelGGL(k_sum_partials<float>, grid, dim3(256), 0, s, (const float*)part, nchunk, B, N, add, y, pb);
 }
 
 // ============================================================== Helmholtz setup

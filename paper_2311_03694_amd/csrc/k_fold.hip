@@ -211,7 +211,8 @@ struct FoldArgs {
     void* part;                    // [nsplit][Bpad][N] partial tiles (accumulation type)
     FoldLay l;
     int Kx, Bpad;
-    int njr, jc, ppb, nsplit;      // pieces per chunk, slabs per piece, pieces per block, blocks per tile
+    int njr, jc, ppb;              // pieces per chunk, slabs per piece, pieces per block
+    int sp0, nsplit;               // first partial tile, their number: blocks per tile
     int gx, gy;
 };
 
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(256) void k_fold_mm(FoldArgs p) {
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b0 = by * NC;
-    const int piece0 = sp * p.ppb;
+    const int piece0 = (p.sp0 + sp) * p.ppb;
     const int piece1 = piece0 + p.ppb < l.nk * p.njr ? piece0 + p.ppb : l.nk * p.njr;
 
     Acc4 Y[FN];
@@ -458,8 +459,7 @@ constexpr int kFoldVariants = kFoldShapes * 7;
 // (weights, X fragments, first slabs); rounds of concurrent blocks are counted fractionally;
 // and the whole is no less than the tensor's stream over HBM.  Fitted to sweeps of all shapes
 // and splits at N = 64 .. 1000 and B = 7 .. 256.
-// nsplit_max > 0 bounds the partial tiles.
-FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max, int nsplit_max) {
+FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max) {
     constexpr double kPiece = 7000, kLatency = 1500;
     const size_t accb = dt == DT_F64 ? 8 : 4, per_cu = (size_t)150 << 10;
     const int gx = (l.N + 15) / 16;
@@ -514,7 +514,6 @@ FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_m
         }
     }
     const int pieces = l.nk * pl.njr;
-    if (nsplit_max > 0 && (pieces + pl.ppb - 1) / pl.ppb > nsplit_max) pl.ppb = (pieces + nsplit_max - 1) / nsplit_max;
     pl.nsplit = (pieces + pl.ppb - 1) / pl.ppb;
     pl.gx = gx;
     // with one column tile nothing re-reads the tensor through L2 (FP32 at N = 700, B = 16:
@@ -564,8 +563,10 @@ hipError_t fold_set_lds_limit(size_t lds) {
     return e;
 }
 
-void launch_fold_batched(int dt, const FoldPlan& pl, const void* C, const void* Clo, const FoldLay& l, int Kx, int Bpad,
-                         const void* X, const void* Xlo, const void* S, void* part, hipStream_t s) {
+void launch_fold_batched(int dt, const FoldPlan& pl0, int sp0, int nsp, const void* C, const void* Clo, const FoldLay& l,
+                         int Kx, int Bpad, const void* X, const void* Xlo, const void* S, void* part, hipStream_t s) {
+    FoldPlan pl = pl0;
+    if (nsp != pl.nsplit) pl.blocks = (int)(((long long)pl.gx * pl.gy * nsp + 7) / 8 * 8);
     FoldArgs a{};
     a.C = C;
     a.Clo = (const unsigned short*)Clo;
@@ -579,7 +580,8 @@ void launch_fold_batched(int dt, const FoldPlan& pl, const void* C, const void* 
     a.njr = pl.njr;
     a.jc = pl.jc;
     a.ppb = pl.ppb;
-    a.nsplit = pl.nsplit;
+    a.sp0 = sp0;
+    a.nsplit = nsp;
     a.gx = pl.gx;
     a.gy = pl.gy;
     if (dt == DT_F64) fold_go<DT_F64>(a, pl, s);

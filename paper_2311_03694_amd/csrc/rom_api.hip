@@ -195,19 +195,24 @@ FoldJob fold_job(rom_ctx c, const void* wj, const double* u_base, const long lon
     return make_fold_job(c->dtype, c->F, c->F_lo, c->fl, wj, u_base, stepp, slot_stride, part, fold_njr(c));
 }
 // kinds 2 (CP projections) and 3 (CP scatter): k_gemm variants first, then the LDS-tile
-// kernel's
-SkinnyPlan skinny_plan(rom_ctx c, int kind, int Bpad) {
+// kernel's.  Planned for plan_Bpad columns, launched over Bpad of them.
+SkinnyPlan skinny_plan(rom_ctx c, int kind, int plan_Bpad, int Bpad) {
     SkinnyPlan sp{};
     const int v = c->tile[kind];
     const int M = kind == 2 ? 2 * c->Rp : c->N;
     if (v >= gemm_variants()) {
         sp.engine = 1;
         const MfmaTile t = mfma_variant(v - gemm_variants());
-        sp.m = kind == 2 ? mfma_proj_plan(c->dtype, c->Np, c->Rp, Bpad, t) : mfma_scatter_plan(c->dtype, c->N, c->Rp, Bpad, t);
+        sp.m = kind == 2 ? mfma_proj_plan(c->dtype, c->Np, c->Rp, plan_Bpad, t)
+                         : mfma_scatter_plan(c->dtype, c->N, c->Rp, plan_Bpad, t);
+        sp.m.grid_y = Bpad / sp.m.bt;
+        sp.m.blocks = (sp.m.grid_x * sp.m.grid_y * sp.m.nsplit + 7) / 8 * 8;
         sp.nsplit = sp.m.nsplit;
     } else {
         sp.engine = 0;
-        sp.g = gemm_plan(M, Bpad, v > 0 ? v : 1);
+        sp.g = gemm_plan(M, plan_Bpad, v > 0 ? v : 1);
+        sp.g.gy = Bpad / (16 * sp.g.fn);
+        sp.g.blocks = (sp.g.gx * sp.g.gy + 7) / 8 * 8;
         sp.nsplit = 1;
     }
     return sp;
@@ -267,10 +272,12 @@ void launch_zero_fill(void* p, size_t bytes, hipStream_t s) {
 // rom_nonlinear): layout and launch plans.
 struct WsPlan {
     int B = 1, Bpad = 16;
+    bool single = true;             // the kernels of one trajectory
     int nchunk = 0;                 // B = 1 dense: partial chunks per row
     DensePlan pd{};                 // B > 1: dense contraction (BF16)
     FoldPlan pf{};                  // B > 1: dense contraction (folded tensor)
     int nsplit = 1;                 // B > 1: partial tiles of the contraction
+    int held = 1;                   // of which the workspace holds so many at a time
     SkinnyPlan pp{}, ps{};          // B > 1: CP projection, CP scatter
     size_t part_off = 0;            // dense / scatter partials, or CP s,t (B = 1)
     size_t part2_off = 0;           // CP projection partials (B > 1)
@@ -281,16 +288,20 @@ struct WsPlan {
     size_t total = 0;
 };
 
-// splits > 0 asks for a smaller workspace: at most that many partial tiles of a batched folded
-// contraction, and y of the batched CP products in the place of the operand copies (such a
-// plan's contraction runs once: it overwrites them).
-WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
+// plan_B > 0: B trajectories out of a batch of plan_B, by the kernel plans of that batch (B a
+// multiple of 64, or the rest of such slices).  held > 0: at most that many partial tiles of a
+// batched folded contraction at a time.  Either way the sums keep their order, and so a
+// smaller workspace gives the same bits.
+WsPlan plan_ws(rom_ctx c, int B, int plan_B = 0, int held = 0) {
     WsPlan p;
+    if (plan_B <= 0) plan_B = B;
     p.B = B;
     p.Bpad = (B + 15) / 16 * 16;
+    p.single = plan_B == 1;
+    const int plan_Bpad = (plan_B + 15) / 16 * 16;
     const size_t ab = acc_bytes(c->dtype);
     size_t off = 0;
-    if (B == 1) {
+    if (p.single) {
         if (c->dense || c->svd) {
             p.nchunk = c->F ? c->fl.nk * fold_njr(c) : dense_gemv_nchunk(c->N, gemv_tile(c));
             p.part_off = off;
@@ -305,38 +316,32 @@ WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
         }
     } else {
         const size_t eb = elem_bytes(c->dtype);
-        size_t part_end = 0;
         if (c->dense) {
             if (c->dtype != DT_BF16) {
-                if (splits > 0) {
-                    p.pf = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, splits);
-                } else {
-                    if (c->fplan_B != p.Bpad || c->fplan_v != c->tile[1]) {
-                        c->fplan = fold_plan(c->dtype, c->fl, p.Bpad, c->tile[1], c->lds_max, 0);
-                        c->fplan_B = p.Bpad;
-                        c->fplan_v = c->tile[1];
-                    }
-                    p.pf = c->fplan;
+                if (c->fplan_B != plan_Bpad || c->fplan_v != c->tile[1]) {
+                    c->fplan = fold_plan(c->dtype, c->fl, plan_Bpad, c->tile[1], c->lds_max);
+                    c->fplan_B = plan_Bpad;
+                    c->fplan_v = c->tile[1];
                 }
+                p.pf = c->fplan;
                 p.nsplit = p.pf.nsplit;
             } else {
-                p.pd = dense_batched_plan(c->N, c->Np, p.Bpad, c->tile[1], c->lds_max);
+                p.pd = dense_batched_plan(c->N, c->Np, plan_Bpad, c->tile[1], c->lds_max);
                 p.nsplit = p.pd.nsplit;
             }
+            p.held = held > 0 && held < p.nsplit && c->dtype != DT_BF16 ? held : p.nsplit;
             p.part_off = off;
-            off = align256(off + (size_t)p.nsplit * p.Bpad * c->N * ab);
+            off = align256(off + (size_t)p.held * p.Bpad * c->N * ab);
         } else {
-            p.pp = skinny_plan(c, 2, p.Bpad);
-            p.ps = skinny_plan(c, 3, p.Bpad);
-            p.nsplit = p.ps.nsplit;
+            p.pp = skinny_plan(c, 2, plan_Bpad, p.Bpad);
+            p.ps = skinny_plan(c, 3, plan_Bpad, p.Bpad);
+            p.nsplit = p.held = p.ps.nsplit;
             p.part2_off = off;
             if (p.pp.engine == 1) off = align256(off + (size_t)p.pp.nsplit * p.Bpad * 2 * c->Rp * ab);
             p.w_off = off;
             off = align256(off + (size_t)p.Bpad * gemm_kt(c->dtype == DT_F64 ? DT_F64 : DT_F32, c->Rp) * ab);
             p.part_off = off;
-            const size_t part = align256((size_t)p.ps.nsplit * p.Bpad * c->N * ab);
-            if (splits == 0 || p.pp.engine != 0 || p.ps.engine != 0) off += part;
-            else part_end = off + part;
+            off = align256(off + (size_t)p.ps.nsplit * p.Bpad * c->N * ab);
         }
         const size_t urow = c->dense ? c->Np : gemm_kt(c->dtype, c->Np);
         p.ucv_off = off;
@@ -345,7 +350,6 @@ WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
         off = align256(off + (c->dtype == DT_BF16X3 ? (size_t)p.Bpad * urow * 2 : 0));
         p.usc_off = off;
         if (c->dense) off = align256(off + (size_t)p.Bpad * c->Np * ab);
-        if (off < part_end) off = part_end;
         if (!c->diagA) p.ph = gemm_plan(c->N, p.Bpad, 1);
     }
     p.total = off + 256;
@@ -353,8 +357,8 @@ WsPlan plan_ws(rom_ctx c, int B, int splits = 0) {
 }
 
 // The workspace by which rom_nonlinear_noalloc decides whether it serves a batch: partial
-// tiles, products and operand copies in rows, whatever plan the kernels then take (never a
-// larger one), so that the batches it serves do not move with the kernels.
+// tiles, products and operand copies in rows, whatever layout the kernels then take, so that
+// the batches it serves do not move with the kernels.
 size_t noalloc_bytes(rom_ctx c, int B) {
     if (B == 1) return plan_ws(c, 1).total;
     const size_t Bpad = (B + 15) / 16 * 16, ab = acc_bytes(c->dtype), eb = elem_bytes(c->dtype);
@@ -363,7 +367,7 @@ size_t noalloc_bytes(rom_ctx c, int B) {
         const int np = dense_partials(c->dtype, c->N, c->Np, (int)Bpad, c->tile[1], c->lds_max);
         off = align256((size_t)np * Bpad * c->N * ab);
     } else {
-        const SkinnyPlan pp = skinny_plan(c, 2, (int)Bpad), ps = skinny_plan(c, 3, (int)Bpad);
+        const SkinnyPlan pp = skinny_plan(c, 2, (int)Bpad, (int)Bpad), ps = skinny_plan(c, 3, (int)Bpad, (int)Bpad);
         off = align256((size_t)pp.nsplit * Bpad * 2 * c->Rp * ab);
         off = align256(off + Bpad * c->Rp * ab);
         off = align256(off + (size_t)ps.nsplit * Bpad * c->N * ab);
@@ -373,10 +377,13 @@ size_t noalloc_bytes(rom_ctx c, int B) {
     return align256(off + Bpad * c->Np * ab) + 256;
 }
 
-// The batched dense contraction of plan p: partial tiles in `part`.
+// The batched dense contraction of plan p: its partial tiles sp0 .. sp0 + held - 1 in `part`
+// (sp0 = 0 where all are held).
 void launch_dense_term(rom_ctx c, const WsPlan& p, const void* X, const void* Xlo, const void* S, void* part,
-                       hipStream_t s) {
-    if (c->dtype != DT_BF16) launch_fold_batched(c->dtype, p.pf, c->F, c->F_lo, c->fl, c->Np, p.Bpad, X, Xlo, S, part, s);
+                       hipStream_t s, int sp0 = 0) {
+    if (c->dtype != DT_BF16)
+        launch_fold_batched(c->dtype, p.pf, sp0, std::min(p.held, p.nsplit - sp0), c->F, c->F_lo, c->fl, c->Np, p.Bpad, X, Xlo,
+                            S, part, s);
     else launch_dense_batched(p.pd, c->C, c->Ct, c->N, c->Np, p.Bpad, X, S, part, s);
 }
 
@@ -1395,24 +1402,35 @@ static bool overlap(const double* a, const double* b, size_t n) {
 // contraction kernels, and the sum of the partial results into y.  With kernel_us the
 // contraction is captured `reps` times into a HIP graph, launched once to warm up and
 // once between two events; *kernel_us is the average per repetition.
+//
+// ws_given: a caller-chosen workspace of ws_bytes (zeroed here: what the kernels may read
+// beyond the regions they write, lane vectors up to one k-step past the last row, must be
+// zero, as a fresh workspace is).  Where the plan of the batch does not fit in it, a folded
+// contraction runs in several parts, and a CP batch in slices (plan_batch: the whole batch).
+static rom_status nonlinear_slices(rom_ctx c, int32_t batch, const double* u_dev, double* y_dev, char* ws, size_t ws_bytes);
 static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, double* y_dev, int reps,
-                                 double* kernel_us, char* ws_given = nullptr, size_t ws_given_bytes = 0) {
+                                 double* kernel_us, char* ws_given = nullptr, size_t ws_bytes = 0, int plan_batch = 0) {
     if (!c) return fail(ROM_E_INVALID, "ctx is NULL");
     if (batch < 1 || batch > c->max_batch) return fail(ROM_E_INVALID, "batch %d outside [1, %d]", batch, c->max_batch);
     if (!u_dev || !y_dev) return fail(ROM_E_INVALID, "u_dev / y_dev is NULL");
-    WsPlan p = plan_ws(c, batch);
-    // a bounded workspace: a smaller plan where the usual one does not fit
-    for (int ns = p.nsplit; ws_given && batch > 1 && p.total > ws_given_bytes && ns > 0; ns /= 2)
-        p = plan_ws(c, batch, ns > 1 ? ns / 2 : 1);
+    WsPlan p = plan_ws(c, batch, plan_batch);
     char* ws = ws_given;
     if (ws) {
-        // a caller-chosen workspace: it must hold the plan, and what the kernels may
-        // read beyond the regions they write (lane vectors run up to one k-step past
-        // the last row) must be zero, as a fresh workspace is
-        const size_t need = std::max(noalloc_bytes(c, batch), p.total);
-        if (need > ws_given_bytes)
-            return fail(ROM_E_UNSUPPORTED, "the evaluation needs %zu bytes of workspace, more than the %zu available",
-                        need, ws_given_bytes);
+        size_t need = plan_batch ? 0 : noalloc_bytes(c, batch);
+        if (need <= ws_bytes && p.total > ws_bytes) {
+            if (c->dense && !p.single) {
+                const size_t tile = (size_t)p.Bpad * c->N * acc_bytes(c->dtype);
+                const size_t rest = plan_ws(c, batch, plan_batch, 1).total - align256(tile);
+                const size_t held = rest < ws_bytes ? (ws_bytes - rest) / tile : 0;
+                p = plan_ws(c, batch, plan_batch, (int)std::min<size_t>(std::max<size_t>(held, 1), p.nsplit));
+            } else if (!p.single && !plan_batch) {
+                return nonlinear_slices(c, batch, u_dev, y_dev, ws, ws_bytes);
+            }
+        }
+        if (p.total > need) need = p.total;
+        if (need > ws_bytes)
+            return fail(ROM_E_UNSUPPORTED, "the evaluation needs %zu bytes of workspace, more than the %zu available", need,
+                        ws_bytes);
         launch_zero_fill(ws, p.total, c->stream);
     } else {
         rom_status st = ensure_ws(c, p.total);
@@ -1421,7 +1439,7 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     }
     const int accf = acc_f64(c->dtype);
     StepArgs a{};
-    if (batch > 1) {
+    if (!p.single) {
         // operand copies of the caller's u in the contraction format
         a.N = c->N;
         a.Np = c->Np;
@@ -1439,7 +1457,7 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     // still read u: in place (or with arrays that overlap) the two launches run instead
     const bool apart = !overlap(u_dev, y_dev, (size_t)c->N);
     auto contract = [&]() {
-        if (batch == 1) {
+        if (p.single) {
             if (c->dense) {
                 if (c->F)
                     launch_fold_gemv(c->dtype, fold_job(c, nullptr, u_dev, nullptr, 0, ws + p.part_off), c->stream);
@@ -1492,12 +1510,32 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
         if (e != hipSuccess) return fail(ROM_E_DEVICE, "timing the contraction failed: %s", hipGetErrorString(e));
         *kernel_us = 1e3 * (double)ms / reps;
     }
-    if (batch == 1) {
-        if (c->dense || c->svd) launch_sum_partials(accf, ws + p.part_off, p.nchunk, 1, 1, c->N, y_dev, c->stream);
+    if (p.single) {
+        if (c->dense || c->svd) launch_sum_partials1(accf, ws + p.part_off, p.nchunk, c->N, y_dev, c->stream);
     } else {
-        launch_sum_partials(accf, ws + p.part_off, p.nsplit, p.Bpad, batch, c->N, y_dev, c->stream);
+        launch_sum_partials(accf, ws + p.part_off, p.held, p.Bpad, batch, c->N, 0, y_dev, c->stream);
+        for (int sp = p.held; sp < p.nsplit; sp += p.held) {
+            launch_dense_term(c, p, a.ucv, a.ucv_lo, a.uj, ws + p.part_off, c->stream, sp);
+            launch_sum_partials(accf, ws + p.part_off, std::min(p.held, p.nsplit - sp), p.Bpad, batch, c->N, 1, y_dev,
+                                c->stream);
+        }
     }
     HIPCHK(hipGetLastError());
+    return ROM_OK;
+}
+
+// A CP batch in slices that fit the workspace, by the plans of the whole batch: a trajectory's
+// sums do not depend on its neighbours.  The order is that of a copy between overlapping
+// arrays: no slice's y covers u that a later slice reads.
+static rom_status nonlinear_slices(rom_ctx c, int32_t batch, const double* u_dev, double* y_dev, char* ws, size_t ws_bytes) {
+    int cols = (batch + 63) / 64 * 64;
+    while (cols > 64 && plan_ws(c, cols, batch).total > ws_bytes) cols = (cols / 2 + 63) / 64 * 64;
+    const int n = (batch + cols - 1) / cols;
+    for (int q = 0; q < n; ++q) {
+        const int b0 = ((uintptr_t)y_dev > (uintptr_t)u_dev ? n - 1 - q : q) * cols;
+        const size_t at = (size_t)b0 * c->N;
+        TRYS(nonlinear_impl(c, std::min(cols, batch - b0), u_dev + at, y_dev + at, 1, nullptr, ws, ws_bytes, batch));
+    }
     return ROM_OK;
 }
 

@@ -327,9 +327,11 @@ void launch_bdf_from_partials(const StepArgs& a, int acc_f64, const void* part, 
 void launch_helm_apply(const StepArgs& a, hipStream_t s);
 // Write the batched coefficient copies from the current level (state create / set).
 void launch_prep_ucv(const StepArgs& a, const double* u_src, hipStream_t s);
-// Sum partials into FP64 y [B][N] (rom_nonlinear).
-void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N,
-                         double* y, hipStream_t s);
+// Sum partials into FP64 y [B][N] (rom_nonlinear), in order; add: behind the sum already in y.
+void launch_sum_partials(int acc_f64, const void* part, int nchunk, int pb, int B, int N, int add, double* y,
+                         hipStream_t s);
+// One trajectory.
+void launch_sum_partials1(int acc_f64, const void* part, int nchunk, int N, double* y, hipStream_t s);
 
 // Helmholtz setup on the device: H = (beta0/dt) I + nu A, Cholesky, inverse.
 int helm_setup_dense(int N, int Np, double nu, double dt, const double* A_dev, const double* M_dev,
@@ -414,9 +416,10 @@ struct FoldPlan {
     int gx, gy, blocks;
     size_t lds;
 };
-FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max, int nsplit_max);
+FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max);
 hipError_t fold_set_lds_limit(size_t lds);
-void launch_fold_batched(int dt, const FoldPlan& pl, const void* C, const void* Clo, const FoldLay& l, int Kx, int Bpad,
+// Partial tiles sp0 .. sp0 + nsp - 1 of the plan's.
+void launch_fold_batched(int dt, const FoldPlan& pl, int sp0, int nsp, const void* C, const void* Clo, const FoldLay& l, int Kx, int Bpad,
                          const void* X, const void* Xlo, const void* S, void* part, hipStream_t s);
 
 // Skinny products of the batched path (k_gemm.hip): one block per output tile over the
