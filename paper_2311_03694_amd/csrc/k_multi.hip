@@ -21,7 +21,7 @@ __device__ __forceinline__ void mix_body(const MixJob& jb, int blk) {
     constexpr int V = 16 / (int)sizeof(T);
     switch (jb.kind) {
         case MIX_GEMV:
-            if constexpr (DT == DT_BF16) dense_gemv_body<4>(jb.g, blk);
+            dense_gemv_body<DT, V, 4, 256>(jb.g, blk);
             break;
         case MIX_FOLD:
             if (jb.d.stream) fold_gemv_body<DT, kFoldU, true>(jb.d, blk);
@@ -108,7 +108,7 @@ int mix_job_blocks(const MixJob& jb) {
 
 size_t mix_job_lds(const MixJob& jb) {
     switch (jb.kind) {
-        case MIX_GEMV: return lds_u(jb.dtype, jb.g.Np);
+        case MIX_GEMV: return dense_gemv_lds(jb.dtype, jb.g.Np, jb.g.wj ? jb.g.J : 0);
         case MIX_FOLD: return fold_gemv_lds(jb.dtype, jb.d);
         case MIX_PROJ: return proj_lds_of(jb.dtype, jb.p.Np);
         case MIX_BDF: return 0;

@@ -1,5 +1,5 @@
 // kbody.h -- the per-block bodies of the one-trajectory step kernels: the dense
-// streaming contraction of large BF16 tensors, the CP projections (general and
+// streaming contraction of large BF16 tensors and SVD slabs, the CP projections (general and
 // pair form) and Hadamard-scatter, the Helmholtz apply with the next projections, the SVD
 // form's first product, the BDF update from contraction partials and the full form's
 // zeroth-mode and mass terms.  Each body runs one block's share of one state's work
@@ -15,30 +15,38 @@ namespace rom {
 
 // ============================================================== dense contraction, one trajectory
 
-template <int UNR>
+template <int DT, int V, int UNR, int NT>
 __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
-    constexpr int V = 8, NT = 256;                       // BF16 words per 16-byte load, threads
+    typedef typename Store<DT>::T T;
+    typedef typename Store<DT>::Acc Acc;
+    typedef typename RawT<V * (int)sizeof(T)>::T Raw;
+    constexpr int BYTES = V * (int)sizeof(T);
+    constexpr bool X3 = (DT == DT_BF16X3);
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ float red[NT / kWave];
+    __shared__ Acc red[NT / kWave];
     const int N = jb.N, Np = jb.Np, nchunk = jb.nchunk;
     const long long chunk_len = jb.chunk_len;
-    const unsigned short* __restrict__ C = reinterpret_cast<const unsigned short*>(jb.C);
-    LdsU<DT_BF16> L;
+    const T* __restrict__ C = reinterpret_cast<const T*>(jb.C);
+    LdsU<DT> L;
     L.bind(smem, Np);
+    // slab weights: u itself (its accumulation-format image), or jb.wj staged behind it
+    Acc* wl = reinterpret_cast<Acc*>(smem + LdsU<DT>::bytes(Np));
+    const Acc* wsrc = jb.wj ? wl : L.uw;
 
     const int i = blk / nchunk;
     const int c = blk - i * nchunk;
-    const long long NN = (long long)N * Np;
+    const long long NN = (long long)jb.J * Np;
     const long long m0 = (long long)c * chunk_len;
     const long long m1 = (m0 + chunk_len < NN) ? m0 + chunk_len : NN;
-    const unsigned short* row = C + (size_t)i * NN;
+    const T* row = C + (size_t)i * NN;
+    const unsigned short* rowlo = X3 ? jb.Clo + (size_t)i * NN : nullptr;
 
     constexpr int STEP = NT * V;
     const int dj = STEP / Np, dk = STEP - (STEP / Np) * Np;
     long long m = m0 + (long long)threadIdx.x * V;
     int j = (int)(m / Np), k = (int)(m - (long long)j * Np);
 
-    u32x4 r[UNR];
+    Raw r[UNR], rl[UNR];
     int jj[UNR], kk[UNR];
     auto issue = [&](long long mb) {
 #pragma unroll
@@ -46,7 +54,10 @@ __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
             const long long mq = mb + (long long)q * STEP;
             jj[q] = j;
             kk[q] = k;
-            if (mq < m1) r[q] = ld_stream<16>(row + mq);
+            if (mq < m1) {
+                r[q] = ld_stream<BYTES>(row + mq);
+                if constexpr (X3) rl[q] = ld_stream<BYTES>(rowlo + mq);
+            }
             k += dk;
             j += dj;
             if (k >= Np) { k -= Np; ++j; }
@@ -55,21 +66,24 @@ __device__ __forceinline__ void dense_gemv_body(const GemvJob& jb, int blk) {
 
     if (m < m1) issue(m);
     L.fill(jb.u_base + (jb.stepp ? (size_t)slot_of(*jb.stepp) * jb.slot_stride : 0), N, Np);
+    if (jb.wj) {
+        const Acc* wg = reinterpret_cast<const Acc*>(jb.wj);
+        for (int q = threadIdx.x; q < jb.J; q += NT) wl[q] = wg[q];
+    }
     __syncthreads();
 
-    float acc = 0;
+    Acc acc = 0;
     while (m < m1) {
 #pragma unroll
         for (int q = 0; q < UNR; ++q) {
-            if (m + (long long)q * STEP < m1) acc += L.uw[jj[q]] * dot_vec<DT_BF16, V>(r[q], r[q], L, kk[q]);
+            if (m + (long long)q * STEP < m1) acc += wsrc[jj[q]] * dot_vec<DT, V>(r[q], rl[q], L, kk[q]);
         }
         m += (long long)STEP * UNR;
         if (m < m1) issue(m);
     }
-    const float s = block_sum(acc, red);
-    if (threadIdx.x == 0) reinterpret_cast<float*>(jb.part)[(size_t)c * N + i] = s;
+    const Acc s = block_sum(acc, red);
+    if (threadIdx.x == 0) reinterpret_cast<Acc*>(jb.part)[(size_t)c * N + i] = s;
 }
-
 
 // ============================================================== full form terms
 
@@ -527,7 +541,8 @@ __device__ __forceinline__ void helm_proj_body(const HelmJob& jb, long long n, i
 
 // First product of the SVD-ROM (Sec. 4.4): w_r = sigma_r sum_j U[j][r] u_j over the rows
 // of Ut [Rsp][Np] (rows past the rank are zero, so w is zero there).  One wavefront per
-// row, four per block; the second product is the stream of R weighted slabs (kfold.h).
+// row, four per block; the second product is the stream of R weighted slabs (kfold.h, or dense_gemv_body
+// where they are large).
 
 template <int DT, int V, int U>
 __device__ __forceinline__ void svd_proj_body(const SvdProj& a, int blk) {

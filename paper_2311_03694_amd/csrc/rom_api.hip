@@ -77,10 +77,10 @@ struct rom_ctx_s {
     bool own_stream = false;
     // operators in the contraction format
     // (contracted indices padded with zeros: Np, Rp = N, R rounded up to multiples of 8)
-    void* C = nullptr;                         // dense BF16 [N][N][Np]
+    void *C = nullptr, *Clo = nullptr;         // dense BF16 [N][N][Np], or large SVD slabs [N][Rs][Np]
     void* Ct = nullptr;                        // dense BF16, max_batch > 1: tiled copy for k_kr
     // dense FP64, FP32, BF16X3: the folded tensor (kfold.h), for one trajectory and batches;
-    // small dense BF16: the unfolded one, for one trajectory; SVD form: the slabs of V
+    // small dense BF16: the unfolded one, for one trajectory; SVD form: the slabs of V, up to a size
     FoldLay fl{};
     FoldPlan fplan{};                          // the latest unbounded batch plan, of fplan_B columns and
     int fplan_B = 0, fplan_v = 0;              // variant fplan_v (planning is a search of some 100 splits)
@@ -187,12 +187,23 @@ namespace {
 GemvTile gemv_tile(rom_ctx c) { return dense_gemv_variant(c->tile[0] < 0 ? 0 : c->tile[0]); }
 // The folded stream's pieces per chunk: its blocks (16 rows each) are an eighth of the
 // unfolded kernel's target, 1024 by default (FP32 at N = 300: 11.7 us, with 2048 blocks 15.5);
-// in FP64 half of it (100 SVD slabs at N = 1000: 118 us against 122, dense N = 400 42 against
-// 44).
+// in FP64 half of it (dense N = 400 42 us against 44).
 int fold_njr(rom_ctx c) { return fold_gemv_njr(c->fl, gemv_tile(c).chunk_target / (c->dtype == DT_F64 ? 2 : 8)); }
 FoldJob fold_job(rom_ctx c, const void* wj, const double* u_base, const long long* stepp, long long slot_stride,
                  void* part) {
     return make_fold_job(c->dtype, c->F, c->F_lo, c->fl, wj, u_base, stepp, slot_stride, part, fold_njr(c));
+}
+// The stream of one trajectory over the tensor, or over the SVD form's slabs with their weights
+// wj: in the tiled storage where there is one, else in rows.
+GemvJob gemv_job(rom_ctx c, const void* wj, const double* u_base, const long long* stepp, long long slot_stride, void* part,
+                 int nchunk) {
+    return make_gemv_job(c->dtype, c->C, c->Clo, c->N, c->Np, c->svd ? c->Rs : c->N, wj, u_base, stepp, slot_stride, part,
+                         nchunk, gemv_tile(c));
+}
+void launch_stream(rom_ctx c, const void* wj, const double* u_base, const long long* stepp, long long slot_stride,
+                   void* part, int nchunk, hipStream_t s) {
+    if (c->F) launch_fold_gemv(c->dtype, fold_job(c, wj, u_base, stepp, slot_stride, part), s);
+    else launch_dense_gemv(c->dtype, gemv_job(c, wj, u_base, stepp, slot_stride, part, nchunk), gemv_tile(c), s);
 }
 // kinds 2 (CP projections) and 3 (CP scatter): k_gemm variants first, then the LDS-tile
 // kernel's.  Planned for plan_Bpad columns, launched over Bpad of them.
@@ -491,6 +502,13 @@ static rom_status stage_folded(rom_ctx c, const double* host, int J, bool svd, d
 // 18.5).  Larger ones stream at the memory's rate either way, and their rows are padded less
 // (to 8 elements instead of 32: N = 450 29.2 us against 34.3).
 constexpr double kBf16TileBytes = 100e6;
+// SVD slabs up to this size take the tiled storage; larger ones stream from HBM, in rows at a
+// higher rate (us a step, tiled against rows; N = 1000 unless said otherwise: BF16 80 MB 25.4
+// against 29.6, FP32 160 MB 31.9 against 32.9, BF16 196 MB (N = 700) 38.0 both; BF16X3 392 MB
+// (N = 700) 67.1 against 64.7, FP32 400 MB 65.0 against 62.6, FP64 800 MB 127.0 against 121.6,
+// FP32 1 GB 153.4 against 150.8).  Weights that leave the row stream no LDS of its own stay
+// tiled as well.
+constexpr double kSvdTileBytes = 200e6;
 
 // Column pairs of CP factors that keep the partial skew-symmetry (Sec. 3.3, eq.
 // skew_abc_struct): pair p = (c0, c1) with lam[c0] == lam[c1], Bf[:,c0] == Bf[:,c1],
@@ -834,7 +852,8 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
     const bool lo = dt == DT_BF16X3;
     const size_t Np = c->Np;
     if (sv) {
-        // SVD form (Sec. 4.4): Ut rows are the columns of U, V's slabs r in the tiled storage
+        // SVD form (Sec. 4.4): Ut rows are the columns of U, V's slabs r in the tiled storage or in
+        // rows [N][Rs][Np]
         const size_t Rs = (size_t)sv->R, Rsp = (Rs + 7) / 8 * 8;
         c->Rs = (int)Rs;
         c->Rsp = (int)Rsp;
@@ -850,7 +869,26 @@ static rom_status create_ctx(const rom_desc* d, const SvdDesc* sv, const rom_ful
         for (size_t n = 0; n < (size_t)N; ++n)
             for (size_t r = 0; r < Rs; ++r) t[r * N + n] = sv->U[n * Rs + r];
         TRY(upload_convert(c, t.data(), Rs, (int)N, (int)Np, c->Ut, c->Ut_lo, stage, stage_elems));
-        TRY(stage_folded(c, sv->V, (int)Rs, true, stage, stage_elems));
+        const size_t rows = (size_t)N * Rs * Np;
+        if ((double)nn * Rs * (lo ? 4 : eb) > kSvdTileBytes && dense_gemv_lds(dt, (int)Np, (int)Rs) + 64 <= 65536) {
+            TRY(dmalloc(&c->C, rows * eb + kSlack, &c->bytes, &c->allocs));
+            HTRY(hipMemsetAsync(c->C, 0, rows * eb + kSlack, c->stream));
+            if (lo) {
+                TRY(dmalloc(&c->Clo, rows * 2 + kSlack, &c->bytes, &c->allocs));
+                HTRY(hipMemsetAsync(c->Clo, 0, rows * 2 + kSlack, c->stream));
+            }
+            const int per = (int)std::max<size_t>(1, stage_elems / (N * Rs));
+            for (int i0 = 0; i0 < (int)N; i0 += per) {
+                const int ni = std::min(per, (int)N - i0);
+                HTRY(hipMemcpyAsync(stage, sv->V + (size_t)i0 * N * Rs, sizeof(double) * (size_t)ni * N * Rs,
+                                    hipMemcpyHostToDevice, c->stream));
+                launch_slab_rows(dt, stage, i0, ni, (int)N, (int)Rs, (int)Np, c->C, c->Clo, c->stream);
+                HTRY(hipGetLastError());
+                HTRY(hipStreamSynchronize(c->stream));
+            }
+        } else {
+            TRY(stage_folded(c, sv->V, (int)Rs, true, stage, stage_elems));
+        }
         HTRY(hipMemcpyAsync(stage, sv->sigma, sizeof(double) * Rs, hipMemcpyHostToDevice, c->stream));
         launch_cvt_lambda(dt, stage, c->sig, (long long)Rs, c->stream);
         HTRY(hipGetLastError());
@@ -1347,17 +1385,12 @@ static rom_status enqueue_step(rom_ctx c, rom_state s, hipStream_t stream, long 
     if (s->B == 1) {
         char* ws = (char*)s->scratch;
         if (c->dense) {
-            if (c->F)
-                launch_fold_gemv(c->dtype, fold_job(c, nullptr, a.uring, a.step, (long long)c->N, ws + p.part_off), stream);
-            else
-                launch_dense_gemv(c->C, c->N, c->Np, a.uring, a.step, (long long)c->N, ws + p.part_off, p.nchunk,
-                                  gemv_tile(c), stream);
+            launch_stream(c, nullptr, a.uring, a.step, (long long)c->N, ws + p.part_off, p.nchunk, stream);
             launch_bdf_from_partials(a, accf, ws + p.part_off, p.nchunk, 1, diag, stream);
         } else if (c->svd) {
             launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, a.uring, a.step, (long long)c->N,
                             ws + p.svdw_off, stream);
-            launch_fold_gemv(c->dtype, fold_job(c, ws + p.svdw_off, a.uring, a.step, (long long)c->N, ws + p.part_off),
-                             stream);
+            launch_stream(c, ws + p.svdw_off, a.uring, a.step, (long long)c->N, ws + p.part_off, p.nchunk, stream);
             launch_bdf_from_partials(a, accf, ws + p.part_off, p.nchunk, 1, diag, stream);
         } else {
             // a.st holds w = lam .* s .* t of level n: computed here with a diagonal
@@ -1459,15 +1492,11 @@ static rom_status nonlinear_impl(rom_ctx c, int32_t batch, const double* u_dev, 
     auto contract = [&]() {
         if (p.single) {
             if (c->dense) {
-                if (c->F)
-                    launch_fold_gemv(c->dtype, fold_job(c, nullptr, u_dev, nullptr, 0, ws + p.part_off), c->stream);
-                else
-                    launch_dense_gemv(c->C, c->N, c->Np, u_dev, nullptr, 0, ws + p.part_off, p.nchunk, gemv_tile(c),
-                                      c->stream);
+                launch_stream(c, nullptr, u_dev, nullptr, 0, ws + p.part_off, p.nchunk, c->stream);
             } else if (c->svd) {
                 launch_svd_proj(c->dtype, c->Ut, c->Ut_lo, c->sig, c->N, c->Np, c->Rs, u_dev, nullptr, 0,
                                 ws + p.svdw_off, c->stream);
-                launch_fold_gemv(c->dtype, fold_job(c, ws + p.svdw_off, u_dev, nullptr, 0, ws + p.part_off), c->stream);
+                launch_stream(c, ws + p.svdw_off, u_dev, nullptr, 0, ws + p.part_off, p.nchunk, c->stream);
             } else if (!apart || !launch_cp_eval_small(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->Af, c->Af_lo, c->N,
                                                        c->Np, c->Rp, skew_of(c), u_dev, y_dev, c->stream)) {
                 launch_cp_proj1(c->dtype, proj_op(c), proj_op_lo(c), c->lam, c->N, c->Np, c->Rp, skew_of(c), u_dev,
@@ -2389,7 +2418,7 @@ void pair_jobs(rom_ctx c, rom_state st, long long lev, std::vector<MixJob> (&ph)
             jg.d = fold_job(c, wj, sa.uring, sa.step, c->N, scr + p.part_off);
         } else {
             jg.kind = MIX_GEMV;
-            jg.g = make_gemv_job(c->C, c->N, c->Np, sa.uring, sa.step, c->N, scr + p.part_off, p.nchunk, gemv_tile(c));
+            jg.g = gemv_job(c, wj, sa.uring, sa.step, c->N, scr + p.part_off, p.nchunk);
         }
         add(1, jg);
         MixJob jb{};

@@ -69,9 +69,12 @@ struct StepArgs {
 
 // A job is one kernel's work for one (context, state) pair; grouped launches run the
 // jobs of many pairs (uneven N, R) in one grid, job p owning blocks [blk0, blk0+nblk).
-struct GemvJob {           // dense contraction of a large BF16 tensor, one trajectory
-    const void* C;                 // [N][N][Np]
+struct GemvJob {           // dense contraction of a large BF16 tensor or SVD slabs, one trajectory
+    const void* C;                 // [N][J][Np]
+    const unsigned short* Clo;
     int N, Np;
+    int J;                         // slabs per row: N (dense tensor), or the SVD rank
+    const void* wj;                // slab weights [J] (accumulation type); null: u itself
     const double* u_base;
     const long long* stepp;
     long long slot_stride;
@@ -194,19 +197,25 @@ void launch_cvt_f64_to(int dt, const double* src, void* dst, void* dst_lo, long 
 void launch_cvt_lambda(int dt, const double* src, void* dst, long long n, hipStream_t s);
 
 // Dense contraction of a large BF16 tensor, one trajectory: partial sums part[c][i] of
-// y_i = sum_j u_j sum_k C[i][j][k] u_k over chunk c of the (j,k) plane.
+// y_i = sum_j u_j sum_k C[i][j][k] u_k over chunk c of the (j,k) plane; with J slabs and weights
+// wj of their own, the second product of the SVD form (any format).
 struct GemvTile { int threads, unroll, chunk_target; };
 int dense_gemv_variants();
 GemvTile dense_gemv_variant(int idx);
 int dense_gemv_nchunk(int N, GemvTile t);
-void launch_dense_gemv(const void* C, int N, int Np, const double* u_base, const long long* stepp, long long slot_stride,
-                       void* part, int nchunk, GemvTile t, hipStream_t s);
+void launch_dense_gemv(int dt, const GemvJob& jb, GemvTile t, hipStream_t s);
+size_t dense_gemv_lds(int dt, int Np, int slabs);   // slabs: those with weights of their own
 // SVD-ROM first product: w_r = sigma_r U[:,r]^T u over the rows of Ut [Rsp][Np]
 void launch_svd_proj(int dt, const void* Ut, const void* Ut_lo, const void* sigma, int N, int Np, int Rs,
                      const double* u_base, const long long* stepp, long long slot_stride, void* w, hipStream_t s);
 
-GemvJob make_gemv_job(const void* C, int N, int Np, const double* u_base, const long long* stepp, long long slot_stride,
-                      void* part, int nchunk, GemvTile t);
+GemvJob make_gemv_job(int dt, const void* C, const void* Clo, int N, int Np, int J, const void* wj,
+                      const double* u_base, const long long* stepp, long long slot_stride, void* part, int nchunk,
+                      GemvTile t);
+// Rows i0 .. i0 + ni - 1 of V[i][k][r] (src = V[i0][0][0], FP64) as slabs dst[i][r][Np] in the
+// format (k past N is left as it is).
+void launch_slab_rows(int dt, const double* src, int i0, int ni, int N, int R, int Np, void* dst, void* dst_lo,
+                      hipStream_t s);
 // Dense-stiffness apply of a step with, for CP states (np > 0), the projections of the
 // new level (k_contract.hip), one state.
 void launch_helm_proj(int dt, const HelmJob& jb, hipStream_t s);
