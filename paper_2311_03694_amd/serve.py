@@ -78,6 +78,36 @@ def op_key(r: Request) -> Tuple:
 RAMP = 2          # start-up steps a request takes alone (BDF1, BDF2) before joining a pool
 
 
+# ----------------------------------------------------------------------------- operator bytes
+
+def _up(n: int, to: int) -> int:
+    return (n + to - 1) // to * to
+
+
+def operator_bytes(N: int, R: int, kind: str, dtype: str) -> int:
+    """Device bytes of a context for batches (max_batch > 1) with a dense stiffness: the dense
+    tensor, or CP factors of rank R with skew column pairs, in every layout that rom_create
+    stages (rows for one trajectory, tiles for batches)."""
+    eb = {"fp64": 8, "fp32": 4, "bf16": 2, "bf16x3": 4}[dtype]
+    acc = 8 if dtype == "fp64" else 4
+    step = {"fp64": 8, "fp32": 16, "bf16": 32, "bf16x3": 32}[dtype]       # k of one fragment
+    Np, Nt = _up(N, 8), _up(N, 16)
+    helm = 8 * 3 * (N + Nt) * Np                                           # Hinv_1..3, rows and tiles
+    kc = 64 if dtype in ("bf16", "bf16x3") else 32                        # chunk of the tensor's tiles
+    nk = (N + kc - 1) // kc
+    if kind == "dense" and dtype == "bf16":
+        tiles = Nt * nk * N * kc if 2 * N ** 3 <= 100e6 else 0             # one trajectory, small tensors
+        return eb * (N * N * Np + Nt * N * _up(N, step) + tiles) + helm
+    if kind == "dense":                                                    # folded: about half the entries
+        lmax = min(N, (nk // 2 + 1) * kc)
+        return eb * Nt * nk * lmax * kc + helm
+    Rp, P = _up(R, 8), R // 2
+    kw = 8 if dtype == "fp64" else 16                                      # the scatter's fragments
+    rows = 2 * Rp * Np + N * Rp + (P + R) * Np + 3 * (2 * Rp + P + R) * Np # [B|C], A, pairs, times Hinv_1..3
+    tiles = (2 * _up(Rp, 16) + 3 * _up(Rp // 2, 16)) * _up(Np, step) + Nt * _up(Rp, kw)
+    return eb * (rows + tiles) + acc * Rp + helm
+
+
 # ----------------------------------------------------------------------------- backends
 
 class RomBackend:
@@ -98,18 +128,9 @@ class RomBackend:
 
     # -- operators
     def estimate_op_bytes(self, key) -> int:
+        """Device bytes of an operator and its start-up state."""
         N, _seed, kind, dtype = key
-        eb = {"fp64": 8, "fp32": 4, "bf16": 2, "bf16x3": 4}[dtype]
-        Np = (N + 7) // 8 * 8
-        helm = 3 * N * Np * 8
-        if kind == "dense" and dtype == "bf16":
-            return 2 * N * N * Np * eb + helm              # stream layout and the batched kernel's tiles
-        if kind == "dense":                                # folded tensor: about half the entries (small N: all)
-            kc = 64 if dtype == "bf16x3" else 32
-            lmax = min(N, N // 2 + 2 * kc)
-            return (N + 15) // 16 * 16 * lmax * ((N + kc - 1) // kc * kc) * eb + helm
-        R = 2 * N
-        return 2 * 3 * R * Np * eb + helm                  # factors and the projection operators
+        return operator_bytes(N, 2 * N, kind, dtype) + 8 * (6 * N + 16 * (N + 8) + 1024) + (1 << 20)
 
     def host_tensor(self, N, seed):
         k = (N, seed)
