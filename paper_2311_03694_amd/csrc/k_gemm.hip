@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs p) {
 
 // Column-tile width: 1, 2, 3 force FN = 1, 2, 4; 0 (row-major operands) picks the widest that
 // still gives about one block per compute unit.  The tiled step products take FN = 1 unless a
-// caller's knob says otherwise: in every format and at every size measured, more blocks and
+// caller's knob (0 .. 3) says otherwise: in every format and at every size measured, more blocks and
 // waves were worth more than re-using a fragment of A (N = 1000, R = 2000, B = 64 FP32: 22.4,
 // 27.6 and 44 us per step with FN = 1, 2, 4).  So were 4 wavefronts per block against 8 or 16
 // (22.5, 23.2, 25.9 us) and a ring of 8 steps against 6, 12 or 16.

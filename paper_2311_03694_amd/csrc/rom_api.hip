@@ -221,7 +221,7 @@ SkinnyPlan skinny_plan(rom_ctx c, int kind, int plan_Bpad, int Bpad) {
         sp.nsplit = sp.m.nsplit;
     } else {
         sp.engine = 0;
-        sp.g = gemm_plan(M, plan_Bpad, v > 0 ? v : 1);
+        sp.g = gemm_plan(M, plan_Bpad, v >= 0 ? v : 1);
         sp.g.gy = Bpad / (16 * sp.g.fn);
         sp.g.blocks = (sp.g.gx * sp.g.gy + 7) / 8 * 8;
         sp.nsplit = 1;
