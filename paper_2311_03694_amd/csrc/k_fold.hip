@@ -452,6 +452,7 @@ static FoldTile fold_tile(int dt, int v) {
 // Variants: shape v % 3; v / 3 = 0: the split of the plan below, else a fixed one of 1, 2, 3,
 // 4, 6 or 8 pieces per chunk, one piece per block.
 constexpr int kFoldVariants = kFoldShapes * 7;
+int fold_variants() { return kFoldVariants; }
 
 // Shape, pieces per chunk (njr) and pieces a block walks (ppb) of least estimated time.  The
 // estimate is in cycles of one wavefront: a slab costs its shape's cycles times the blocks

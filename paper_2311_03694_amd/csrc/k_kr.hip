@@ -742,7 +742,7 @@ static DensePlan dense_plan_of(int dt, int N, int Np, int Bpad, int variant, siz
 }
 
 DensePlan dense_batched_plan(int N, int Np, int Bpad, int variant, size_t lds_max) {
-    return dense_plan_of(DT_BF16, N, Np, Bpad, variant, lds_max);
+    return dense_plan_of(DT_BF16, N, Np, Bpad, variant < 0 ? variant : variant % dense_batched_variants(), lds_max);
 }
 
 int dense_partials(int dt, int N, int Np, int Bpad, int variant, size_t lds_max) {

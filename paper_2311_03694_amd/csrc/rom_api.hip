@@ -2687,7 +2687,7 @@ extern "C" rom_status rom_query(rom_ctx c, rom_state s, int32_t what, int64_t* v
 extern "C" int32_t rom_tile_count(int32_t kind) {
     switch (kind) {
         case 0: return dense_gemv_variants();
-        case 1: return dense_batched_variants();
+        case 1: return std::max(dense_batched_variants(), fold_variants());
         case 2: case 3: return gemm_variants() + mfma_variants();
         case 4: return 2;
         case 5: return 2;

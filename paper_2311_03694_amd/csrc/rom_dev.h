@@ -425,6 +425,7 @@ struct FoldPlan {
     int gx, gy, blocks;
     size_t lds;
 };
+int fold_variants();
 FoldPlan fold_plan(int dt, const FoldLay& l, int Bpad, int variant, size_t lds_max);
 hipError_t fold_set_lds_limit(size_t lds);
 // Partial tiles sp0 .. sp0 + nsp - 1 of the plan's.
