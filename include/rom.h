@@ -299,8 +299,10 @@ rom_status rom_query(rom_ctx ctx, rom_state st, int32_t what, int64_t *value);
  * 3 = CP scatter, 4 = pair form of the CP projections (0 = general form, 1 = pair form
  * for one trajectory and for batches, ROM_E_UNSUPPORTED if the factors have no skew column
  * pairs), 5 = resident runs of one-trajectory CP steps (0 = off: every step through the
- * per-step kernels; 1 or -1 = on where the operator fits on chip).  Kind 0 concerns BF16
- * tensors of more than 100 MB; the other tensors' stream has no variants.  value: an index into
+ * per-step kernels; 1 or -1 = on where the operator fits on chip).  Kind 0 selects the kernel
+ * of BF16 tensors of more than 100 MB and of SVD slabs of more than 200 MB; for the other
+ * tensors and slabs it sets the number of pieces that their stream is cut into.  Either way
+ * the partial sums, and with them the last bits of the results, follow it.  value: an index into
  * that kernel's variant table (see rom_tile_count), in kind 1 modulo the number of variants
  * of the format's kernel; -1 restores the built-in choice (for
  * kind 4: the pair form for one trajectory whenever the factors allow it, the general
