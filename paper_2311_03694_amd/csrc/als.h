@@ -13,7 +13,7 @@ void launch_als_unfold(int N, int np, int layout, const double* C, double* U, hi
 void launch_als_transpose(int N, int R, int np, const double* F, double* Ft, hipStream_t s);
 // T [Bn][R] = U F in FP64 for U [Bn][np] (16-byte aligned, Bn = N^2, np a multiple of 8; its
 // columns past N are finite) and F [N][R]: ncg groups of g 16-column tiles and nrr row
-// ranges.  ok is false when a tile's columns do not fit in LDS (np > 1000) or the allowance
+// ranges.  ok is false when a tile's columns do not fit in LDS (np > 1280) or the allowance
 // is refused.
 struct AlsProductPlan {
     int g, ncg, nrr;

@@ -1010,7 +1010,7 @@ struct AlsSlab {
 
 // The tensor-factor product of the ALS sweeps, T[row][m] = sum_c U[row][c] F[c][m]: on its own
 // FP64 MFMA kernel (k_als.hip; its LDS allowance is set here, before any capture), else
-// (np > 1000) on the skinny GEMM with the transposed factor.  The skinny GEMM reads whole
+// (np > 1280) on the skinny GEMM with the transposed factor.  The skinny GEMM reads whole
 // 16-row tiles of padded rows; the kernel reads a tensor whose rows are whole 8-k steps, and
 // 16-byte aligned, in place.
 struct AlsProduct {
