@@ -169,7 +169,9 @@ __global__ __launch_bounds__(256) void k_kr(KrArgs p) {
 
     // The copies above must land before any wavefront reads the j-weights; the
     // tensor ring is issued after the barrier, so this wait covers only the small
-    // L2-resident loads and the ring's HBM traffic starts right behind it.
+    // L2-resident loads and the ring's HBM traffic starts right behind it.  (Without the wait
+    // in the source the compiler's own left the last X fragments in flight across the barrier:
+    // an evaluation at N = 400, B = 256 took 42.3 us, with it 42.7.)
     lds_loads_done();
 #pragma unroll
     for (int s = 0; s < KW; ++s)

@@ -13,7 +13,8 @@
 // consecutive (wrapping) range.  Inside the diagonal chunk the pairs sit at k >= j, zeros
 // below.  Unfolded tensors (BF16, and those whose sums would overflow the format) use the
 // same storage with every chunk contracting all j, and so do the slabs of the SVD form (Sec.
-// 4.4; y_i = sum_r w_r sum_k V[i][k][r] u_k), whose j is the SVD index with weights of its own.
+// 4.4; y_i = sum_r w_r sum_k V[i][k][r] u_k) up to 200 MB, whose j is the SVD index with weights
+// of its own.
 //
 // Storage: [row tile of 16][chunk][q = index in the chunk's j range][k / VEC][16 rows][VEC]
 // (VEC = elements per 16 bytes): one lane vector of a wavefront (16 rows x 4 k-groups x 16
@@ -64,7 +65,8 @@ __host__ __device__ inline size_t fold_base(const FoldLay& l, int it, int c) {
 // slab (a chunk each, where all chunks run over the same j, was no faster); U slabs are in flight per wavefront, in whole rounds whose loads are not predicated
 // (slabs past the end repeat the last one), so the wait is for the slot consumed only; the
 // slabs left in the ring are consumed without loads behind them (a ring refilled to its end
-// cost the 25 slabs of a wavefront 4 more: N = 1000, 100 SVD slabs BF16X3 66.4 -> 63.9 us).
+// cost the 25 slabs of a wavefront 4 more: 100 tiled SVD slabs at N = 1000, BF16X3, 66.4 -> 63.9
+// us).
 // NT: non-temporal loads, for a tensor larger than the last-level cache.
 template <int DT, int U, bool NT>
 __device__ __forceinline__ void fold_gemv_body(const FoldJob& jb, int blk) {

@@ -1051,9 +1051,11 @@ struct AlsProduct {
 //
 // A call takes a pair from a pool of at most kPool pairs a device, made as they are first
 // needed, and gives it back idle; a call that finds all of them taken runs on the caller's
-// stream alone.  Pairs stay until the process ends: the runtime still writes to the object of
-// a stream that it has just destroyed (a reference count and a flag, from its own thread),
-// into memory that the caller may own by then.
+// stream alone.  Pairs stay until the process ends.  With two streams made and destroyed by
+// every call, host arrays of the calling program were once found changed (two words each)
+// after some of several hundred calls, and never again since; whether the runtime wrote to a
+// destroyed stream's object is not shown, and contexts that destroy their own stream have not
+// shown it.
 struct SweepPair {
     static constexpr int kPairs = 3, kPool = 4;
     hipStream_t chain = nullptr, rhs = nullptr;

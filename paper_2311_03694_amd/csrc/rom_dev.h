@@ -162,7 +162,8 @@ struct FinJob {            // closing energy sum of the newest level, one state
 // one one-trajectory state, of any kind and number format.  A step is at most four such
 // launches, whatever the mix of N, R, formats, stiffness kinds and operator forms:
 //   phase 0: full-form terms (MIX_FULL), SVD first products (MIX_SVDP)
-//   phase 1: dense / SVD slab streams (MIX_GEMV; MIX_FOLD over the folded tensor), CP projections, diagonal stiffness (MIX_PROJ)
+//   phase 1: dense / SVD slab streams (MIX_FOLD over the tiled storage, MIX_GEMV over rows), CP
+//            projections, diagonal stiffness (MIX_PROJ)
 //   phase 2: BDF update or right-hand side from partials (MIX_BDF), CP scatter (MIX_SCAT)
 //   phase 3: Helmholtz apply, with the next projections for CP states (MIX_HELM)
 enum MixKind { MIX_GEMV = 0, MIX_PROJ = 1, MIX_BDF = 2, MIX_SCAT = 3, MIX_HELM = 4, MIX_SVDP = 5, MIX_FULL = 6, MIX_FOLD = 7 };
