@@ -375,7 +375,8 @@ size_t noalloc_bytes(rom_ctx c, int B) {
     const size_t Bpad = (B + 15) / 16 * 16, ab = acc_bytes(c->dtype), eb = elem_bytes(c->dtype);
     size_t off = 0;
     if (c->dense) {
-        const int np = dense_partials(c->dtype, c->N, c->Np, (int)Bpad, c->tile[1], c->lds_max);
+        const int v = c->tile[1] < 0 ? -1 : c->tile[1] % dense_batched_variants();
+        const int np = dense_partials(c->dtype, c->N, c->Np, (int)Bpad, v, c->lds_max);
         off = align256((size_t)np * Bpad * c->N * ab);
     } else {
         const SkinnyPlan pp = skinny_plan(c, 2, (int)Bpad, (int)Bpad), ps = skinny_plan(c, 3, (int)Bpad, (int)Bpad);

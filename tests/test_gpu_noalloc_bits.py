@@ -58,3 +58,15 @@ def test_cp_in_slices(torch_gpu, dt, N, R, B, knob):
     for kind in (2, 3):
         rg.rom_set_tile(rom.handle, kind, knob)
     _check(torch_gpu, rom, N, B)
+
+
+@pytest.mark.parametrize("dt", ["fp64", "fp32", "bf16", "bf16x3"])
+def test_every_dense_variant(torch_gpu, dt):
+    """Each tile choice of the batched contraction, the index past the BF16 kernels' own included."""
+    N, B = 70, 20
+    C = np.random.default_rng(N).standard_normal((N, N, N)) / N
+    for v in range(rg.rom_tile_count(1)):
+        print(f"[case] noalloc bits dense N={N} B={B} {dt} variant {v}", flush=True)
+        rom = rg.Rom(N, 1e-3, 1e-3, romsynth.stiffness_diag(N), C=C, dtype=dt, max_batch=B)
+        rg.rom_set_tile(rom.handle, 1, v)
+        _check(torch_gpu, rom, N, B)
